@@ -657,7 +657,7 @@ extern "C" attt_status attt_ngram_set_weights(void* const* sets, const int32_t* 
 // ------------------------------------------------------------------------------------------
 namespace {
 
-// float32 backward (three VALU GEMMs) blocking: rows per block and vocab columns per staged dZ
+// float32 backward (three GEMMs) blocking: rows per block and vocab columns per staged dZ
 // chunk. The bf16 backward stages nothing of that shape (ce_fused.hip).
 constexpr int64_t kCeRowBlock = 8192;
 constexpr int64_t kCeVocabChunk = 131072;
@@ -668,7 +668,8 @@ struct CePlan {
   int slices = 0, consumers = 0, passes = 0, ksplit = 1, slots = 0, items_max = 0, sync_ints = 0;
   size_t off_part = 0, off_label = 0, off_lse = 0, off_coef = 0, off_rowloss = 0;
   size_t off_flag = 0, off_sync = 0, off_sync2 = 0, off_ring = 0, off_split = 0;
-  size_t off_wt = 0, off_dz = 0, total = 0;
+  size_t off_wt = 0, off_dz = 0, off_dhp = 0, total = 0;
+  int dh_splits = 1;
 };
 
 CeGemmShape mfma_shape(int64_t rows, int64_t cols) {
@@ -745,6 +746,16 @@ CePlan ce_plan(int64_t N, int64_t d, int64_t V, int32_t dtype, bool grad, bool h
     } else {
       P.off_dz = o;
       o += align256((size_t)P.R * P.Vc * 4);
+      // dH has few 64 x 64 tiles where rows and d are small (32 at 512 x 256), each with the whole
+      // vocabulary to walk: below two workgroups per CU its range is split, at least 128 per split.
+      // At 512 x 256 x 4096, 32 workgroups took 290 us.
+      const int64_t tiles = ceil_div(P.R, 64) * ceil_div(d, 64);
+      if (tiles < 512)
+        P.dh_splits = (int)std::max<int64_t>(1, std::min<int64_t>({ceil_div(512, tiles), P.Vc / 128, 32}));
+      if (P.dh_splits > 1) {
+        P.off_dhp = o;
+        o += align256((size_t)P.dh_splits * P.R * d * 4);
+      }
     }
   }
   P.total = std::max<size_t>(o, 256);
@@ -912,7 +923,7 @@ extern "C" attt_status attt_weighted_ce_fwd_bwd_ex(const void* hidden, const voi
   };
 
   if (dtype == ATTT_F32) {
-    // float32: three VALU GEMMs, dZ = coef (softmax - onehot) staged per (row block, vocab chunk)
+    // float32: three GEMMs, dZ = coef (softmax - onehot) staged per (row block, vocab chunk)
     st = forward(nullptr);
     if (st || !grad) return st;
     float* dz = reinterpret_cast<float*>(ws + P.off_dz);
@@ -925,7 +936,8 @@ extern "C" attt_status attt_weighted_ce_fwd_bwd_ex(const void* hidden, const voi
                                  s),
                 "ce_bwd_dz");
         HIP_TRY(launch_ce_bwd_dh(dz, (int)P.Vc, static_cast<const float*>(lm_head), (int)r0, (int)R, (int)d, (int)c0,
-                                 (int)round_up(width, 16), (int)V, static_cast<float*>(grad_hidden), c0 == 0, s),
+                                 (int)round_up(width, 16), (int)V, P.dh_splits,
+                                 reinterpret_cast<float*>(ws + P.off_dhp), static_cast<float*>(grad_hidden), c0 == 0, s),
                 "ce_bwd_dh");
       }
     }
@@ -1073,7 +1085,8 @@ LoraPlan lora_plan(const attt_lora_problem* p, int32_t count, int32_t dtype) {
     if (!placed) P.chunks.push_back({i});
   }
   // Row splits of pass 2: about 512 rows (eight steps of 64) per workgroup, at most 16 splits;
-  // shorter chains of dependent loads for more float32 partials.
+  // shorter chains of dependent loads for more float32 partials. Float32: 128 rows (its waves split
+  // them again), since its problems are small and the splits are what fills the chip.
   size_t o = 0;
   for (int32_t i = 0; i < count; ++i) {
     const attt_lora_problem& q = p[i];
@@ -1081,7 +1094,7 @@ LoraPlan lora_plan(const attt_lora_problem* p, int32_t count, int32_t dtype) {
     LoraProb& Q = P.prob[i];
     Q.rp = tiles[i] * 16;
     Q.rows_pad = (int32_t)round_up(q.rows, kLoraRowTile);
-    Q.splits = std::max(1, std::min(16, Q.rows_pad / 512));
+    Q.splits = std::max(1, std::min(16, Q.rows_pad / (dtype == ATTT_BF16 ? 512 : 128)));
     Q.bt_off = (int64_t)o;  o += align256((size_t)Q.rp * q.d_out * esz);
     // pass-1 results U^T and dU^T: float32, or for bf16 two planes (hi, lo) per rank tile
     Q.ut_off = (int64_t)o;  o += align256((size_t)Q.rp * Q.rows_pad * esz * lt_planes);
@@ -1230,7 +1243,7 @@ extern "C" attt_status attt_lora_grad(const attt_lora_problem* problems, int32_t
   // pass 1: jobs sorted by tile count, each launch specialised on its batch's largest count
   std::stable_sort(p1.begin(), p1.end(), [](const LoraP1Job& a, const LoraP1Job& b) { return a.nt > b.nt; });
   st = lora_launch_all(
-      p1, [](const LoraP1Job& J) { return J.rows_pad / kLoraP1Rows; },
+      p1, [&](const LoraP1Job& J) { return J.rows_pad / (dtype == ATTT_BF16 ? kLoraP1Rows : kLoraP1RowsF32); },
       [&](const LoraP1Batch& b, int n) { return launch_lora_pass1(dtype, b.j[0].nt, b, n, ws, s); }, "lora_u_du");
   if (st) return st;
   st = lora_launch_all(

@@ -22,9 +22,9 @@
 //
 // bf16 GEMMs: MFMA v_mfma_f32_32x32x16_bf16 through the core in gemm_core.hpp (256x256 tiles on 8
 // waves, 128x128 on 4 for small problems; XCD-aware tile order).
-// f32 path: plain VALU tiles (64x64, 4x4 per thread) running the three-GEMM algorithm (forward,
-// dZ = coef (softmax - onehot) staged per block of rows and vocabulary, dH = dZ W); it serves the
-// float32 configuration.
+// f32 path: 64x64 tiles on the float32 MFMA running the three-GEMM algorithm (forward,
+// dZ = coef (softmax - onehot) staged per block of rows and vocabulary, dH = dZ W, its vocabulary
+// range split over workgroups when there are few tiles); it serves the float32 configuration.
 #include "common.hpp"
 #include "gemm_core.hpp"
 #include "internal.hpp"
@@ -179,82 +179,131 @@ __global__ __launch_bounds__(256) void ce_coef_kernel(CeEpBatch b, const float* 
 }
 
 // ------------------------------------------------------------------------------------------
-// f32 path: VALU tiles of 64x64, 256 threads with 4x4 outputs each.
+// f32 path: 64x64 tiles on v_mfma_f32_32x32x2_f32 (float32 products and sums), 4 waves with one
+// 32x32 block each. K advances 32 per step through two LDS buffers; the next step's global loads
+// are in flight while the current one computes, and a step costs one barrier. These GEMMs are
+// small (1 GFLOP at 512 x 256 x 4096) and bound by the latency of their K walk and by how many
+// tiles there are, not by the matrix cores. At that size forward and dZ take 17 us each (25 with
+// VALU tiles and no prefetch) and dH 16 us plus 4 for its split sums (290 us unsplit, 32 workgroups).
 // ------------------------------------------------------------------------------------------
-constexpr int kVT = 64, kVK = 16;
+constexpr int kVT = 64, kVK = 32;
+constexpr int kVP = kVK + 4;   // LDS pitch (floats) of a row-major [64][32] operand tile
+constexpr int kVPn = kVT + 8;  // LDS pitch of a [32][64] tile (rows 4 apart fall in other banks)
+constexpr int kVTile = kVT * kVP > kVK * kVPn ? kVT * kVP : kVK * kVPn;
 
-// acc += A[0:64, 0:K] * op(B): NT reads B as [64 cols, K] (K-contiguous), NN as [K, 64 cols].
+// acc = A[0:64, 0:K] * op(B) of this wave's 32x32 block: NT reads B as [64, K] (K-contiguous), NN
+// as [K, 64]. Rows at or past mval (nval columns) and K past kval_a (A) or kval_b (B, NN) read as
+// zero. The k slots of an MFMA pair follow the 16-byte reads of a row-major tile (slot i of lane
+// half h is k = 8 j + 4 h + i), the same order for both operands.
 template <bool NN>
-__device__ __forceinline__ void valu_mainloop(const float* __restrict__ A, int64_t lda, int mval,
-                                              const float* __restrict__ B, int64_t ldb, int nval,
-                                              int K, int kval_b, float (&acc)[4][4]) {
-  __shared__ float As[kVK][kVT + 4];
-  __shared__ float Bs[kVK][kVT + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  for (int k0 = 0; k0 < K; k0 += kVK) {
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (lr < mval && k0 + lk < K) a = *reinterpret_cast<const float4*>(A + (int64_t)lr * lda + k0 + lk);
-    As[lk + 0][lr] = a.x; As[lk + 1][lr] = a.y; As[lk + 2][lr] = a.z; As[lk + 3][lr] = a.w;
-    if (!NN) {
-      float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (lr < nval && k0 + lk < K) b = *reinterpret_cast<const float4*>(B + (int64_t)lr * ldb + k0 + lk);
-      Bs[lk + 0][lr] = b.x; Bs[lk + 1][lr] = b.y; Bs[lk + 2][lr] = b.z; Bs[lk + 3][lr] = b.w;
-    } else {
-      const int kr = tid >> 4, nc = (tid & 15) * 4;
-      float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (k0 + kr < kval_b && nc < nval) b = *reinterpret_cast<const float4*>(B + (int64_t)(k0 + kr) * ldb + nc);
-      Bs[kr][nc + 0] = b.x; Bs[kr][nc + 1] = b.y; Bs[kr][nc + 2] = b.z; Bs[kr][nc + 3] = b.w;
+__device__ __forceinline__ void f32_mainloop(const float* __restrict__ A, int64_t lda, int mval,
+                                             const float* __restrict__ B, int64_t ldb, int nval, int k_begin,
+                                             int k_end, int kval_b, float (&lds)[2][2][kVTile], f32x16& acc) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hi = lane >> 5;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  const int lr = tid >> 3, lk = (tid & 7) * 4;   // row-major tiles: rows lr and lr + 32, k lk .. +3
+  const int kr = tid >> 4, nc = (tid & 15) * 4;  // [k][64] tiles: k kr and kr + 16, columns nc .. +3
+  f32x4 ra[2], rb[2];
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int row = lr + 32 * u;
+      ra[u] = row < mval && k0 + lk < k_end ? *reinterpret_cast<const f32x4*>(A + (int64_t)row * lda + k0 + lk) : zero;
+      if (!NN) {
+        rb[u] = row < nval && k0 + lk < k_end ? *reinterpret_cast<const f32x4*>(B + (int64_t)row * ldb + k0 + lk) : zero;
+      } else {
+        const int k = k0 + kr + 16 * u;
+        rb[u] = k < k_end && k < kval_b && nc < nval ? *reinterpret_cast<const f32x4*>(B + (int64_t)k * ldb + nc) : zero;
+      }
     }
-    __syncthreads();
+  };
+  auto store = [&](int buf) {
 #pragma unroll
-    for (int k = 0; k < kVK; ++k) {
-      float a4[4], b4[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a4[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b4[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a4[i], b4[j], acc[i][j]);
+    for (int u = 0; u < 2; ++u) {
+      *reinterpret_cast<f32x4*>(&lds[buf][0][(lr + 32 * u) * kVP + lk]) = ra[u];
+      if (!NN)
+        *reinterpret_cast<f32x4*>(&lds[buf][1][(lr + 32 * u) * kVP + lk]) = rb[u];
+      else
+        *reinterpret_cast<f32x4*>(&lds[buf][1][(kr + 16 * u) * kVPn + nc]) = rb[u];
     }
+  };
+  load(k_begin);
+  store(0);
+  int buf = 0;
+  for (int k0 = k_begin; k0 < k_end; k0 += kVK, buf ^= 1) {
+    // this step's tiles are stored, and every wave is done with the other buffer
     __syncthreads();
+    const bool more = k0 + kVK < k_end;
+    if (more) load(k0 + kVK);
+    const float* As = &lds[buf][0][(wm * 32 + l32) * kVP + 4 * hi];
+    const float* Bs = &lds[buf][1][NN ? 4 * hi * kVPn + wn * 32 + l32 : (wn * 32 + l32) * kVP + 4 * hi];
+#pragma unroll
+    for (int j = 0; j < kVK / 8; ++j) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(As + 8 * j);
+      f32x4 b;
+      if (!NN) {
+        b = *reinterpret_cast<const f32x4*>(Bs + 8 * j);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = Bs[(8 * j + i) * kVPn];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+    }
+    if (more) store(buf ^ 1);
   }
 }
 
+// Forward, transposed like the bf16 form (z^T = W h^T): each lane holds 16 logits of one token, and
+// a token's (max, sum exp) meets across the lane pair and the two waves of its columns.
 __global__ __launch_bounds__(256) void ce_fwd_f32_kernel(const float* __restrict__ h,
                                                          const float* __restrict__ W,
                                                          const int32_t* __restrict__ labels, int N,
                                                          int d, int V, int tiles_m,
                                                          float2* __restrict__ partials, int n_vb,
                                                          float* __restrict__ label_logit) {
+  __shared__ __align__(16) float lds[2][2][kVTile];
+  __shared__ float red[2][2][kVT];  // (max, sum) of each wave row's half of the tile
   const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
-  const int m0 = tm * kVT, n0 = tn * kVT;
-  float acc[4][4];
-  valu_mainloop<false>(h + (int64_t)m0 * d, d, N - m0, W + (int64_t)n0 * d, d, V - n0, d, 0, acc);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    float mx = -INFINITY;
-    for (int j = 0; j < 4; ++j)
-      if (n0 + tx * 4 + j < V) mx = fmaxf(mx, acc[i][j]);
-    mx = group_max<16>(mx);
-    float s = 0.0f;
-    if (mx != -INFINITY)
-      for (int j = 0; j < 4; ++j)
-        if (n0 + tx * 4 + j < V) s += expf(acc[i][j] - mx);
-    s = group_sum<16>(s);
-    if (row < N) {
-      if (tx == 0) partials[(int64_t)row * n_vb + tn] = make_float2(mx, s);
-      const int y = labels[row];
-      for (int j = 0; j < 4; ++j)
-        if (n0 + tx * 4 + j == y) label_logit[row] = acc[i][j];
-      // outside the contract: the row's loss term becomes NaN instead of reading stale memory
-      if ((y < 0 || y >= V) && tn == 0 && tx == 0) label_logit[row] = __int_as_float(0x7FC00000);
+  const int t0 = tm * kVT, v0 = tn * kVT;
+  f32x16 acc;
+  f32_mainloop<false>(W + (int64_t)v0 * d, d, V - v0, h + (int64_t)t0 * d, d, N - t0, 0, d, 0, lds, acc);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int tl = wn * 32 + (lane & 31), row = t0 + tl;
+  const int vb = v0 + wm * 32;
+  const int y = row < N ? labels[row] : -1;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (vb + mfma_row(r, lane) < V) mx = fmaxf(mx, acc[r]);
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  float s = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int v = vb + mfma_row(r, lane);
+    if (v < V) {
+      if (mx != -INFINITY) s += expf(acc[r] - mx);
+      if (v == y) label_logit[row] = acc[r];
     }
+  }
+  s += __shfl_xor(s, 32, 64);
+  if (lane < 32) {
+    red[0][wm][tl] = mx;
+    red[1][wm][tl] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < kVT && t0 + (int)threadIdx.x < N) {
+    const int t = t0 + threadIdx.x;
+    float m = red[0][0][threadIdx.x], sum = red[1][0][threadIdx.x];
+    lse_merge(m, sum, red[0][1][threadIdx.x], red[1][1][threadIdx.x]);
+    partials[(int64_t)t * n_vb + tn] = make_float2(m, sum);
+    // outside the contract: the row's loss term becomes NaN instead of reading stale memory
+    const int yt = labels[t];
+    if (tn == 0 && (yt < 0 || yt >= V)) label_logit[t] = __int_as_float(0x7FC00000);
   }
 }
 
@@ -266,49 +315,75 @@ __global__ __launch_bounds__(256) void ce_dz_f32_kernel(const float* __restrict_
                                                         int R, int d, int c0, int cend, int V,
                                                         int tiles_m, float* __restrict__ dz,
                                                         int ldz) {
+  __shared__ __align__(16) float lds[2][2][kVTile];
   const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
   const int m0 = tm * kVT, n0 = tn * kVT;
-  float acc[4][4];
-  valu_mainloop<false>(h + (int64_t)(r0 + m0) * d, d, R - m0, W + (int64_t)(c0 + n0) * d, d,
-                       cend - (c0 + n0), d, 0, acc);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  for (int i = 0; i < 4; ++i) {
-    const int rl = m0 + ty * 4 + i;
+  f32x16 acc;  // transposed: vocabulary entries on the rows, tokens on the columns
+  f32_mainloop<false>(W + (int64_t)(c0 + n0) * d, d, cend - (c0 + n0), h + (int64_t)(r0 + m0) * d, d, R - m0, 0, d, 0,
+                      lds, acc);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rl = m0 + (wave & 1) * 32 + (lane & 31);
+  if (rl >= R) return;
+  const int row = r0 + rl;
+  const float l = lse[row], c = coef[row];
+  const int y = labels[row];
+  const bool bad = y < 0 || y >= V;  // outside the contract: NaN gradient row
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int cl = n0 + (wave >> 1) * 32 + mfma_row(4 * q, lane);
+    f32x4 g;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int col = c0 + cl + e;
+      g[e] = 0.0f;
+      if (col < V) g[e] = bad ? __int_as_float(0x7FC00000) : c * (expf(acc[4 * q + e] - l) - (col == y ? 1.0f : 0.0f));
+    }
+    *reinterpret_cast<f32x4*>(dz + (int64_t)rl * ldz + cl) = g;
+  }
+}
+
+// dH rows [r0, r0 + R) (+)= dZ chunk . W[c0 : c0 + K]. With `splits` > 1 the K range of a tile is cut
+// into splits of `kper` (a multiple of kVK) whose sums go to `part` [splits][R][d]; a second kernel
+// adds them in order.
+__global__ __launch_bounds__(256) void ce_dh_f32_kernel(const float* __restrict__ dz, int ldz,
+                                                        const float* __restrict__ W, int r0, int R,
+                                                        int d, int c0, int K, int kval,
+                                                        int tiles_m, int tiles, int kper,
+                                                        float* __restrict__ part, float* __restrict__ grad,
+                                                        int first) {
+  __shared__ __align__(16) float lds[2][2][kVTile];
+  const int sp = blockIdx.x / tiles, tile = blockIdx.x - sp * tiles;
+  const int tm = tile % tiles_m, tn = tile / tiles_m;
+  const int m0 = tm * kVT, n0 = tn * kVT;
+  f32x16 acc;
+  f32_mainloop<true>(dz + (int64_t)m0 * ldz, ldz, R - m0, W + (int64_t)c0 * d + n0, d, d - n0, sp * kper,
+                     min(K, sp * kper + kper), kval, lds, acc);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = n0 + (wave & 1) * 32 + (lane & 31);
+  if (col >= d) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int rl = m0 + (wave >> 1) * 32 + mfma_row(r, lane);
     if (rl >= R) continue;
-    const int row = r0 + rl;
-    const float l = lse[row], c = coef[row];
-    const int y = labels[row];
-    const bool bad = y < 0 || y >= V;  // outside the contract: NaN gradient row
-    for (int j = 0; j < 4; ++j) {
-      const int cl = n0 + tx * 4 + j, col = c0 + cl;
-      float g = 0.0f;
-      if (col < V) g = bad ? __int_as_float(0x7FC00000) : c * (expf(acc[i][j] - l) - (col == y ? 1.0f : 0.0f));
-      dz[(int64_t)rl * ldz + cl] = g;
+    if (part) {
+      part[((int64_t)sp * R + rl) * d + col] = acc[r];
+    } else {
+      const int64_t o = (int64_t)(r0 + rl) * d + col;
+      grad[o] = first ? acc[r] : grad[o] + acc[r];
     }
   }
 }
 
-__global__ __launch_bounds__(256) void ce_dh_f32_kernel(const float* __restrict__ dz, int ldz,
-                                                        const float* __restrict__ W, int r0, int R,
-                                                        int d, int c0, int K, int kval,
-                                                        int tiles_m, float* __restrict__ grad,
-                                                        int first) {
-  const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
-  const int m0 = tm * kVT, n0 = tn * kVT;
-  float acc[4][4];
-  valu_mainloop<true>(dz + (int64_t)m0 * ldz, ldz, R - m0, W + (int64_t)c0 * d + n0, d, d - n0, K,
-                      kval, acc);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  for (int i = 0; i < 4; ++i) {
-    const int rl = m0 + ty * 4 + i;
-    if (rl >= R) continue;
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col >= d) continue;
-      const int64_t o = (int64_t)(r0 + rl) * d + col;
-      grad[o] = first ? acc[i][j] : grad[o] + acc[i][j];
-    }
-  }
+// grad [n] (+)= sum over the splits of part [splits][n], in split order; n is a multiple of 8.
+__global__ __launch_bounds__(256) void ce_dh_reduce_kernel(const float* __restrict__ part, int splits, int64_t n,
+                                                           float* __restrict__ grad, int first) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= n) return;
+  f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int sp = 0; sp < splits; ++sp) s += *reinterpret_cast<const f32x4*>(part + sp * n + i);
+  if (!first) s += *reinterpret_cast<const f32x4*>(grad + i);
+  *reinterpret_cast<f32x4*>(grad + i) = s;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -555,12 +630,18 @@ hipError_t launch_ce_bwd_dz(const float* h, const float* W, const int32_t* label
 }
 
 hipError_t launch_ce_bwd_dh(const float* dz, int ldz, const float* W, int r0, int R, int d, int c0, int K, int V,
-                            float* grad, bool first, hipStream_t s) {
+                            int splits, float* part, float* grad, bool first, hipStream_t s) {
   if (R == 0) return hipSuccess;
   const int tm = (R + kVT - 1) / kVT, tn = (d + kVT - 1) / kVT;
+  const int kper = ((K + splits - 1) / splits + kVK - 1) / kVK * kVK;
   KernelTimer tt(K_CE_BWD_DH, s);
-  hipLaunchKernelGGL(ce_dh_f32_kernel, dim3(tm * tn), dim3(256), 0, s, dz, ldz, W, r0, R, d, c0, K, V - c0, tm, grad,
-                     first ? 1 : 0);
+  hipLaunchKernelGGL(ce_dh_f32_kernel, dim3(tm * tn * splits), dim3(256), 0, s, dz, ldz, W, r0, R, d, c0, K, V - c0,
+                     tm, tm * tn, kper, splits > 1 ? part : nullptr, grad, first ? 1 : 0);
+  if (splits > 1) {
+    const int64_t n = (int64_t)R * d;
+    hipLaunchKernelGGL(ce_dh_reduce_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, part, splits, n,
+                       grad + (int64_t)r0 * d, first ? 1 : 0);
+  }
   return hipGetLastError();
 }
 

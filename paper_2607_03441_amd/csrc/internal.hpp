@@ -236,12 +236,13 @@ hipError_t launch_ce_row_final(int r0, int R, const float* sig_part, int n_vb, c
                                float* sa, float* sb, hipStream_t s);
 // float32 backward: dZ chunk, rows [r0, r0+R) x vocab [c0, c0+Vc) of coef * (softmax - onehot)
 // into staging [R, ldz], zero past V; then dH rows [r0, r0+R) (+)= dZ chunk . W[c0 : c0+K]
-// (first: overwrite).
+// (first: overwrite). splits > 1: the K range cut over that many workgroups per tile, their sums
+// through part [splits][R][d].
 hipError_t launch_ce_bwd_dz(const float* h, const float* W, const int32_t* labels, const float* lse,
                             const float* coef, int r0, int R, int d, int c0, int Vc, int V, float* dz, int ldz,
                             hipStream_t s);
 hipError_t launch_ce_bwd_dh(const float* dz, int ldz, const float* W, int r0, int R, int d, int c0, int K, int V,
-                            float* grad, bool first, hipStream_t s);
+                            int splits, float* part, float* grad, bool first, hipStream_t s);
 
 // Fused bf16 backward (ce_fused.hip): one persistent cooperative grid of 8 x kCeTeam workgroups,
 // one per CU, in XCD teams of kCeTeam producers and consumers sharing a ring of bf16 tiles.
@@ -283,6 +284,7 @@ hipError_t launch_ce_fused_nan(const int* sync, float* loss, int E, float* lse, 
 // ---- LoRA ------------------------------------------------------------------------------
 constexpr int kLoraRowTile = 128;  // row padding of the transposed pass-1 results
 constexpr int kLoraP1Rows = 64;    // pass-1 rows per workgroup (16 per wave)
+constexpr int kLoraP1RowsF32 = 16; // the same, float32 (the waves split the contraction)
 constexpr int kLoraKBlock = 128;   // pass-1 contraction step
 constexpr int kLoraColTile = 64;   // pass-2 output columns per workgroup
 constexpr int kLoraTStep = 64;     // pass-2 rows per step

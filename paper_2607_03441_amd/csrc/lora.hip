@@ -22,7 +22,7 @@
 //     Rows are split into `splits` ranges whose float32 partials go to the workspace.
 //   Reduce (lora_reduce_kernel): sums the split partials in a fixed order and adds them to
 //     dA [r, d_in] and dB [d_out, r]. No float atomics: results are bit-reproducible.
-// The float32 path runs the same jobs with plain VALU loops.
+// The float32 path runs the same jobs on the float32 MFMA.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -288,46 +288,132 @@ __global__ __launch_bounds__(256) void lora_p2_bf16_kernel(LoraP2Batch b, int ma
 }
 
 // ------------------------------------------------------------------------------------------
-// f32 passes (VALU), same jobs and workspace layout
+// f32 passes on v_mfma_f32_16x16x4_f32, same jobs and workspace layout. Float32 adapters are small
+// (rank 8 on 512 rows of 256), so both passes are bound by latency: every operand is a 16-byte load
+// straight from memory in the order the MFMAs use it, four chunks of 16 in flight, and the four waves
+// of a workgroup split the contraction and meet in LDS in a fixed order. (One thread per output
+// walking its whole contraction took 128 and 262 us at that shape; these take 4.0 and 4.6.)
 // ------------------------------------------------------------------------------------------
+__device__ __forceinline__ f32x4 bload_f4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+
+// 16 rows per workgroup; wave w takes the 16-wide k chunks w, w + 4, ... Slot i of lane group g in a
+// chunk is k = 16 j + 4 g + i for both operands.
 __global__ __launch_bounds__(256) void lora_p1_f32_kernel(LoraP1Batch b, uint8_t* __restrict__ ws) {
   const int ji = find_job(b, (int)blockIdx.x);
   const LoraP1Job& J = b.j[ji];
-  const int rt = (int)blockIdx.x - J.b_begin;
-  const float* src = static_cast<const float*>(J.src);
-  for (int idx = threadIdx.x; idx < kLoraP1Rows * 16 * J.nt; idx += blockDim.x) {
-    const int rl = idx % kLoraP1Rows, c = idx / kLoraP1Rows;  // c: rank within the job
-    const int t = c >> 4, cr = c & 15;
-    const int row = rt * kLoraP1Rows + rl;
-    float s = 0.0f;
-    if (row < J.rows && cr < J.t[t].valid) {
-      const float* xr = src + (int64_t)row * J.kdim;
-      const float* op = static_cast<const float*>(J.t[t].op) + (int64_t)cr * J.kdim;
-      for (int k = 0; k < J.kdim; ++k) s = fmaf(xr[k], op[k], s);
+  const int kdim = J.kdim, nt = J.nt;
+  const int row0 = ((int)blockIdx.x - J.b_begin) * kLoraP1RowsF32;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nrows = max(0, min(16, J.rows - row0));
+  const float* src = static_cast<const float*>(J.src) + (int64_t)min(row0, J.rows) * kdim;
+  const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(src, nrows * kdim * 4);
+  __amdgpu_buffer_rsrc_t ro[kLoraMaxTiles];
+#pragma unroll
+  for (int t = 0; t < kLoraMaxTiles; ++t)
+    ro[t] = buffer_rsrc(t < nt ? J.t[t].op : src, t < nt ? J.t[t].valid * kdim * 4 : 0);
+  f32x4 acc[kLoraMaxTiles];
+#pragma unroll
+  for (int t = 0; t < kLoraMaxTiles; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kb = 16 * wave; kb < kdim; kb += 256) {
+    uint32_t off[4];
+    f32x4 x[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int k = kb + 64 * c + 4 * g;
+      off[c] = k < kdim ? (uint32_t)(l16 * kdim + k) * 4u : kOOB;
+      x[c] = bload_f4(rs, off[c]);
     }
-    reinterpret_cast<float*>(ws + J.t[t].out_off)[(int64_t)cr * J.rows_pad + row] = J.t[t].scale * s;
+    f32x4 o[kLoraMaxTiles][4];
+#pragma unroll
+    for (int t = 0; t < kLoraMaxTiles; ++t)
+      if (t < nt)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[t][c] = bload_f4(ro[t], off[c]);
+#pragma unroll
+    for (int t = 0; t < kLoraMaxTiles; ++t)
+      if (t < nt)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c][i], o[t][c][i], acc[t], 0, 0, 0);
   }
+  __shared__ f32x4 red[4][kLoraMaxTiles][64];
+#pragma unroll
+  for (int t = 0; t < kLoraMaxTiles; ++t)
+    if (t < nt) red[wave][t][lane] = acc[t];
+  __syncthreads();
+  if (wave >= nt) return;
+  // wave t finishes tile t: lane (l16, g), register r holds rank l16, row 4 g + r
+  const f32x4 v = (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
+  float* out = reinterpret_cast<float*>(ws + J.t[wave].out_off) + (int64_t)l16 * J.rows_pad + row0 + 4 * g;
+  *reinterpret_cast<f32x4*>(out) = J.t[wave].scale * v;
 }
 
+// 64 columns x one row range per workgroup; wave w takes the 16-row chunks w, w + 4, ... of the range.
+// Column tile q of the wave holds columns 4 l16 + q, so that a lane's loads are 16 bytes.
 __global__ __launch_bounds__(256) void lora_p2_f32_kernel(LoraP2Batch b, uint8_t* __restrict__ ws) {
   const int ji = find_job(b, (int)blockIdx.x);
   const LoraP2Job& J = b.j[ji];
-  const int ncb = (J.cols + kLoraColTile - 1) / kLoraColTile;
+  const int cols = J.cols, nt = J.nt;
+  const int ncb = (cols + kLoraColTile - 1) / kLoraColTile;
   const int local = (int)blockIdx.x - J.b_begin;
   const int sp = local / ncb, cb = local % ncb;
   const int tper = ((J.rows_pad / J.splits + kLoraTStep - 1) / kLoraTStep) * kLoraTStep;
   const int t_begin = sp * tper;
-  const int t_end = min(J.rows, t_begin + tper);
-  const int col = cb * kLoraColTile + (threadIdx.x & 63);
+  const int t_end = min(J.rows_pad, t_begin + tper);
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = cb * kLoraColTile + 4 * l16;  // cols % 8 == 0: the four columns are whole or absent
   const float* src = static_cast<const float*>(J.src);
-  for (int c = threadIdx.x >> 6; c < 16 * J.nt; c += 4) {
-    const int t = c >> 4, cr = c & 15;
-    const float* lt = reinterpret_cast<const float*>(ws + J.t[t].lt_off) + (int64_t)cr * J.rows_pad;
-    float s = 0.0f;
-    if (col < J.cols)
-      for (int r = t_begin; r < t_end; ++r) s = fmaf(lt[r], src[(int64_t)r * J.cols + col], s);
-    if (col < J.cols)
-      reinterpret_cast<float*>(ws + J.t[t].part_off)[((int64_t)sp * 16 + cr) * J.cols + col] = s;
+  __amdgpu_buffer_rsrc_t rl[kLoraMaxTiles];
+#pragma unroll
+  for (int t = 0; t < kLoraMaxTiles; ++t)
+    rl[t] = buffer_rsrc(ws + (t < nt ? J.t[t].lt_off : 0), t < nt ? 16 * J.rows_pad * 4 : 0);
+  f32x4 acc[kLoraMaxTiles][4];
+#pragma unroll
+  for (int t = 0; t < kLoraMaxTiles; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int tb = t_begin + 16 * wave; tb < t_end; tb += 128) {
+    f32x4 x[2][4], l[kLoraMaxTiles][2];  // rows t0 + 4 g + i of chunk c
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int t0 = tb + 64 * c;
+      const int nr = t0 < t_end ? max(0, min(16, J.rows - t0)) : 0;
+      const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(src + (int64_t)min(t0, J.rows) * cols, nr * cols * 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        x[c][i] = bload_f4(rs, col < cols ? (uint32_t)((4 * g + i) * cols + col) * 4u : kOOB);
+#pragma unroll
+      for (int t = 0; t < kLoraMaxTiles; ++t)
+        if (t < nt) l[t][c] = bload_f4(rl[t], t0 < t_end ? (uint32_t)(l16 * J.rows_pad + t0 + 4 * g) * 4u : kOOB);
+    }
+#pragma unroll
+    for (int t = 0; t < kLoraMaxTiles; ++t)
+      if (t < nt)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(l[t][c][i], x[c][i][q], acc[t][q], 0, 0, 0);
+  }
+  // D: lane (l16, g), register v -> rank 4 g + v, column 4 l16 + q of column tile q
+  __shared__ f32x4 red[4][4][64];  // [wave][register v][lane], the four columns together
+#pragma unroll
+  for (int t = 0; t < kLoraMaxTiles; ++t) {
+    if (t >= nt) break;
+    if (t > 0) __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][v][lane] = f32x4{acc[t][0][v], acc[t][1][v], acc[t][2][v], acc[t][3][v]};
+    __syncthreads();
+    const f32x4 s = (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
+    float* part = reinterpret_cast<float*>(ws + J.t[t].part_off) + ((int64_t)sp * 16 + 4 * g + wave) * cols;
+    if (col < cols) *reinterpret_cast<f32x4*>(part + col) = s;
   }
 }
 
