@@ -1324,70 +1324,72 @@ extern "C" attt_status attt_lora_forward(const attt_lora_fwd_problem* problems, 
     }
     if (!placed) groups.push_back({i});
   }
-  // Jobs of at most 16 rows (decoding) run on 8-wave workgroups that split d_in eight ways;
-  // larger jobs on 4-wave workgroups of 64 rows.
-  std::vector<LoraFwdJob> jobs[2];  // [0] 4-wave, [1] 8-wave
-  int64_t row_blocks = 0;
-  int64_t max_dout = 8, max_dout_small = 8;
+  // Column splits: every row block's outputs over ncs workgroups, each recomputing x A^T (its x and A
+  // come from the XCD's L2, the splits of a block running on one XCD), up to one workgroup per CU: the
+  // decoding step of 16 episodes (32 row blocks) took 25, 19, 17 and 27 us with 2, 4, 8 and 16 splits.
+  int64_t row_blocks = 0, max_dout = 8;
   for (const auto& gr : groups) {
+    row_blocks += ceil_div(problems[gr[0]].rows, kLoraFwdRows);
+    for (int i : gr) max_dout = std::max<int64_t>(max_dout, problems[i].d_out);
+  }
+  const int ncs = row_blocks == 0 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>({16, ceil_div(256, row_blocks), ceil_div(max_dout, 64)}));
+  // larger unit counts first: a launch is compiled for its largest
+  std::vector<int> group_units;
+  for (const auto& gr : groups) {
+    int u = 0;
+    for (int i : gr) u += units[i];
+    group_units.push_back(u);
+  }
+  std::vector<size_t> order(groups.size());
+  for (size_t k = 0; k < order.size(); ++k) order[k] = k;
+  std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return group_units[x] > group_units[y]; });
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  LoraFwdBatch b{};
+  int64_t total = 0;
+  int nu = 0;
+  auto flush = [&]() -> attt_status {
+    if (b.count == 0) return ATTT_OK;
+    b.total = (int32_t)total;
+    b.ncs = ncs;
+    HIP_TRY(launch_lora_fwd(nu, b, s), "lora_fwd");
+    b = LoraFwdBatch{};
+    total = 0;
+    nu = 0;
+    return ATTT_OK;
+  };
+  for (size_t k : order) {
+    const auto& gr = groups[k];
     const attt_lora_fwd_problem& f = problems[gr[0]];
-    const bool small = f.rows <= 16;
-    LoraFwdJob J{};
+    const int64_t wgs = ceil_div(f.rows, kLoraFwdRows) * ncs;
+    // Jobs of fewer units go through the motions of the launch's largest count. From two workgroups per
+    // CU on, a launch of their own is cheaper: 143 us in one and 137 in two at 16 x 512 rows of q, k, v, o.
+    if (b.count == kLoraFwdBatch || (row_blocks >= 512 && b.count > 0 && group_units[k] != nu) || b.outs + (int)gr.size() > 2 * kLoraFwdBatch || total + wgs >= ((int64_t)1 << 31) - 8) {
+      attt_status st = flush();
+      if (st) return st;
+    }
+    LoraFwdJob& J = b.j[b.count++];
     J.x = f.x;
     J.rows = (int32_t)f.rows;
     J.d_in = (int32_t)f.d_in;
-    J.rb = small ? 16 : 64;
-    J.kw = small ? 8 : 1;
-    J.ncs = 1;
+    J.b_begin = (int32_t)total;
+    J.o_begin = (int16_t)b.outs;
     for (int i : gr) {
       const attt_lora_fwd_problem& q = problems[i];
-      LoraFwdOut& O = J.o[J.no++];
+      LoraFwdOut& O = b.o[b.outs++];
+      O.A = q.A;
       O.B = q.B;
       O.y = q.y;
+      O.scale = q.scale;
       O.d_out = (int32_t)q.d_out;
-      O.rank = q.rank;
-      O.u0 = 16 * J.nu;
-      for (int t = 0; t < units[i]; ++t) {
-        LoraFwdUnit& U = J.u[J.nu++];
-        U.A = static_cast<const uint8_t*>(q.A) + (int64_t)16 * t * q.d_in * 2;
-        U.valid = std::min(16, q.rank - 16 * t);
-        U.scale = q.scale;
-      }
-      (small ? max_dout_small : max_dout) = std::max<int64_t>(small ? max_dout_small : max_dout, q.d_out);
+      O.rank = (int16_t)q.rank;
+      O.u0 = J.nu;
+      J.nu = (int8_t)(J.nu + units[i]);
+      ++J.no;
     }
-    if (!small) row_blocks += ceil_div(f.rows, J.rb);
-    jobs[small ? 1 : 0].push_back(J);
+    nu = std::max<int>(nu, J.nu);
+    total += wgs;
   }
-  // Few row blocks: split each block's columns over several workgroups, each recomputing x A^T
-  // (x and A stay in the XCD's L2, the splits of a block running on one XCD), so that the
-  // launch still fills the chip.
-  int ncs = 1;
-  if (row_blocks > 0 && row_blocks < 512)
-    ncs = (int)std::min<int64_t>({16, ceil_div(1024, row_blocks), ceil_div(max_dout, 64)});
-  ncs = std::max(ncs, 1);
-  for (auto& J : jobs[0]) J.ncs = ncs;
-  // decoding: every job's columns over up to 16 workgroups of at least 256 columns each
-  const int ncs_small = (int)std::max<int64_t>(1, std::min<int64_t>(16, ceil_div(max_dout_small, 256)));
-  for (auto& J : jobs[1]) J.ncs = ncs_small;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  for (int kind = 0; kind < 2; ++kind) {
-    auto& js = jobs[kind];
-    std::stable_sort(js.begin(), js.end(), [](const LoraFwdJob& a, const LoraFwdJob& b) { return a.nu > b.nu; });
-    for (size_t j0 = 0; j0 < js.size(); j0 += kLoraFwdBatch) {
-      LoraFwdBatch b{};
-      b.count = (int32_t)std::min<size_t>(kLoraFwdBatch, js.size() - j0);
-      int64_t total = 0;
-      for (int i = 0; i < b.count; ++i) {
-        b.j[i] = js[j0 + i];
-        b.j[i].b_begin = (int32_t)total;
-        total += ceil_div(b.j[i].rows, b.j[i].rb) * b.j[i].ncs;
-      }
-      if (total >= ((int64_t)1 << 31) - 8) return fail(ATTT_EUNSUPPORTED, "lora_forward: too many row blocks");
-      b.total = (int32_t)total;
-      HIP_TRY(launch_lora_fwd(b.j[0].nu, kind ? 8 : 4, b, s), "lora_fwd");
-    }
-  }
-  return ATTT_OK;
+  return flush();
 }
 
 extern "C" attt_status attt_lora_hot_swap(const attt_lora_swap_item* items, int32_t count, void* stream) {

@@ -375,39 +375,37 @@ hipError_t launch_lora_reduce(const LoraRedBatch& b, int blocks, uint8_t* ws, hi
 // A job is a group of adapted projections reading one input x [rows, d_in] (one episode's
 // rows; q, k and v of a layer together). Phase 1 computes U = x A^T for up to four units of
 // 16 ranks; phase 2 adds scale-weighted U B^T into each projection's y [rows, d_out].
-struct LoraFwdUnit {
-  const void* A;    // first row of the unit in its problem's A [rank, d_in]
-  float scale;
-  int32_t valid;    // ranks in the unit (<= 16); the rest read as zero
-};
 struct LoraFwdOut {
+  const void* A;    // [rank, d_in]
   const void* B;    // [d_out, rank]
   void* y;          // [rows, d_out], updated in place
-  int32_t d_out, rank;
-  int32_t u0;       // first column of U that belongs to this projection
-  int32_t pad;
+  float scale;
+  int32_t d_out;
+  int16_t rank;
+  int16_t u0;       // first unit of U that belongs to this projection
 };
 struct LoraFwdJob {
   const void* x;
   int32_t rows, d_in;
-  int32_t nu, no;   // units, projections
-  int32_t rb;       // rows per workgroup: 64 (one wave per 16 rows) or 16 (the waves split d_in)
-  int32_t kw;       // waves splitting d_in: 1, 4, or 8 (8-wave workgroups)
-  int32_t ncs;      // column splits of the outputs (workgroups per row block)
-  int32_t b_begin;  // first logical workgroup
-  LoraFwdUnit u[kLoraMaxTiles];
-  LoraFwdOut o[kLoraMaxTiles];
+  int32_t b_begin;      // first logical workgroup
+  int16_t o_begin;      // first of the job's projections in the batch
+  int8_t no, nu;        // projections, units
 };
-constexpr int kLoraFwdBatch = 16;
+constexpr int kLoraFwdRows = 16;   // rows per workgroup
+constexpr int kLoraFwdBatch = 32;  // jobs per launch, and twice as many projections: the 16 episodes of
+                                   // a decoding step (q, k, v and o) are one launch
 struct LoraFwdBatch {
+  static constexpr int kCap = kLoraFwdBatch;
   int32_t count;
   int32_t total;    // logical workgroups
+  int32_t ncs;      // column splits of the outputs (workgroups per row block)
+  int32_t outs;     // projections in o
   LoraFwdJob j[kLoraFwdBatch];
+  LoraFwdOut o[2 * kLoraFwdBatch];
 };
 static_assert(sizeof(LoraFwdBatch) <= 3840, "kernel arguments");
-// nu: the largest unit count of the batch's jobs; waves: 4, or 8 for jobs of at most 16 rows
-// (kw = 8)
-hipError_t launch_lora_fwd(int nu, int waves, const LoraFwdBatch& b, hipStream_t s);
+// nu: the largest unit count of the batch's jobs
+hipError_t launch_lora_fwd(int nu, const LoraFwdBatch& b, hipStream_t s);
 
 // Swap: dst (bf16) = RN(src (float32)) for every tensor of the batch.
 struct LoraSwapJob {

@@ -6,19 +6,26 @@
 // caller has written into y; this adds y <- RN(y + scale (x A^T) B^T) for every (episode,
 // projection), in one launch for all of them. A job is one x (an episode's rows) with up to
 // four projections reading it (q, k, v of a layer): x is read once for all their ranks.
-//   Phase 1: U = x A^T on v_mfma_f32_16x16x32_bf16, 16 rows per wave over the contraction
-//     (64 rows per 4-wave workgroup), or, for at most 16 rows (decoding), an 8-wave workgroup
-//     whose waves take an eighth of d_in each, their partial U summed in LDS in a fixed order. x rows and adapter rows are 16-byte loads in the MFMA's own k order, the next
-//     128-wide step in flight.
-//     scale U (float32) stays in LDS: nothing goes through HBM between the phases.
-//   Phase 2: per projection, 256-column chunks of B [d_out, rank] staged transposed in LDS;
-//     each thread adds the rank-long dot products for 8 consecutive columns of up to 8 rows
-//     to y in float32 and rounds once to bf16 (16-byte loads and stores of y).
-//   A row block's outputs may be split over `ncs` workgroups (each recomputing phase 1) so
-//   that few rows still fill the chip; logical workgroups are mapped so that consecutive ones
-//   (the splits of one row block) run on one XCD and share its L2.
+//   Phase 1: U = x A^T on v_mfma_f32_16x16x32_bf16 for 16 rows per workgroup; its waves split d_in
+//     and their partial U meet in LDS in a fixed order. Rows of x and A lie 2 d_in bytes apart, so an
+//     MFMA's own operand order (16 rows x 64 bytes per load) would touch 16 half lines of one cache set
+//     and one L2 channel; each wave loads 8 rows x 128 bytes instead (whole lines), two steps of 64 in
+//     flight, and turns them into operands through 9 KiB of LDS of its own. (Operand-order loads ran at
+//     20 GB/s per CU: 21 us for a decoding step's 15 MB, 165 us at prefill.) scale U (float32) stays in
+//     LDS: nothing goes through HBM between the phases.
+//   Phase 2: y's columns in blocks of 64, dealt to the waves. U B^T runs on the
+//     float32 MFMA (v_mfma_f32_16x16x4_f32 on U and the widened B: the products and sums of float32
+//     arithmetic); MFMA column n of tile q is column 4 n + q of the block, so a lane ends up with 4
+//     consecutive columns of 4 rows: an 8-byte load and store of y each, 128 contiguous bytes per row.
+//   The rank product is a sixth of the float32 matrix rate at prefill, where the bytes of x and y
+//   bound the kernel.
+//   A row block's outputs are split over `ncs` workgroups (each recomputing phase 1) only where row
+//   blocks are too few to fill the chip; logical workgroups are mapped so that consecutive ones
+//   (the splits of one row block, the row blocks of one episode) run on one XCD and share its L2.
 // lora_swap_kernel: the swap. float32 adapter tensors -> their bf16 serving copies, rounded to
 // nearest even, every tensor of an adapter in one launch.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -27,190 +34,269 @@ namespace attt {
 namespace {
 constexpr uint32_t kOOBF = 0x7FFFFFF0u;  // offset past every descriptor's range: loads return 0
 constexpr int kUP = 65;                  // LDS pitch (floats) of a row of U
-constexpr int kBC = 256;                 // output columns per phase-2 chunk
-constexpr int kBP = kBC + 8;             // LDS pitch (bf16) of a rank row of the transposed B chunk
-constexpr int kBtBytes = 64 * kBP * 2;
-// LDS scratch of a W-wave workgroup: the waves' partial U [W][16][kUP] floats, later the B chunk
-template <int W>
-constexpr int scratch_bytes() { return W * 16 * kUP * 4 > kBtBytes ? W * 16 * kUP * 4 : kBtBytes; }
+constexpr int kSP = 144;                 // LDS pitch (bytes) of a staged row's 64 elements: conflict-free b128 reads
 
+// Job of logical workgroup li: the last whose first workgroup is at most li. Each lane looks at one
+// job (two above 64), so the search is one load and a ballot however many jobs a launch has.
 template <class Batch>
 __device__ __forceinline__ int job_of(const Batch& b, int li) {
-  int j = 0;
-  while (j + 1 < b.count && b.j[j + 1].b_begin <= li) ++j;
-  return __builtin_amdgcn_readfirstlane(j);
+  const int lane = threadIdx.x & 63;
+  int n = __popcll(__ballot(lane < b.count && b.j[lane < b.count ? lane : 0].b_begin <= li));
+  if constexpr (Batch::kCap > 64)
+    n += __popcll(__ballot(lane + 64 < b.count && b.j[lane + 64 < b.count ? lane + 64 : 0].b_begin <= li));
+  return __builtin_amdgcn_readfirstlane(n - 1);
 }
 
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+// A lane's SPL consecutive elements of a row of B, from byte offset `off`.
+template <int SPL>
+struct BRow {
+  uint32_t w[(SPL + 1) / 2];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    if constexpr (SPL == 2) {
+      w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+    } else if constexpr (SPL == 4) {
+      const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+      w[0] = v.x, w[1] = v.y;
+    } else {
+#pragma unroll
+      for (int q = 0; q < SPL / 8; ++q) {
+        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off + 16u * q, 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[4 * q + e] = v[e];
+      }
+    }
+  }
+  __device__ __forceinline__ float get(int i) const { return (i & 1) ? bf_hi(w[i >> 1]) : bf_lo(w[i >> 1]); }
+};
+// Any rank: element loads, zero past the lane's `n` elements.
+struct BRowAny {
+  uint32_t w[8];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off, int n) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(r, 2 * i < n ? off + 4u * i : kOOBF, 0, 0);
+      const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(r, 2 * i + 1 < n ? off + 4u * i + 2u : kOOBF, 0, 0);
+      w[i] = (lo & 0xFFFFu) | (hi << 16);
+    }
+  }
+  __device__ __forceinline__ float get(int i) const { return (i & 1) ? bf_hi(w[i >> 1]) : bf_lo(w[i >> 1]); }
+};
+
+// Phase 2 of one projection: blocks first, first + stride, ... < nb of 64 columns from o_lo. Lane
+// (l16, g) holds row l16 of U and, for column tile q, column TQ l16 + q of B, at k = g SPL .. +SPL-1;
+// it ends up with columns TQ l16 .. + TQ - 1 of rows 4 g .. 4 g + 3. kDepth blocks have their loads in
+// flight.
+template <int SPL, bool kAny, int kDepth>
+__device__ __forceinline__ void add_columns(const LoraFwdOut& O, const float* Uf, int row0, int nrows, int o_lo,
+                                            int o_hi, int first, int stride, int nb, int lane) {
+  constexpr int TQ = 4;
+  typedef uint32_t YVec __attribute__((ext_vector_type(2)));  // 4 bf16 of a row of y
+  const int l16 = lane & 15, g = lane >> 4;
+  const int d_out = O.d_out, rank = O.rank;
+  const int spl = kAny ? (rank + 3) / 4 : SPL;
+  float u[SPL];
+#pragma unroll
+  for (int i = 0; i < SPL; ++i)
+    u[i] = !kAny || (i < spl && g * spl + i < rank) ? Uf[l16 * kUP + 16 * O.u0 + g * spl + i] : 0.0f;
+  const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(O.B, d_out * rank * 2);
+  const __amdgpu_buffer_rsrc_t ry = buffer_rsrc(static_cast<bf16_t*>(O.y) + (int64_t)row0 * d_out, nrows * d_out * 2);
+  using Row = std::conditional_t<kAny, BRowAny, BRow<SPL>>;
+  YVec yv[kDepth][4];
+  Row br[kDepth][TQ];
+  // column of the lane's first element of y in a block, and its byte offset in row 4 g + v; rows at or
+  // past nrows fall outside the descriptor's range
+  auto ycol = [&](int blk) { return o_lo + blk * 16 * TQ + TQ * l16; };
+  auto yoff = [&](int yc, int v) { return yc < o_hi ? (uint32_t)((4 * g + v) * d_out + yc) * 2u : kOOBF; };
+  auto load = [&](int d, int blk) {
+    const int yc = ycol(blk);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      yv[d][v] = __builtin_bit_cast(YVec, __builtin_amdgcn_raw_buffer_load_b64(ry, yoff(yc, v), 0, 0));
+#pragma unroll
+    for (int q = 0; q < TQ; ++q) {
+      const uint32_t off = yc < o_hi ? (uint32_t)((yc + q) * rank + g * spl) * 2u : kOOBF;
+      if constexpr (kAny)
+        br[d][q].load(rb, off, yc < o_hi ? min(spl, rank - g * spl) : 0);
+      else
+        br[d][q].load(rb, off);
+    }
+  };
+  // Loads past the last block fall outside the descriptors' ranges; they are issued all the same, so that
+  // the number of loads in flight is the same on every path and each wait names only what it needs.
+#pragma unroll
+  for (int d = 0; d < kDepth; ++d) load(d, first + d * stride);
+  for (int b0 = first; b0 < nb; b0 += kDepth * stride) {
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) {
+      const int blk = b0 + d * stride;
+      if (blk >= nb) break;
+      f32x4 acc[TQ];
+#pragma unroll
+      for (int q = 0; q < TQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < SPL; ++i)
+#pragma unroll
+        for (int q = 0; q < TQ; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[i], br[d][q].get(i), acc[q], 0, 0, 0);
+      const int yc = ycol(blk);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        YVec out;
+#pragma unroll
+        for (int e = 0; e < TQ / 2; ++e)
+          out[e] = pack_bf16x2(bf_lo(yv[d][v][e]) + acc[2 * e][v], bf_hi(yv[d][v][e]) + acc[2 * e + 1][v]);
+        __builtin_amdgcn_raw_buffer_store_b64(out, ry, yoff(yc, v), 0, 0);
+      }
+      // this slot's next block: the loads of the other slots stay in flight behind it
+      load(d, blk + kDepth * stride);
+    }
+  }
+}
 }  // namespace
 
-// W waves: 4 (up to 64 rows per workgroup, 16 per wave, or 16 rows with d_in split four ways)
-// or 8 (decoding: 16 rows, d_in split eight ways, twice the loads in flight per workgroup).
-template <int NU, int W>
-__global__ __launch_bounds__(64 * W) void lora_fwd_kernel(LoraFwdBatch b, int grid) {
-  constexpr int NT = 64 * W;
+// Eight waves, blocks of 64 columns. kLight: every rank of the launch is 8 or 16, which keeps the
+// kernel at 100 registers (four waves per SIMD); the other ranks hold up to 16 k values per lane.
+// 16 x 512 rows of q, k, v and o (483 MB): 279 us with 64-row workgroups that recomputed U in eight
+// column splits and walked the rank per thread, 137 us now (3.5 TB/s); the decoding step of 16 episodes
+// 42 us in two launches, 17 in one.
+template <int NU, bool kLight>
+__global__ __launch_bounds__(512) void lora_fwd_kernel(LoraFwdBatch b, int grid) {
+  constexpr int W = 8, NT = 64 * W, TQ = 4;
+  constexpr int kWaveStage = 16 * (1 + NU) * kSP;  // bytes: 16 rows of x, then the units' rows of A
+  static_assert(kWaveStage >= 16 * kUP * 4, "the partial U reuses the stage");
   // hardware places workgroup i on XCD i % 8: give each XCD a contiguous range of logical ids
   const int per = grid >> 3;
   const int li = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
   if (li >= b.total) return;
-  const int ji = job_of(b, li);
-  const LoraFwdJob& J = b.j[ji];
+  const LoraFwdJob& J = b.j[job_of(b, li)];
+  const int ncs = b.ncs;
   const int local = li - J.b_begin;
-  const int rb = local / J.ncs, cs = local - rb * J.ncs;
-  const int row0 = rb * J.rb;
+  const int rblk = local / ncs, cs = local - rblk * ncs;
+  const int row0 = rblk * kLoraFwdRows;
+  const int nrows = min(kLoraFwdRows, J.rows - row0);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
-  __shared__ __align__(16) float Uf[64 * kUP];
-  __shared__ __align__(16) uint8_t scr[scratch_bytes<W>()];
-  float* Up = reinterpret_cast<float*>(scr);    // phase 1: [wave][16][kUP] partial U
-  bf16_t* Bt = reinterpret_cast<bf16_t*>(scr);  // phase 2: [rank][kBP] transposed B chunk
+  __shared__ __align__(16) float Uf[16 * kUP];
+  __shared__ __align__(16) uint8_t scr[W * kWaveStage];
+  uint8_t* mine = scr + w * kWaveStage;
+  const int no = J.no, nu = J.nu;
+  const LoraFwdOut* outs = b.o + J.o_begin;
 
   // ---- phase 1 ------------------------------------------------------------------------
-  const int d_in = J.d_in, nu = J.nu;
-  const int rg = J.kw > 1 ? 0 : w;  // this wave's 16 rows
-  const int kp = J.kw > 1 ? w : 0;  // this wave's share of d_in
-  const int r0w = row0 + 16 * rg;
-  const int nrows = max(0, min(16, J.rows - r0w));
-  const bf16_t* xs = static_cast<const bf16_t*>(J.x) + (int64_t)min(r0w, J.rows) * d_in;
+  const int d_in = J.d_in;
+  const bf16_t* xs = static_cast<const bf16_t*>(J.x) + (int64_t)row0 * d_in;
   const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(xs, nrows * d_in * 2);
+  // unit t: 16 ranks (the last of a projection may have fewer; the rest read as zero)
   __amdgpu_buffer_rsrc_t ra[NU];
+  float usc[NU];
 #pragma unroll
-  for (int t = 0; t < NU; ++t)
-    ra[t] = buffer_rsrc(t < nu ? J.u[t].A : xs, t < nu ? J.u[t].valid * d_in * 2 : 0);
-  const int ns = (d_in + 127) / 128;
-  const int spw = (ns + J.kw - 1) / J.kw;
-  const int s_begin = kp * spw, s_end = min(ns, s_begin + spw);
+  for (int t = 0; t < NU; ++t) {
+    int p = 0;
+    while (p + 1 < no && outs[p + 1].u0 <= t) ++p;
+    const LoraFwdOut& O = outs[p];
+    const int sub = t - O.u0;
+    ra[t] = buffer_rsrc(static_cast<const bf16_t*>(O.A) + (int64_t)16 * sub * d_in,
+                        t < nu ? max(0, min(16, O.rank - 16 * sub)) * d_in * 2 : 0);
+    usc[t] = O.scale;
+  }
+  const int ns = (d_in + 63) / 64;
+  const int spw = (ns + W - 1) / W;
+  const int s_begin = w * spw, s_end = min(ns, s_begin + spw);
   f32x4 acc[NU];
 #pragma unroll
   for (int t = 0; t < NU; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // step s, MFMA q: lane (l16, g) holds row l16 (x) / rank l16 (A) at k = 128 s + 32 q + 8 g .. +7
-  auto load = [&](int s, u32x4 (&xa)[4], u32x4 (&ao)[NU][4]) {
+  // step s of 64: a load instruction takes rows sr (+ 8) at 16-byte chunk sc of the step
+  const int sr = lane >> 3, sc = lane & 7;
+  auto load = [&](int s, u32x4 (&v)[1 + NU][2]) {
+    const int k = s * 64 + sc * 8;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = s * 128 + q * 32 + g * 8;
-      const uint32_t off = k < d_in ? (uint32_t)(l16 * d_in + k) * 2u : kOOBF;
-      xa[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0));
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t off = s < s_end && k < d_in ? (uint32_t)((sr + 8 * h) * d_in + k) * 2u : kOOBF;
+      v[0][h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0));
 #pragma unroll
       for (int t = 0; t < NU; ++t)
-        if (t < nu) ao[t][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra[t], off, 0, 0));
+        v[1 + t][h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra[t], off, 0, 0));
     }
   };
-  auto mma = [&](const u32x4 (&xa)[4], const u32x4 (&ao)[NU][4]) {
+  // The stage is this wave's own and its LDS operations run in order: no barrier.
+  auto mma = [&](const u32x4 (&v)[1 + NU][2]) {
 #pragma unroll
-    for (int t = 0; t < NU; ++t) {
-      if (t >= nu) break;
+    for (int t = 0; t < 1 + NU; ++t)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xa[q]),
-                                                         __builtin_bit_cast(bf16x8, ao[t][q]), acc[t], 0, 0, 0);
+      for (int h = 0; h < 2; ++h)
+        *reinterpret_cast<u32x4*>(mine + (16 * t + sr + 8 * h) * kSP + 16 * sc) = v[t][h];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const uint8_t* f = mine + l16 * kSP + (32 * q + 8 * g) * 2;
+      const bf16x8 x = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(f));
+#pragma unroll
+      for (int t = 0; t < NU; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            x, __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(f + 16 * (1 + t) * kSP)), acc[t], 0, 0, 0);
     }
   };
   {
-    u32x4 x0[4], a0[NU][4], x1[4], a1[NU][4];
-    if (s_begin < s_end) load(s_begin, x0, a0);
+    u32x4 v0[1 + NU][2], v1[1 + NU][2];
+    // steps at or past s_end and absent units load zeros (no memory access), on every path alike
+    load(s_begin, v0);
+    load(s_begin + 1, v1);
     for (int s = s_begin; s < s_end; s += 2) {
-      if (s + 1 < s_end) load(s + 1, x1, a1);
-      mma(x0, a0);
-      if (s + 1 < s_end) {
-        if (s + 2 < s_end) load(s + 2, x0, a0);
-        mma(x1, a1);
-      }
+      mma(v0);
+      load(s + 2, v0);
+      mma(v1);
+      load(s + 3, v1);
     }
   }
   // D of a 16x16 tile: lane l, register v -> row 4 (l / 16) + v, rank l % 16
+  float* Up = reinterpret_cast<float*>(mine);
 #pragma unroll
   for (int t = 0; t < NU; ++t) {
     if (t >= nu) break;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Up[(w * 16 + 4 * g + v) * kUP + 16 * t + l16] = acc[t][v];
+    for (int v = 0; v < 4; ++v) Up[(4 * g + v) * kUP + 16 * t + l16] = acc[t][v];
   }
   __syncthreads();
-  for (int i = tid; i < J.rb * 64; i += NT) {
+  for (int i = tid; i < 16 * 64; i += NT) {
     const int row = i >> 6, c = i & 63, t = c >> 4;
     if (t >= nu) continue;
-    float sc = J.u[0].scale;
+    float sc2 = usc[0];
 #pragma unroll
     for (int k = 1; k < NU; ++k)
-      if (t == k) sc = J.u[k].scale;
-    float v = Up[row * kUP + c];  // kw == 1: wave row/16 wrote row row%16 of its block here
-    for (int k = 1; k < J.kw; ++k) v += Up[(16 * k + row) * kUP + c];  // kw > 1: fixed order
-    Uf[row * kUP + c] = sc * v;
+      if (t == k) sc2 = usc[k];
+    const float* part = reinterpret_cast<const float*>(scr) + row * kUP + c;
+    float v = part[0];
+#pragma unroll
+    for (int k = 1; k < W; ++k) v += part[k * (kWaveStage / 4)];  // fixed order
+    Uf[row * kUP + c] = sc2 * v;
   }
-  __syncthreads();  // Up is dead from here on; its space holds the B chunks
+  __syncthreads();
 
-  // ---- phase 2 ------------------------------------------------------------------------
-  const int og = tid & 31, rs = tid >> 5;  // 8 columns og*8 .. +7 of rows rs, rs + 2W, ...
-  const int nri = (J.rb + 2 * W - 1) / (2 * W);
+  // ---- phase 2: the blocks of all projections in one sequence, dealt to the waves in turn ------
+  int base = 0;
 #pragma unroll 1
-  for (int p = 0; p < kLoraMaxTiles; ++p) {
-    if (p >= J.no) break;
-    const LoraFwdOut& O = J.o[p];
-    const int d_out = O.d_out, rank = O.rank, u0 = O.u0;
-    const int cw = (((d_out + J.ncs - 1) / J.ncs) + 7) & ~7;
-    const int o_lo = cs * cw, o_hi = min(d_out, o_lo + cw);
-    const bf16_t* B = static_cast<const bf16_t*>(O.B);
-    bf16_t* y = static_cast<bf16_t*>(O.y);
-    for (int oc = o_lo; oc < o_hi; oc += kBC) {
-      const int nvo = min(kBC, o_hi - oc);  // a multiple of 8
-      // B[oc .. oc + nvo)[0 .. rank) is contiguous: 16-byte loads, scattered into Bt[c][o]
-      const int nel = nvo * rank;
-      const bf16_t* src = B + (int64_t)oc * rank;
-      for (int i8 = tid * 8; i8 < nel; i8 += NT * 8) {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(src + i8);
-        int o = i8 / rank, c = i8 - o * rank;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          Bt[c * kBP + o] = (bf16_t)((e & 1) ? (v[e >> 1] >> 16) : (v[e >> 1] & 0xFFFFu));
-          if (++c == rank) c = 0, ++o;
-        }
-      }
-      __syncthreads();
-      const int ocol = og * 8;
-      if (ocol < nvo) {
-        // this thread's rows of y, loaded before the rank loop so that their latency overlaps it
-        u32x4 yv[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          if (i >= nri) break;
-          const int rl = rs + 2 * W * i, row = row0 + rl;
-          yv[i] = u32x4{0u, 0u, 0u, 0u};
-          if (rl < J.rb && row < J.rows)
-            yv[i] = *reinterpret_cast<const u32x4*>(y + (int64_t)row * d_out + oc + ocol);
-        }
-        float a[8][8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) a[i][e] = 0.0f;
-        for (int c = 0; c < rank; ++c) {
-          const u32x4 bw = *reinterpret_cast<const u32x4*>(Bt + c * kBP + ocol);
-          float bv[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) bv[2 * e] = bf_lo(bw[e]), bv[2 * e + 1] = bf_hi(bw[e]);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            if (i >= nri) break;
-            const float u = Uf[min(rs + 2 * W * i, 63) * kUP + u0 + c];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) a[i][e] = fmaf(u, bv[e], a[i][e]);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          if (i >= nri) break;
-          const int rl = rs + 2 * W * i;
-          const int row = row0 + rl;
-          if (rl >= J.rb || row >= J.rows) continue;
-          u32x4 out;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            out[e] = pack_bf16x2(bf_lo(yv[i][e]) + a[i][2 * e], bf_hi(yv[i][e]) + a[i][2 * e + 1]);
-          *reinterpret_cast<u32x4*>(y + (int64_t)row * d_out + oc + ocol) = out;
-        }
-      }
-      __syncthreads();  // Bt is rewritten by the next chunk
+  for (int p = 0; p < no; ++p) {
+    const LoraFwdOut& O = outs[p];
+    constexpr int CB = 16 * TQ;
+    const int cw = (((O.d_out + ncs - 1) / ncs) + CB - 1) & ~(CB - 1);
+    const int o_lo = min(O.d_out, cs * cw), o_hi = min(O.d_out, o_lo + cw);
+    const int nb = (o_hi - o_lo + CB - 1) / CB;
+    const int first = (w - base) & (W - 1);
+    base += nb;
+    if (O.rank == 16) {
+      add_columns<4, false, 2>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
+    } else if (O.rank == 8) {
+      add_columns<2, false, 2>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
+    } else if constexpr (!kLight) {
+      if (O.rank == 32)
+        add_columns<8, false, 1>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
+      else if (O.rank == 64)
+        add_columns<16, false, 1>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
+      else
+        add_columns<16, true, 1>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
     }
   }
 }
@@ -234,24 +320,27 @@ __global__ __launch_bounds__(256) void lora_swap_kernel(LoraSwapBatch b) {
   }
 }
 
-template <int W>
-static void launch_fwd_w(int nu, const LoraFwdBatch& b, int grid, hipStream_t s) {
+template <bool kLight>
+static void launch_fwd(int nu, const LoraFwdBatch& b, int grid, hipStream_t s) {
+  const dim3 g(grid), t(512);
   switch (nu) {
-    case 1: hipLaunchKernelGGL((lora_fwd_kernel<1, W>), dim3(grid), dim3(64 * W), 0, s, b, grid); break;
-    case 2: hipLaunchKernelGGL((lora_fwd_kernel<2, W>), dim3(grid), dim3(64 * W), 0, s, b, grid); break;
-    case 3: hipLaunchKernelGGL((lora_fwd_kernel<3, W>), dim3(grid), dim3(64 * W), 0, s, b, grid); break;
-    default: hipLaunchKernelGGL((lora_fwd_kernel<4, W>), dim3(grid), dim3(64 * W), 0, s, b, grid); break;
+    case 1: hipLaunchKernelGGL((lora_fwd_kernel<1, kLight>), g, t, 0, s, b, grid); break;
+    case 2: hipLaunchKernelGGL((lora_fwd_kernel<2, kLight>), g, t, 0, s, b, grid); break;
+    case 3: hipLaunchKernelGGL((lora_fwd_kernel<3, kLight>), g, t, 0, s, b, grid); break;
+    default: hipLaunchKernelGGL((lora_fwd_kernel<4, kLight>), g, t, 0, s, b, grid); break;
   }
 }
 
-hipError_t launch_lora_fwd(int nu, int waves, const LoraFwdBatch& b, hipStream_t s) {
+hipError_t launch_lora_fwd(int nu, const LoraFwdBatch& b, hipStream_t s) {
   if (b.total <= 0) return hipSuccess;
   const int grid = (b.total + 7) & ~7;
+  bool light = true;
+  for (int i = 0; i < b.outs; ++i) light = light && (b.o[i].rank == 8 || b.o[i].rank == 16);
   KernelTimer t(K_LORA_FWD, s);
-  if (waves == 8)
-    launch_fwd_w<8>(nu, b, grid, s);
+  if (light)
+    launch_fwd<true>(nu, b, grid, s);
   else
-    launch_fwd_w<4>(nu, b, grid, s);
+    launch_fwd<false>(nu, b, grid, s);
   return hipGetLastError();
 }
 

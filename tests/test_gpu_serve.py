@@ -208,3 +208,30 @@ def test_swap_then_forward_on_one_stream(attt):
     attt.lora_forward([dict(x=_dev(p["x"]), y=y, A=A, B=B, scale=2.0)])
     q = dict(p, A=serve.hot_swap(A32).reshape(8, 256), B=serve.hot_swap(B32).reshape(128, 8))
     _check_forward(_bits_of(y), q)
+
+
+@pytest.mark.parametrize("rows,episodes,d_in,d_out,rank", [(1, 1, 8, 8, 16), (2, 40, 72, 136, 8), (15, 3, 1000, 2056, 16),
+                                                           (33, 2, 200, 1096, 24), (600, 16, 64, 72, 16),
+                                                           (520, 17, 136, 64, 32)])
+def test_forward_blocks_and_splits(attt, rows, episodes, d_in, d_out, rank):
+    """Edges of the 16-row blocks, the 64-column blocks and their splits, more jobs and projections
+    than one launch holds, and launches with and without column splits; q and k share x, o has its own."""
+    rng = np.random.default_rng(rows + d_in)
+    probs = []
+    for _ in range(episodes):
+        x = _bits(rng, (rows, d_in))
+        probs += [_problem(rng, rows, d_in, d_out, rank, x=x), _problem(rng, rows, d_in, 8, rank, x=x),
+                  _problem(rng, rows, d_in, d_out, rank)]
+    note(f"lora_forward {episodes} x {rows} rows {d_in}->{d_out} rank {rank}")
+    for g, p in zip(_run(attt, probs), probs):
+        _check_forward(g, p)
+
+
+def test_forward_infinities(attt):
+    """An infinite adapter entry reaches exactly the elements it reaches in float32 arithmetic."""
+    rng = np.random.default_rng(31)
+    p = _problem(rng, 20, 64, 72, 16)
+    p["B"][5, 3] = 0x7F80
+    got, = _run(attt, [p])
+    bad = (got & 0x7F80) == 0x7F80
+    assert bad[:, 5].all() and not np.delete(bad, 5, 1).any() and np.all((got[:, 5] & 0x7F) == 0)
