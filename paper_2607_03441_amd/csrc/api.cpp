@@ -1275,10 +1275,11 @@ extern "C" attt_status attt_lora_sgd_step(const attt_lora_param* params, int32_t
     J.grad = q.grad;
     J.param_bf16 = static_cast<uint16_t*>(q.param_bf16);
     J.n = q.n;
+    J.vec = aligned16(q.param) && aligned16(q.grad) && aligned16(q.param_bf16);
     jobs.push_back(J);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return lora_launch_all(
+  return lora_launch_all<LoraSgdBatch>(
       jobs, [](const LoraSgdJob& J) { return (int)ceil_div(J.n, (int64_t)kLoraSgdPerBlock); },
       [&](const LoraSgdBatch& b, int n) { return launch_lora_sgd(b, n, lr, zero_grad, s); }, "lora_sgd");
 }

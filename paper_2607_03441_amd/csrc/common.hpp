@@ -42,6 +42,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* p, int
   return __builtin_amdgcn_make_buffer_rsrc(q, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
+// Job of workgroup `bid` of a launch over several jobs: the last whose b_begin is at most bid. Each lane
+// looks at one job (two above 64), so the search is one load and a ballot however many jobs a launch
+// has (a scan is a chain of scalar loads, 18 us for 96 jobs). Wave-uniform, and made explicit, so that
+// descriptors built from the job's pointers live in scalar registers.
+template <class Batch>
+__device__ __forceinline__ int find_job(const Batch& b, int bid) {
+  const int lane = threadIdx.x & 63;
+  int n = __popcll(__ballot(lane < b.count && b.j[lane < b.count ? lane : 0].b_begin <= bid));
+  if constexpr (Batch::kCap > 64)
+    n += __popcll(__ballot(lane + 64 < b.count && b.j[lane + 64 < b.count ? lane + 64 : 0].b_begin <= bid));
+  return __builtin_amdgcn_readfirstlane(n - 1);
+}
+
 template <int W>
 __device__ __forceinline__ float group_max(float v) {
 #pragma unroll

@@ -358,10 +358,11 @@ struct LoraSgdJob {
   uint16_t* param_bf16;  // nullable
   int64_t n;
   int32_t b_begin;
-  int32_t pad;
+  int32_t vec;           // every array 16-byte aligned
 };
-using LoraSgdBatch = LoraBatchOf<LoraSgdJob>;
-constexpr int kLoraSgdPerBlock = 1024;  // elements per workgroup (256 threads x 4)
+using LoraSgdBatch = LoraBatchOf<LoraSgdJob, 72>;
+static_assert(sizeof(LoraSgdBatch) <= 3840, "kernel arguments");
+constexpr int kLoraSgdPerBlock = 2048;  // elements per workgroup (256 threads x 8)
 hipError_t launch_lora_sgd(const LoraSgdBatch& b, int blocks, float lr, int zero_grad, hipStream_t s);
 
 hipError_t launch_lora_bt(int dtype, const LoraBTBatch& b, int blocks, uint8_t* ws, hipStream_t s);

@@ -36,17 +36,6 @@ constexpr uint32_t kOOBF = 0x7FFFFFF0u;  // offset past every descriptor's range
 constexpr int kUP = 65;                  // LDS pitch (floats) of a row of U
 constexpr int kSP = 144;                 // LDS pitch (bytes) of a staged row's 64 elements: conflict-free b128 reads
 
-// Job of logical workgroup li: the last whose first workgroup is at most li. Each lane looks at one
-// job (two above 64), so the search is one load and a ballot however many jobs a launch has.
-template <class Batch>
-__device__ __forceinline__ int job_of(const Batch& b, int li) {
-  const int lane = threadIdx.x & 63;
-  int n = __popcll(__ballot(lane < b.count && b.j[lane < b.count ? lane : 0].b_begin <= li));
-  if constexpr (Batch::kCap > 64)
-    n += __popcll(__ballot(lane + 64 < b.count && b.j[lane + 64 < b.count ? lane + 64 : 0].b_begin <= li));
-  return __builtin_amdgcn_readfirstlane(n - 1);
-}
-
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
@@ -171,7 +160,7 @@ __global__ __launch_bounds__(512) void lora_fwd_kernel(LoraFwdBatch b, int grid)
   const int per = grid >> 3;
   const int li = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
   if (li >= b.total) return;
-  const LoraFwdJob& J = b.j[job_of(b, li)];
+  const LoraFwdJob& J = b.j[find_job(b, li)];
   const int ncs = b.ncs;
   const int local = li - J.b_begin;
   const int rblk = local / ncs, cs = local - rblk * ncs;
@@ -302,7 +291,7 @@ __global__ __launch_bounds__(512) void lora_fwd_kernel(LoraFwdBatch b, int grid)
 }
 
 __global__ __launch_bounds__(256) void lora_swap_kernel(LoraSwapBatch b) {
-  const int ji = job_of(b, (int)blockIdx.x);
+  const int ji = find_job(b, (int)blockIdx.x);
   const LoraSwapJob J = b.j[ji];
   const int64_t i0 = ((int64_t)((int)blockIdx.x - J.b_begin) * 256 + threadIdx.x) * 8;
   if (i0 >= J.n) return;

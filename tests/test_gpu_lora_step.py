@@ -100,3 +100,25 @@ def test_two_gradient_steps_chained_f32(attt):
     dA_or, dB_or = Ao - A, Bo - B
     assert np.abs(dA_or).max() > 1e-3         # step 2 moved A (B was nonzero by then)
     assert rel_norm(dA_gpu, dA_or) <= 1e-5 and rel_norm(dB_gpu, dB_or) <= 1e-5
+
+
+def test_sgd_step_many_tensors_and_alignments(attt):
+    """More tensors than one launch holds, sizes around a workgroup's 2048 elements, and views whose
+    alignment rules the 16-byte accesses out."""
+    import torch
+    rng = np.random.default_rng(52)
+    sizes = [1, 2047, 2048, 2049, 4096, 8, 16384] * 25
+    note(f"lora sgd {len(sizes)} tensors")
+    params, want = [], []
+    for k, n in enumerate(sizes):
+        p, g = rng.standard_normal(n + 1).astype(np.float32), rng.standard_normal(n + 1).astype(np.float32)
+        o = k % 3 == 1  # one element in: 4-byte aligned only
+        b = torch.zeros(n + 1, dtype=torch.bfloat16, device="cuda")
+        params.append(dict(param=dev_f32(p)[o:o + n], grad=dev_f32(g)[o:o + n], param_bf16=b[o:o + n] if k % 5 else None))
+        want.append(olora.sgd_step(p[o:o + n], g[o:o + n], 0.25))
+    attt.lora_sgd_step(params, 0.25, zero_grad=True)
+    for d, w in zip(params, want):
+        assert np.array_equal(_bits(host(d["param"])), _bits(w)) and not host(d["grad"]).any()
+        if d["param_bf16"] is not None:
+            got_b = d["param_bf16"].view(torch.int16).cpu().numpy().view(np.uint16)
+            assert np.array_equal(got_b, olora.bf16_round_bits(w))
