@@ -2,9 +2,10 @@
 (arXiv 2607.03441: n-gram token weights, Eq. 8-9; weighted LM-head cross-entropy, Eq. 10;
 LoRA adapter gradients).
 
-This module only marshals arguments: torch tensors provide device memory and the current
-HIP stream, and every step runs in the library's HIP kernels. There is no fallback: if the
-library is not built, every call raises.
+This module only marshals arguments (those of the calls that take a list of problems natively,
+csrc/binding.cpp): torch tensors provide device memory and the current HIP stream, and every step
+runs in the library's HIP kernels. There is no fallback: if the library is not built, every call
+raises.
 """
 import ctypes
 import os
@@ -134,6 +135,23 @@ def load():
     L.attt_timing_kernel_name.argtypes = [i32]
     _LIB = L
     return L
+
+
+_NATIVE = None
+
+
+def _native():
+    """The native marshalling of the calls that take a list of problems (csrc/binding.cpp)."""
+    global _NATIVE
+    if _NATIVE is None:
+        load()
+        import torch  # noqa: F401  the module resolves against torch's libraries
+        path = os.path.join(_HERE, "_binding.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is not built; run __graft_entry__.build() first")
+        from . import _binding as module
+        _NATIVE = module
+    return _NATIVE
 
 
 def _check(status):
@@ -459,38 +477,16 @@ def weighted_ce_fwd_bwd(hidden, lm_head, labels, weights, row_offsets=None, want
 
 
 # ------------------------------------------------------------------------------------------
-def _lora_array(problems):
-    arr = (LoraProblem * max(len(problems), 1))()
-    for i, p in enumerate(problems):
-        x, dy, A, B = p["x"], p["dy"], p["A"], p["B"]
-        arr[i] = LoraProblem(_dptr(x), _dptr(dy), _dptr(A), _dptr(B), _dptr(p["dA"]), _dptr(p["dB"]),
-                             x.shape[0], x.shape[1], dy.shape[1], A.shape[0], float(p["scale"]))
-    return arr
-
-
 def lora_workspace_size(problems, dtype):
-    L = load()
-    arr = _lora_array(problems)
-    out = ctypes.c_size_t(0)
-    _check(L.attt_lora_workspace_size(arr, len(problems), dtype, ctypes.byref(out)))
-    return out.value
+    status, nbytes = _native().lora_workspace_size(problems, dtype)
+    _check(status)
+    return nbytes
 
 
 def lora_grad(problems, workspace=None):
     """LoRA dA / dB for a group of projections, accumulated (+=) into each problem's float32
     dA [r, d_in] and dB [d_out, r]. Each problem: dict(x, dy, A, B, dA, dB, scale)."""
-    L = load()
-    if not problems:
-        return
-    dt = _dtype_code(problems[0]["x"])
-    for p in problems:
-        for k in ("x", "dy", "A", "B", "dA", "dB"):
-            _dev(p[k], k)
-    arr = _lora_array(problems)
-    need = ctypes.c_size_t(0)
-    _check(L.attt_lora_workspace_size(arr, len(problems), dt, ctypes.byref(need)))
-    ws = _workspace(need.value, problems[0]["x"].device, workspace)
-    _check(L.attt_lora_grad(arr, len(problems), dt, _dptr(ws), ws.numel(), _stream_ptr()))
+    _check(_native().lora_grad(problems, workspace))
 
 
 def lora_sgd_step(params, lr, zero_grad=False):
@@ -498,54 +494,20 @@ def lora_sgd_step(params, lr, zero_grad=False):
     Each entry: dict(param, grad[, param_bf16]) of equal numel; param and grad float32,
     param_bf16 (optional) bfloat16, which receives the updated param rounded to nearest even.
     With zero_grad the gradients are reset to 0 after they are read."""
-    L = load()
-    torch = _torch()
-    arr = (LoraParam * max(len(params), 1))()
-    for i, p in enumerate(params):
-        P, G, Pb = p["param"], p["grad"], p.get("param_bf16")
-        _dev(P, "param")
-        _dev(G, "grad")
-        if P.dtype != torch.float32 or G.dtype != torch.float32 or G.numel() != P.numel():
-            raise ValueError("param and grad must be float32 tensors of equal size")
-        if Pb is not None:
-            _dev(Pb, "param_bf16")
-            if Pb.dtype != torch.bfloat16 or Pb.numel() != P.numel():
-                raise ValueError("param_bf16 must be a bfloat16 tensor of the param's size")
-        arr[i] = LoraParam(_dptr(P), _dptr(G), _dptr(Pb), P.numel())
-    _check(L.attt_lora_sgd_step(arr, len(params), float(lr), 1 if zero_grad else 0, _stream_ptr()))
+    _check(_native().lora_sgd_step(params, lr, zero_grad))
 
 
 def lora_forward(problems):
     """Grouped multi-adapter forward: for every problem, y <- RN_bf16(y + scale (x A^T) B^T) in
     place (y already holds the base projection). Each problem: dict(x, y, A, B, scale), bf16
     tensors x [rows, d_in], y [rows, d_out], A [r, d_in], B [d_out, r]."""
-    L = load()
-    torch = _torch()
-    arr = (LoraFwdProblem * max(len(problems), 1))()
-    for i, p in enumerate(problems):
-        x, y, A, B = p["x"], p["y"], p["A"], p["B"]
-        for k, t in (("x", x), ("y", y), ("A", A), ("B", B)):
-            _dev(t, k)
-            if t.dtype != torch.bfloat16 or t.dim() != 2:
-                raise ValueError(f"{k} must be a 2-D bfloat16 tensor")
-        arr[i] = LoraFwdProblem(_dptr(x), _dptr(y), _dptr(A), _dptr(B), x.shape[0], x.shape[1], y.shape[1],
-                                A.shape[0], float(p["scale"]))
-    _check(L.attt_lora_forward(arr, len(problems), _stream_ptr()))
+    _check(_native().lora_forward(problems))
 
 
 def lora_hot_swap(pairs):
     """Adapter swap into serving: each (src, dst) pair, src a float32 tensor and dst a bfloat16
     tensor of equal numel, gets dst = src rounded to nearest even, all in one launch."""
-    L = load()
-    torch = _torch()
-    arr = (LoraSwapItem * max(len(pairs), 1))()
-    for i, (src, dst) in enumerate(pairs):
-        _dev(src, "src")
-        _dev(dst, "dst")
-        if src.dtype != torch.float32 or dst.dtype != torch.bfloat16 or src.numel() != dst.numel():
-            raise ValueError("src must be float32 and dst bfloat16 of the same numel")
-        arr[i] = LoraSwapItem(_dptr(src), _dptr(dst), src.numel())
-    _check(L.attt_lora_hot_swap(arr, len(pairs), _stream_ptr()))
+    _check(_native().lora_hot_swap(pairs))
 
 
 # ------------------------------------------------------------------------------------------

@@ -14,6 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libattt.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 DEVICE_SOURCES = ["ngram.hip", "ngram_set.hip", "ce.hip", "ce_fused.hip", "lora.hip", "repetition.hip", "attention.hip", "lora_serve.hip"]
 HOST_SOURCES = ["api.cpp"]
@@ -38,6 +39,19 @@ def _compile(cmd):
     return r.stderr
 
 
+def _binding_cmds(cc, obj, out):
+    """(compile, link) of the Python module that marshals lists of tensors: against the torch and Python
+    of this interpreter, finding libattt.so beside itself."""
+    import sysconfig
+
+    from torch.utils import cpp_extension as ext
+    inc = [a for p in [*ext.include_paths(), sysconfig.get_paths()["include"]] for a in ("-isystem", p)]
+    lib = [a for p in ext.library_paths() for a in ("-L", p)]
+    return ([cc, *_common(), "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", *inc, "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj],
+            [cc, "-shared", "-fPIC", obj, "-o", out, *lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+             "-L", HERE, "-l:libattt.so", "-Wl,-rpath,$ORIGIN"])
+
+
 def build(verbose=False):
     os.makedirs(BUILD, exist_ok=True)
     cc = hipcc()
@@ -55,11 +69,16 @@ def build(verbose=False):
         cmd = [cc, *_common(), "-D__HIP_PLATFORM_AMD__", "-c", os.path.join(CSRC, src), "-o", obj]
         jobs.append(cmd)
         objs.append(obj)
+    obj = os.path.join(BUILD, "binding.cpp.o")
+    compile_binding, link_binding = _binding_cmds(cc, obj, BINDING + ".tmp")
+    jobs.insert(0, compile_binding)
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
         logs = list(ex.map(_compile, jobs))
     tmp = LIB + ".tmp"
     _compile([cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, LIB)
+    _compile(link_binding)
+    os.replace(BINDING + ".tmp", BINDING)
     if verbose:
         for log in logs:
             filtered = "\n".join(l for l in log.splitlines() if "packed-fp32-ops" not in l)
