@@ -202,19 +202,42 @@ attt_status ngram_validate(const int64_t* hoff, const int64_t* toff, int32_t E, 
   return ATTT_OK;
 }
 
-// History chunks: about two workgroups per CU over the whole call, at most 65535 positions
-// per chunk (the per-chunk counts are 16-bit) and at least 2048.
-NgramPlan ngram_plan(const int64_t* hoff, const int64_t* toff, int32_t E, int32_t n) {
+// History chunks: at most 65535 positions per chunk (the per-chunk counts are 16-bit) and at least 2048.
+// A count workgroup's LDS table takes most of a CU, so workgroups run in rounds of 256: the chunks are
+// the shortest with which the call fits the fewest whole rounds. (16 episodes of 524288 history tokens
+// and 24 partitions in chunks of work / 256 made 264 workgroups, a second round for eight of them:
+// 56 us; 240 workgroups in one round take 31.)
+// `smallest`: the longest chunks instead, i.e. the least scratch.
+NgramPlan ngram_plan(const int64_t* hoff, const int64_t* toff, int32_t E, int32_t n, bool smallest = false) {
   NgramPlan P;
+  struct Part {
+    int64_t parts, hist;
+  };
+  std::vector<Part> parts;
   int64_t work = 0;
   for (int32_t e = 0; e < E; ++e) {
     const int64_t L = toff[e + 1] - toff[e], H = hoff[e + 1] - hoff[e];
-    const int64_t Q = std::max<int64_t>(0, L - n + 1);
-    work += ceil_div(Q, kQMax) * std::max<int64_t>(0, H - n + 1);
+    const Part q{ceil_div(std::max<int64_t>(0, L - n + 1), kQMax), std::max<int64_t>(0, H - n + 1)};
+    work += q.parts * q.hist;
+    if (q.parts * q.hist > 0) parts.push_back(q);
   }
-  // one count workgroup per CU (its LDS table takes most of the CU): about 256 chunks in all,
-  // so every workgroup sets its table up once
-  const int64_t chunk_len = std::min<int64_t>(65535, std::max<int64_t>(2048, ceil_div(work, 256)));
+  auto blocks = [&](int64_t len) {
+    int64_t t = 0;
+    for (const Part& q : parts) t += q.parts * ceil_div(q.hist, len);
+    return t;
+  };
+  constexpr int64_t kMin = 2048, kMax = 65535, kRound = 256;
+  int64_t chunk_len = kMax;
+  if (work > 0 && !smallest) {
+    const int64_t rounds = ceil_div(blocks(kMax), kRound);
+    int64_t lo = std::min(kMax, std::max(kMin, ceil_div(work, rounds * kRound)));
+    for (int64_t hi = kMax; lo < hi;) {  // the shortest chunk with at most `rounds` rounds
+      const int64_t mid = (lo + hi) / 2;
+      if (blocks(mid) <= rounds * kRound) hi = mid;
+      else lo = mid + 1;
+    }
+    chunk_len = lo;
+  }
   for (int32_t e = 0; e < E; ++e) {
     NgramEpPlan ep{};
     ep.tok_base = toff[e];
@@ -294,6 +317,7 @@ extern "C" attt_status attt_ngram_weights_noalloc(const int32_t* history, const 
                                     weights);
   if (st) return st;
   NgramPlan P = ngram_plan(history_offsets, token_offsets, num_episodes, n);
+  if (P.total > kNgramScratchBytes) P = ngram_plan(history_offsets, token_offsets, num_episodes, n, true);
   if (P.total > kNgramScratchBytes)
     return fail(ATTT_EUNSUPPORTED,
                 "ngram_noalloc: the call needs %zu bytes of scratch, beyond the static %zu-byte buffer "

@@ -43,3 +43,24 @@ def test_noalloc_rejects_beyond_scratch(attt):
     with pytest.raises(attt.AtttError) as e:
         attt.ngram_weights_noalloc(h, hoff, x, toff, n=3)
     assert e.value.status == 3
+
+
+def test_noalloc_takes_longer_chunks_near_the_scratch_limit(attt):
+    """80 partitions against 20 x 65535 history tokens: the chunks that fill whole rounds of workgroups
+    need more scratch than the static buffer has, the longest ones fit. Same f and w either way."""
+    import torch
+    L, H = 80 * 4096, 20 * 65535
+    hoff, toff = np.array([0, H], np.int64), np.array([0, L], np.int64)
+    assert attt.ngram_workspace_size(hoff, toff, 2) > 1 << 24
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    h = torch.randint(0, 3000, (H,), generator=g, device="cuda", dtype=torch.int32)
+    x = torch.randint(0, 3000, (L,), generator=g, device="cuda", dtype=torch.int32)
+    fw, ww = attt.ngram_weights(h, hoff, x, toff, n=2)
+    fs, ws = attt.ngram_weights_noalloc(h, hoff, x, toff, n=2)
+    key = h[:-1].long() * 3000 + h[1:]
+    cnt = torch.bincount(key, minlength=9000000)[x[:-1].long() * 3000 + x[1:]]
+    want = torch.zeros(L, dtype=torch.int64, device="cuda")
+    want[:-1] = cnt
+    want[1:] = torch.maximum(want[1:], cnt)
+    assert torch.equal(fw.long(), want) and torch.equal(fw, fs) and torch.equal(ww, ws)
