@@ -502,8 +502,11 @@ attt_status rep_plan(const int64_t* toff, const int64_t* etx, int32_t E, RepPlan
     const int64_t cand = etx[e + 1] - 1;
     int64_t longest = toff[cand + 1] - toff[cand];
     for (int64_t t = etx[e]; t < cand; ++t) longest = std::max(longest, toff[t + 1] - toff[t]);
-    // a partition sees about kRepPartWords words of each text: its LDS sets stay below 1/4 full
+    // A partition sees about kRepPartWords words of each text. Texts of at most 8192 words cannot fill
+    // sets of twice the partition's words whatever their hashes; longer ones get sets of kRepSlots, a
+    // quarter full. Small sets let several workgroups share a CU.
     ep.parts = (int32_t)std::max<int64_t>(1, ceil_div(longest, kRepPartWords));
+    ep.slots = longest > 2 * kRepPartWords ? kRepSlots : std::max(256, next_pow2((int)(2 * std::min<int64_t>(longest, kRepPartWords))));
     ep.wg_global = P.records;
     ep.pair_base = P.pairs;
     P.records += (int64_t)(ep.ntexts - 1) * ep.parts;
@@ -548,13 +551,14 @@ extern "C" attt_status attt_update_repetition(const int32_t* words, const int64_
   for (size_t e0 = 0; e0 < P.eps.size(); e0 += kEpBatch) {
     RepBatch b{};
     b.count = (int32_t)std::min<size_t>(kEpBatch, P.eps.size() - e0);
-    int wgs = 0;
+    int wgs = 0, slots = 0;
     for (int i = 0; i < b.count; ++i) {
       b.e[i] = P.eps[e0 + i];
       b.e[i].wg_begin = wgs;
       wgs += (b.e[i].ntexts - 1) * b.e[i].parts;
+      slots = std::max(slots, b.e[i].slots);
     }
-    HIP_TRY(launch_rep_count(b, wgs, words, text_offsets_dev, counts, s), "rep_count");
+    HIP_TRY(launch_rep_count(b, wgs, slots, words, text_offsets_dev, counts, s), "rep_count");
     HIP_TRY(launch_rep_reduce(b, counts, tau, rho, nu, skip, best, pair_counts, s), "rep_reduce");
   }
   return ATTT_OK;

@@ -122,7 +122,7 @@ hipError_t launch_ngram_weight(const NgramEpBatch& b, int total_blocks, int n, f
                                float* weights, hipStream_t s);
 
 // ---- update-text repetition (Eq. 6-7) ------------------------------------------------------
-constexpr int kRepSlots = 16384;        // entries of each LDS word set of the count kernel
+constexpr int kRepSlots = 16384;        // entries of the largest LDS word set of the count kernel
 constexpr int kRepPartWords = 4096;     // words per hash partition the host plans for (load <= 1/4)
 struct RepEp {
   int64_t text0;      // first text of the episode (index into the text offsets)
@@ -132,13 +132,15 @@ struct RepEp {
   int32_t parts;      // hash partitions per pair
   int32_t wg_begin;   // first count-kernel workgroup of the episode within the launch
   int32_t ep;         // episode index (outputs)
+  int32_t slots;      // entries of each LDS word set, a power of two
 };
 struct RepBatch {
   int32_t count;
   int32_t pad;
   RepEp e[kEpBatch];
 };
-hipError_t launch_rep_count(const RepBatch& b, int total_wgs, const int32_t* words, const int64_t* toff,
+// slots: the largest of the batch's episodes
+hipError_t launch_rep_count(const RepBatch& b, int total_wgs, int slots, const int32_t* words, const int64_t* toff,
                             int32_t* counts, hipStream_t s);
 hipError_t launch_rep_reduce(const RepBatch& b, const int32_t* counts, double tau, double* rho, double* nu,
                              int32_t* skip, int32_t* best, int32_t* pair_counts, hipStream_t s);

@@ -2,14 +2,14 @@
 // of the episode of the Jaccard similarity of the word sets W(x_k) and W(x'), nu = 1 - rho, and
 // the sequence-level filter that skips an update when nu < tau.
 //
-//   rep_count_kernel   one 1024-thread workgroup per (previous text, hash partition). Words are
+//   rep_count_kernel   one workgroup per (previous text, hash partition). Words are
 //                      split into `parts` partitions by the high bits of a 32-bit hash (the
 //                      MurmurHash3 finalizer), so |A|, |B| and |A & B| are sums over partitions
 //                      and a partition's sets fit LDS whatever the text lengths. The workgroup
 //                      inserts its partition's words of the candidate into one LDS hash set and
 //                      those of the previous text into another; a new entry of the second set
 //                      that is also in the first counts towards the intersection.
-//   rep_reduce_kernel  one thread per episode: sums the partitions, takes the maximum Jaccard
+//   rep_reduce_kernel  one wave per episode: sums the partitions, takes the maximum Jaccard
 //                      over the previous texts by exact cross-multiplication (the first maximum
 //                      wins a tie), rho = the nearest float64 to |A & B| / |A | B|,
 //                      nu = RN(1 - rho), skip = nu < tau.
@@ -33,35 +33,54 @@ __device__ __forceinline__ uint32_t word_hash(int32_t w) {
 // partition of a hash: multiply-shift range reduction of its high 24 bits
 __device__ __forceinline__ int part_of(uint32_t h, int parts) { return (int)(((h >> 8) * (uint32_t)parts) >> 24); }
 
-// Inserts w into the open-addressing set `tab` (kRepSlots entries, linear probing from the
-// hash's low bits). Returns 1 if w was new, 0 if present, -1 if the set is full (every probe
-// taken: the caller flags the call). The value kRepEmpty marks a free slot.
-__device__ __forceinline__ int set_insert(uint32_t* tab, uint32_t h, uint32_t w) {
-  uint32_t s = h & (kRepSlots - 1);
-  for (int probe = 0; probe < kRepSlots; ++probe) {
-    const uint32_t cur = atomicCAS(tab + s, kRepEmpty, w);
+// A set is an array of buckets of four words (bmask + 1 of them), searched bucket by bucket from the
+// hash's low bits; the slots of a bucket are taken in order and kRepEmpty marks a free one, so a bucket
+// with a free slot ends every search, and one 16-byte read settles nearly all of them (a wave walks on
+// for as long as any of its lanes does).
+//
+// set_insert returns 1 if w was new, 0 if present, -1 if the set is full (the caller flags the call).
+__device__ __forceinline__ int set_insert(uint32_t* tab, uint32_t bmask, uint32_t h, uint32_t w) {
+  uint32_t b = h & bmask;
+  for (uint32_t probe = 0; probe <= bmask;) {
+    const u32x4 e = *reinterpret_cast<const u32x4*>(tab + 4 * b);
+    if (e[0] == w || e[1] == w || e[2] == w || e[3] == w) return 0;
+    const int free = e[0] == kRepEmpty ? 0 : e[1] == kRepEmpty ? 1 : e[2] == kRepEmpty ? 2 : e[3] == kRepEmpty ? 3 : 4;
+    if (free == 4) {
+      b = (b + 1u) & bmask;
+      ++probe;
+      continue;
+    }
+    const uint32_t cur = atomicCAS(tab + 4 * b + free, kRepEmpty, w);
     if (cur == kRepEmpty) return 1;
     if (cur == w) return 0;
-    s = (s + 1u) & (kRepSlots - 1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");  // another word took the slot: read the bucket again
   }
   return -1;
 }
-__device__ __forceinline__ bool set_contains(const uint32_t* tab, uint32_t h, uint32_t w) {
-  uint32_t s = h & (kRepSlots - 1);
-  for (int probe = 0; probe < kRepSlots; ++probe) {
-    const uint32_t cur = tab[s];
-    if (cur == w) return true;
-    if (cur == kRepEmpty) return false;
-    s = (s + 1u) & (kRepSlots - 1);
+__device__ __forceinline__ bool set_contains(const uint32_t* tab, uint32_t bmask, uint32_t h, uint32_t w) {
+  uint32_t b = h & bmask;
+  for (uint32_t probe = 0; probe <= bmask; ++probe) {
+    const u32x4 e = *reinterpret_cast<const u32x4*>(tab + 4 * b);
+    if (e[0] == w || e[1] == w || e[2] == w || e[3] == w) return true;
+    if (e[3] == kRepEmpty) return false;
+    b = (b + 1u) & bmask;
   }
   return false;
 }
 
+// Bound by latency: the words of both texts, then their probes of the LDS sets. The first kRepAhead
+// words per thread of both texts are loaded before the sets are cleared, and the sets are as small as
+// the texts allow (64 KiB for texts of 4096 words, so two workgroups share a CU). 512 such pairs took
+// 32 us with 128 KiB sets probed word by word, 26 us now.
+constexpr int kRepAhead = 4;
+
 __global__ __launch_bounds__(1024) void rep_count_kernel(RepBatch batch, const int32_t* __restrict__ words,
                                                          const int64_t* __restrict__ toff,
                                                          int32_t* __restrict__ counts) {
-  int ei = 0;
-  while (ei + 1 < batch.count && batch.e[ei + 1].wg_begin <= (int)blockIdx.x) ++ei;
+  // the last episode whose first workgroup is at most this one (kEpBatch = 64: one per lane)
+  const int ln = threadIdx.x & 63;
+  const int ei = __builtin_amdgcn_readfirstlane(
+      __popcll(__ballot(ln < batch.count && batch.e[ln < batch.count ? ln : 0].wg_begin <= (int)blockIdx.x)) - 1);
   const RepEp E = batch.e[ei];
   const int local = (int)blockIdx.x - E.wg_begin;
   const int pair = local / E.parts, part = local % E.parts;
@@ -69,38 +88,51 @@ __global__ __launch_bounds__(1024) void rep_count_kernel(RepBatch batch, const i
   const int64_t a0 = toff[ct], a1 = toff[ct + 1], b0 = toff[bt], b1 = toff[bt + 1];
 
   extern __shared__ __align__(16) uint8_t smem[];
-  uint32_t* ta = reinterpret_cast<uint32_t*>(smem);  // [kRepSlots] candidate words of the partition
-  uint32_t* tb = ta + kRepSlots;                     // [kRepSlots] previous text's words
+  uint32_t* ta = reinterpret_cast<uint32_t*>(smem);  // [slots] candidate words of the partition
+  uint32_t* tb = ta + E.slots;                       // [slots] previous text's words
+  const uint32_t mask = (uint32_t)(E.slots >> 2) - 1u;  // of the buckets
   __shared__ int cnt[4];                             // |A|, |B|, |A & B|, full
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  int32_t wa[kRepAhead], wb[kRepAhead];
+#pragma unroll
+  for (int u = 0; u < kRepAhead; ++u) {
+    const int64_t i = tid + (int64_t)u * nt;
+    wa[u] = a0 + i < a1 ? words[a0 + i] : 0;
+    wb[u] = b0 + i < b1 ? words[b0 + i] : 0;
+  }
   {
     u32x4* t4 = reinterpret_cast<u32x4*>(smem);
-    for (int i = tid; i < 2 * kRepSlots / 4; i += 1024) t4[i] = u32x4{kRepEmpty, kRepEmpty, kRepEmpty, kRepEmpty};
+    for (int i = tid; i < E.slots / 2; i += nt) t4[i] = u32x4{kRepEmpty, kRepEmpty, kRepEmpty, kRepEmpty};
     if (tid < 4) cnt[tid] = 0;
   }
   __syncthreads();
-  int na = 0, full = 0;
-  for (int64_t i = a0 + tid; i < a1; i += 1024) {
-    const int32_t w = words[i];
+  int na = 0, nb = 0, ni = 0, full = 0;
+  auto insert_a = [&](int32_t w) {
     const uint32_t h = word_hash(w);
-    if (part_of(h, E.parts) != part) continue;
-    const int r = set_insert(ta, h, (uint32_t)w);
+    if (part_of(h, E.parts) != part) return;
+    const int r = set_insert(ta, mask, h, (uint32_t)w);
     na += r > 0;
     full |= r < 0;
-  }
-  __syncthreads();
-  int nb = 0, ni = 0;
-  for (int64_t i = b0 + tid; i < b1; i += 1024) {
-    const int32_t w = words[i];
+  };
+  auto insert_b = [&](int32_t w) {
     const uint32_t h = word_hash(w);
-    if (part_of(h, E.parts) != part) continue;
-    const int r = set_insert(tb, h, (uint32_t)w);
+    if (part_of(h, E.parts) != part) return;
+    const int r = set_insert(tb, mask, h, (uint32_t)w);
     if (r > 0) {
       ++nb;
-      ni += set_contains(ta, h, (uint32_t)w);
+      ni += set_contains(ta, mask, h, (uint32_t)w);
     }
     full |= r < 0;
-  }
+  };
+#pragma unroll
+  for (int u = 0; u < kRepAhead; ++u)
+    if (a0 + tid + (int64_t)u * nt < a1) insert_a(wa[u]);
+  for (int64_t i = a0 + tid + (int64_t)kRepAhead * nt; i < a1; i += nt) insert_a(words[i]);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kRepAhead; ++u)
+    if (b0 + tid + (int64_t)u * nt < b1) insert_b(wb[u]);
+  for (int64_t i = b0 + tid + (int64_t)kRepAhead * nt; i < b1; i += nt) insert_b(words[i]);
   // per-thread counts, then one LDS atomic each
   if (na) atomicAdd(cnt + 0, na);
   if (nb) atomicAdd(cnt + 1, nb);
@@ -110,24 +142,26 @@ __global__ __launch_bounds__(1024) void rep_count_kernel(RepBatch batch, const i
   if (tid < 4) counts[(E.wg_global + local) * 4 + tid] = cnt[tid];
 }
 
+// One wave per episode: lane k takes the previous texts k, k + 64, ..., then the lanes' best fractions
+// meet (a single thread walking an episode's texts took 11 us for 32 of them).
 __global__ __launch_bounds__(64) void rep_reduce_kernel(RepBatch batch, const int32_t* __restrict__ counts, double tau,
                                                         double* __restrict__ rho, double* __restrict__ nu,
                                                         int32_t* __restrict__ skip, int32_t* __restrict__ best,
                                                         int32_t* __restrict__ pair_counts) {
-  const int ei = (int)threadIdx.x;
-  if (ei >= batch.count) return;
-  const RepEp E = batch.e[ei];
-  int64_t bi = 1, bu = 1;  // best fraction bi / bu, starting below every J (0 / 1 is attained)
+  const RepEp E = batch.e[blockIdx.x];
+  const int lane = threadIdx.x;
+  int64_t bi = 0, bu = 1;  // this lane's best fraction bi / bu and its text; none yet
   int bk = -1;
   bool bad = false;
-  for (int k = 0; k + 1 < E.ntexts; ++k) {
+  for (int k = lane; k + 1 < E.ntexts; k += 64) {
     int64_t a = 0, b = 0, in = 0;
+#pragma unroll 4
     for (int p = 0; p < E.parts; ++p) {
-      const int32_t* c = counts + (E.wg_global + (int64_t)k * E.parts + p) * 4;
-      a += c[0];
-      b += c[1];
-      in += c[2];
-      bad |= c[3] != 0;
+      const int4 c = *reinterpret_cast<const int4*>(counts + (E.wg_global + (int64_t)k * E.parts + p) * 4);
+      a += c.x;
+      b += c.y;
+      in += c.z;
+      bad |= c.w != 0;
     }
     const int64_t un = a + b - in;
     if (pair_counts) {
@@ -142,6 +176,15 @@ __global__ __launch_bounds__(64) void rep_reduce_kernel(RepBatch batch, const in
       bu = ju;
     }
   }
+  // the larger fraction wins, the earlier text among equals
+  for (int o = 32; o > 0; o >>= 1) {
+    const int64_t oi = __shfl_xor(bi, o, 64), ou = __shfl_xor(bu, o, 64);
+    const int ok = __shfl_xor(bk, o, 64);
+    const bool take = ok >= 0 && (bk < 0 || oi * bu > bi * ou || (oi * bu == bi * ou && ok < bk));
+    if (take) bi = oi, bu = ou, bk = ok;
+  }
+  bad = __ballot(bad) != 0;
+  if (lane != 0) return;
   double r = 0.0;
   if (bk >= 0) r = __ddiv_rn((double)bi, (double)bu);
   const double v = __dsub_rn(1.0, r);
@@ -159,19 +202,21 @@ __global__ __launch_bounds__(64) void rep_reduce_kernel(RepBatch batch, const in
   best[e] = bk;
 }
 
-hipError_t launch_rep_count(const RepBatch& b, int total_wgs, const int32_t* words, const int64_t* toff,
+hipError_t launch_rep_count(const RepBatch& b, int total_wgs, int slots, const int32_t* words, const int64_t* toff,
                             int32_t* counts, hipStream_t s) {
   if (total_wgs <= 0) return hipSuccess;
   static bool attr = false;
-  const size_t lds = (size_t)2 * kRepSlots * 4;
+  const size_t lds = (size_t)2 * slots * 4;
   if (!attr) {
     hipError_t e = hipFuncSetAttribute((const void*)rep_count_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds);
+                                       2 * kRepSlots * 4);
     if (e != hipSuccess) return e;
     attr = true;
   }
   KernelTimer t(K_REP_COUNT, s);
-  hipLaunchKernelGGL(rep_count_kernel, dim3(total_wgs), dim3(1024), lds, s, b, words, toff, counts);
+  // four words of each text per thread up to 1024 threads
+  const int threads = slots <= 2048 ? 256 : slots <= 4096 ? 512 : 1024;
+  hipLaunchKernelGGL(rep_count_kernel, dim3(total_wgs), dim3(threads), lds, s, b, words, toff, counts);
   return hipGetLastError();
 }
 
@@ -179,7 +224,7 @@ hipError_t launch_rep_reduce(const RepBatch& b, const int32_t* counts, double ta
                              int32_t* skip, int32_t* best, int32_t* pair_counts, hipStream_t s) {
   if (b.count <= 0) return hipSuccess;
   KernelTimer t(K_REP_REDUCE, s);
-  hipLaunchKernelGGL(rep_reduce_kernel, dim3(1), dim3(64), 0, s, b, counts, tau, rho, nu, skip, best, pair_counts);
+  hipLaunchKernelGGL(rep_reduce_kernel, dim3(b.count), dim3(64), 0, s, b, counts, tau, rho, nu, skip, best, pair_counts);
   return hipGetLastError();
 }
 

@@ -110,3 +110,21 @@ def test_workload_histories(attt, key):
     got, want = _run(attt, episodes)
     _check(got, want)
     note(f"rho {np.round(got['rho'][:4], 4).tolist()} skip {got['skip'][:8].tolist()}")
+
+
+@pytest.mark.parametrize("longest", [1, 128, 129, 1025, 4096, 4097, 8192, 8193])
+def test_set_sizes(attt, longest):
+    """Texts around the lengths where the word sets, the partitions and the workgroup change, all words
+    distinct (the fullest sets) and shared by a third."""
+    rng = np.random.default_rng(longest)
+    texts = [rng.permutation(3 * longest)[:max(1, longest // k)].astype(np.int32) for k in (2, 1, 3, 1)]
+    toff = np.zeros(5, np.int64)
+    toff[1:] = np.cumsum([len(t) for t in texts])
+    note(f"repetition, texts up to {longest} words")
+    rho, nu, skip, best, pairs = (t.cpu().numpy() for t in attt.update_repetition(
+        dev_i32(np.concatenate(texts)), toff, np.array([0, 4], np.int64), tau=0.5, want_pairs=True))
+    cand = set(texts[-1].tolist())
+    want = [(len(cand & set(t.tolist())), len(cand | set(t.tolist()))) for t in texts[:-1]]
+    assert pairs.tolist() == [list(w) for w in want]
+    j = [i / u for i, u in want]
+    assert rho[0] == max(j) and best[0] == j.index(max(j)) and nu[0] == 1.0 - rho[0] and skip[0] == (nu[0] < 0.5)
