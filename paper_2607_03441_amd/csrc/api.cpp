@@ -449,18 +449,9 @@ extern "C" attt_status attt_attention_bwd(const void* q, const void* k, const vo
     for (int i = 0; i < b.count; ++i) {
       b.e[i].row0 = off[e0 + i];
       b.e[i].L = (int32_t)(off[e0 + i + 1] - off[e0 + i]);
-      b.e[i].blocks = (int32_t)ceil_div(b.e[i].L, 64);
     }
-    // workgroups per episode: blocks x heads (forward statistics, dQ) or x kv_heads (dK, dV)
-    for (int kernel = 0; kernel < 3; ++kernel) {
-      const int per = kernel == 1 ? kv_heads : heads;
-      int wgs = 0;
-      for (int i = 0; i < b.count; ++i) {
-        b.e[i].wg_begin = wgs;
-        wgs += b.e[i].blocks * per;
-      }
-      HIP_TRY(launch_attn(kernel, a, b, wgs, s), kernel == 0 ? "attn_fwd_stats" : kernel == 1 ? "attn_dkdv" : "attn_dq");
-    }
+    for (int kernel = 0; kernel < 3; ++kernel)
+      HIP_TRY(launch_attn(kernel, a, b, s), kernel == 0 ? "attn_fwd_stats" : kernel == 1 ? "attn_dkdv" : "attn_dq");
   }
   return ATTT_OK;
 }

@@ -5,15 +5,14 @@
 //   D = rowsum(dO * O),  dP = dO V^T,  dS = P * (dP - D),
 //   dQ = scale dS K,  dK = scale dS^T Q,  dV = P^T dO.
 // Three kernels, each recomputing S from Q and K on v_mfma_f32_16x16x32_bf16 over blocks of 64
-// keys, 256 threads (four waves of 16 rows; 32 query rows in the statistics kernel), blocks in
-// the causal order with the longest rows first, the next block's global loads in flight while
-// the current one computes:
-//   attn_fwd_stats_kernel  per (query head, 128-query block): lse and D (online softmax; D as
+// keys, 256 threads (four waves of 16 rows, or of 32 query rows), blocks in the causal order with
+// the longest rows first, the next block's global loads in flight while the current one computes:
+//   attn_fwd_stats_kernel  per (query head, 64- or 128-query block): lse and D (online softmax; D as
 //                          the softmax-weighted sum of dP = dO V^T, so O is never formed)
 //   attn_dkdv_kernel       per (key/value head, 64-key block): dK and dV accumulated in
 //                          registers over every query head of the group and every later query
 //                          block, in a fixed order (no atomics)
-//   attn_dq_kernel         per (query head, 64-query block): dQ over the allowed key blocks
+//   attn_dq_kernel         per (query head, 64- or 128-query block): dQ over the allowed key blocks
 // The operand that stays in a wave (its 16 queries, or its 16 keys) is held in registers as
 // the B operand of the score products, so each lane ends up with 16 scores of its own row. The
 // probabilities (or dS) of that row then enter the second product (P^T dO, dS^T Q, dS K)
@@ -36,7 +35,6 @@ namespace attt {
 namespace {
 constexpr int DH = 128;     // head dimension
 constexpr int BLK = 64;     // query / key rows per block
-constexpr int SBLK = 128;   // query rows per block of the statistics kernel
 constexpr int PR = DH + 8;  // LDS pitch of a [64][128] tile (bf16): 272 B, conflict-free b128 reads
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -136,36 +134,40 @@ __device__ __forceinline__ bf16x8 trfrag(const bf16_t* R, int c0, int u, int lan
   return __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, b.x, b.y});
 }
 
-// lse and D = rowsum(dO * O) of one (query head, 128-query block). Wave w owns queries 32 w ..
-// 32 w + 31 as two tiles of 16; their Q and dO fragments stay in registers. Per key block: S^T =
+// lse and D = rowsum(dO * O) of one (query head, 64 QT-query block). Wave w owns queries 16 QT w ..
+// + 16 QT - 1 as QT tiles of 16; their Q and dO fragments stay in registers. Per key block: S^T =
 // K Q^T and dP^T = V dO^T with the keys on the MFMA rows, each K and V fragment read from LDS once
-// for both tiles, so each lane holds 16 scores of each of its two queries and the online softmax
+// for all tiles, so each lane holds 16 scores of each of its QT queries and the online softmax
 // of a query is a reduction over the lane's registers and its three partner lanes (lanes l,
 // l + 16, l + 32, l + 48 hold the same queries). O = P V is never formed: since
 // O = sum_k P_k V_k, D = sum_k P_k (dO . V_k) = sum_k P_k dP_k, so each lane keeps, beside the
 // running softmax sum, the running sum of p dP over its keys, both rescaled by the same factor
 // when the running max grows; the four partial sums of a query are added at the end.
+template <int QT>
 __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, AttnBatch b) {
+  constexpr int QBLK = 64 * QT;
   int ei, h, qb;
   attn_locate(b, a.heads, true, ei, h, qb);
   const AttnEp E = b.e[ei];
   const int kh = h / (a.heads / a.kv_heads);
-  const int q0 = qb * SBLK, nq = min(SBLK, E.L - q0);
+  const int q0 = qb * QBLK, nq = min(QBLK, E.L - q0);
   extern __shared__ __align__(16) uint8_t smem[];  // two buffers of [K tile][V tile], [64][PR] each
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int l16 = lane & 15, q4 = lane >> 4;
   const int64_t qs = (int64_t)a.heads * DH, ks = (int64_t)a.kv_heads * DH;
-  bf16x8 qf[2][4], of[2][4];
+  bf16x8 qf[QT][4], of[QT][4];
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int qry = 32 * w + 16 * c + l16;
+  for (int c = 0; c < QT; ++c) {
+    const int qry = 16 * QT * w + 16 * c + l16;
     load_key_frags(qf[c], a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
     load_key_frags(of[c], a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
   }
   const float sl = a.scale * kLog2e;
   // per query tile: running max (base 2, the same in the query's four lanes), and this lane's
   // running sums of p and of p dP over its keys
-  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.0f, 0.0f}, dacc[2] = {0.0f, 0.0f};
+  float m[QT], l[QT], dacc[QT];
+#pragma unroll
+  for (int c = 0; c < QT; ++c) m[c] = -INFINITY, l[c] = 0.0f, dacc[c] = 0.0f;
   u32x4 fk[4], fv[4];
   auto fetch = [&](int kb) {
     const int k0 = kb * BLK, nk = min(BLK, E.L - k0);
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, Attn
     fetch_block(fv, a.v + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, nk, tid);
   };
   const int kb_last = (q0 + nq - 1) / BLK;  // the key block of the block's last query
-  const int wq0 = q0 + 32 * w;              // this wave's first query
+  const int wq0 = q0 + 16 * QT * w;              // this wave's first query
   fetch(0);
   store_block(fk, kv_tile(smem, 0, 0), tid);
   store_block(fv, kv_tile(smem, 0, 1), tid);
@@ -184,13 +186,13 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, Attn
     if (kb < kb_last) fetch(kb + 1);  // the next key block loads while this one computes
     // A wave whose queries all precede the block has nothing to add (it still takes part in
     // the barriers and the stores).
-    if (k0 <= wq0 + 31) {
+    if (k0 <= wq0 + 16 * QT - 1) {
       const bf16_t* Ks = kv_tile(smem, kb & 1, 0);
       const bf16_t* Vs = kv_tile(smem, kb & 1, 1);
       // S^T[16 tt + 4 q4 + r][query] and dP^T likewise, for both query tiles
-      f32x4 st[2][4], dp[2][4];
+      f32x4 st[QT][4], dp[QT][4];
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int c = 0; c < QT; ++c)
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) st[c][tt] = f32x4{0, 0, 0, 0}, dp[c][tt] = f32x4{0, 0, 0, 0};
 #pragma unroll
@@ -202,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, Attn
           const bf16x8 av = __builtin_bit_cast(
               bf16x8, *reinterpret_cast<const u32x4*>(Vs + (16 * tt + l16) * PR + 32 * s4 + 8 * q4));
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
+          for (int c = 0; c < QT; ++c) {
             st[c][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak, qf[c][s4], st[c][tt], 0, 0, 0);
             dp[c][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, of[c][s4], dp[c][tt], 0, 0, 0);
           }
@@ -212,15 +214,15 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, Attn
 #pragma unroll
       for (int n = 0; n < 16; ++n) {
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * QT, 0);
       }
       // online softmax (base-2 exponent of scale * S) over this block's keys 16 tt + 4 q4 + r.
       // A whole key block that ends at or before the wave's first query is entirely allowed:
       // no mask there.
       auto softmax = [&](auto masked) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int qry = 32 * w + 16 * c + l16;
+        for (int c = 0; c < QT; ++c) {
+          const int qry = 16 * QT * w + 16 * c + l16;
           float mx = -INFINITY, sum = 0.0f, dsum = 0.0f;
 #pragma unroll
           for (int tt = 0; tt < 4; ++tt)
@@ -261,8 +263,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, Attn
     }
   }
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int qry = 32 * w + 16 * c + l16;
+  for (int c = 0; c < QT; ++c) {
+    const int qry = 16 * QT * w + 16 * c + l16;
     float lc = l[c], dc = dacc[c];
     lc += __shfl_xor(lc, 16, 64);
     lc += __shfl_xor(lc, 32, 64);
@@ -409,136 +411,178 @@ __global__ __launch_bounds__(256, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch
   }
 }
 
-// dQ of one (query head, 64-query block). Wave w owns queries 16 w .. 16 w + 15; their Q and
-// dO fragments stay in registers. Per key block: S^T = K Q^T and dP^T = V dO^T with the keys on
-// the MFMA rows and this wave's queries on the columns, so each lane holds 16 (key, query)
-// values of its own query; dS then feeds dQ += dS K as the A operand (the contraction runs over
-// the keys in the order the lane holds them), with the B operand from the transposed K tile.
+// dQ of one (query head, 64 QT-query block). Wave w owns queries 16 QT w .. + 16 QT - 1 as QT tiles of
+// 16; their Q and dO fragments stay in registers. Per half of a key block (32 keys): S^T = K Q^T and
+// dP^T = V dO^T with the keys on the MFMA rows and this wave's queries on the columns, so each lane
+// holds 8 (key, query) values of its own query of a tile; dS then feeds dQ += dS K as the A operand
+// (the contraction runs over the keys in the order the lane holds them), with the B operand from the
+// row-major K tile through transposing reads. With one tile per wave the LDS reads bound it (1792 of
+// 2140 cycles a block and workgroup at 8192 rows, 32 heads); two tiles halve them per product, and
+// halves of 32 keys, K's next block fetched in the first and V's in the second, keep that within 248
+// VGPRs without spills: 1118 -> 867 us.
+template <int QT>
 __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnArgs a, AttnBatch b) {
+  constexpr int QBLK = 64 * QT;
   int ei, h, qb;
   attn_locate(b, a.heads, true, ei, h, qb);
   const AttnEp E = b.e[ei];
   const int kh = h / (a.heads / a.kv_heads);
-  const int q0 = qb * BLK, nq = min(BLK, E.L - q0);
+  const int q0 = qb * QBLK, nq = min(QBLK, E.L - q0);
   extern __shared__ __align__(16) uint8_t smem[];  // two buffers of [K tile][V tile], [64][PR] each
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int l16 = lane & 15, q4 = lane >> 4;
-  const int qry = 16 * w + l16;  // this lane's query in the block
   const int64_t qs = (int64_t)a.heads * DH, ks = (int64_t)a.kv_heads * DH;
-  bf16x8 qf[4], of[4];
-  load_key_frags(qf, a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
-  load_key_frags(of, a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
-  const int64_t t = (int64_t)h * a.N + E.row0 + q0 + qry;
-  const float ls = qry < nq ? a.lse[t] * kLog2e : INFINITY;  // absent queries: P = 0
-  const float dd = qry < nq ? a.dsum[t] : 0.0f;
-  f32x4 dq[8];
+  const int wq = 16 * QT * w;  // this wave's first query in the block
+  bf16x8 qf[QT][4], of[QT][4];
+  float ls[QT], dd[QT];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) dq[j] = f32x4{0, 0, 0, 0};
+  for (int c = 0; c < QT; ++c) {
+    const int qry = wq + 16 * c + l16;
+    load_key_frags(qf[c], a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
+    load_key_frags(of[c], a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
+    const int64_t t = (int64_t)h * a.N + E.row0 + q0 + qry;
+    ls[c] = qry < nq ? a.lse[t] * kLog2e : INFINITY;  // absent queries: P = 0
+    dd[c] = qry < nq ? a.dsum[t] : 0.0f;
+  }
+  f32x4 dq[QT][8];
+#pragma unroll
+  for (int c = 0; c < QT; ++c)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) dq[c][j] = f32x4{0, 0, 0, 0};
   const float sl = a.scale * kLog2e;
-  u32x4 fk[4], fv[4];
-  auto fetch = [&](int kb) {
+  u32x4 f[4];
+  auto fetch = [&](const bf16_t* src, int kb) {
     const int k0 = kb * BLK, nk = min(BLK, E.L - k0);
-    fetch_block(fk, a.k + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, nk, tid);
-    fetch_block(fv, a.v + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, nk, tid);
+    fetch_block(f, src + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, nk, tid);
   };
-  fetch(0);
-  store_block(fk, kv_tile(smem, 0, 0), tid);
-  store_block(fv, kv_tile(smem, 0, 1), tid);
-  for (int kb = 0; kb <= qb; ++kb) {
-    const int k0 = kb * BLK, nk = min(BLK, E.L - k0);
+  const int kb_last = (q0 + nq - 1) / BLK;  // the key block of the block's last query
+  fetch(a.k, 0);
+  store_block(f, kv_tile(smem, 0, 0), tid);
+  fetch(a.v, 0);
+  store_block(f, kv_tile(smem, 0, 1), tid);
+  for (int kb = 0; kb <= kb_last; ++kb) {
+    const int k0 = kb * BLK;
     // This block's tiles are stored, and every wave is done with the other buffer.
     __syncthreads();
-    if (kb < qb) fetch(kb + 1);  // the next key block loads while this one computes
+    if (kb < kb_last) fetch(a.k, kb + 1);  // the next K block loads during the first half, V during the second
     const bf16_t* Ks = kv_tile(smem, kb & 1, 0);
     const bf16_t* Vs = kv_tile(smem, kb & 1, 1);
-    // S^T[16 t + 4 q4 + r][query] and dP^T likewise
-    f32x4 st[4], dp[4];
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) st[tt] = f32x4{0, 0, 0, 0}, dp[tt] = f32x4{0, 0, 0, 0};
+    for (int u = 0; u < 2; ++u) {
+      const int ku = k0 + 32 * u;
+      // A wave whose queries all precede the half has nothing to add.
+      if (ku <= q0 + wq + 16 * QT - 1) {
+        // S^T[16 t + 4 q4 + r][query] and dP^T likewise
+        f32x4 st[QT][2], dp[QT][2];
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4)
+        for (int c = 0; c < QT; ++c)
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
-        const bf16x8 ak = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const u32x4*>(Ks + (16 * tt + l16) * PR + 32 * s4 + 8 * q4));
-        const bf16x8 av = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const u32x4*>(Vs + (16 * tt + l16) * PR + 32 * s4 + 8 * q4));
-        st[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak, qf[s4], st[tt], 0, 0, 0);
-        dp[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, of[s4], dp[tt], 0, 0, 0);
-      }
-    // dS of this lane's query against 16 keys, in fragment order: chunk u, slot i is key
-    // 32 u + 4 q4 + i (i < 4) or 32 u + 16 + 4 q4 + i - 4. A key block before the query block
-    // is whole and entirely allowed: no mask there.
-    float dsv[2][8];
-    auto grad = [&](auto masked) {
+          for (int t = 0; t < 2; ++t) st[c][t] = f32x4{0, 0, 0, 0}, dp[c][t] = f32x4{0, 0, 0, 0};
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt)
+        for (int s4 = 0; s4 < 4; ++s4)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int kl = 16 * tt + 4 * q4 + r;
-          float p = __builtin_amdgcn_exp2f(st[tt][r] * sl - ls);
-          if constexpr (decltype(masked)::value) p = (k0 + kl <= q0 + qry && kl < nk) ? p : 0.0f;
-          dsv[tt >> 1][4 * (tt & 1) + r] = p * (dp[tt][r] - dd);
+          for (int t = 0; t < 2; ++t) {
+            const bf16x8 ak = __builtin_bit_cast(
+                bf16x8, *reinterpret_cast<const u32x4*>(Ks + (32 * u + 16 * t + l16) * PR + 32 * s4 + 8 * q4));
+            const bf16x8 av = __builtin_bit_cast(
+                bf16x8, *reinterpret_cast<const u32x4*>(Vs + (32 * u + 16 * t + l16) * PR + 32 * s4 + 8 * q4));
+#pragma unroll
+            for (int c = 0; c < QT; ++c) {
+              st[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak, qf[c][s4], st[c][t], 0, 0, 0);
+              dp[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, of[c][s4], dp[c][t], 0, 0, 0);
+            }
+          }
+        // dS of this lane's queries against 8 keys, in fragment order: slot i is key 32 u + 4 q4 + i
+        // (i < 4) or 32 u + 16 + 4 q4 + i - 4. A half that ends at or before the wave's first query is
+        // whole and entirely allowed: no mask there. (Keys past the episode come after every query.)
+        bf16x8 sh[QT], slo[QT];
+        auto grad = [&](auto masked) {
+#pragma unroll
+          for (int c = 0; c < QT; ++c) {
+            float dsv[8];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                float p = __builtin_amdgcn_exp2f(st[c][t][r] * sl - ls[c]);
+                if constexpr (decltype(masked)::value)
+                  p = (ku + 16 * t + 4 * q4 + r <= q0 + wq + 16 * c + l16) ? p : 0.0f;
+                dsv[4 * t + r] = p * (dp[c][t][r] - dd[c]);
+              }
+            split_frag(dsv, sh[c], slo[c]);
+          }
+        };
+        if (ku + 31 <= q0 + wq)
+          grad(std::false_type{});
+        else
+          grad(std::true_type{});
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const bf16x8 bk = trfrag(Ks, 16 * j, u, lane);
+#pragma unroll
+          for (int c = 0; c < QT; ++c) {
+            dq[c][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sh[c], bk, dq[c][j], 0, 0, 0);
+            dq[c][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(slo[c], bk, dq[c][j], 0, 0, 0);
+          }
         }
-    };
-    if (kb < qb)
-      grad(std::false_type{});
-    else
-      grad(std::true_type{});
-    bf16x8 sh[2], slo[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) split_frag(dsv[u], sh[u], slo[u]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const bf16x8 bk = trfrag(Ks, 16 * j, u, lane);
-        dq[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sh[u], bk, dq[j], 0, 0, 0);
-        dq[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(slo[u], bk, dq[j], 0, 0, 0);
       }
-    if (kb < qb) {
-      store_block(fk, kv_tile(smem, (kb + 1) & 1, 0), tid);
-      store_block(fv, kv_tile(smem, (kb + 1) & 1, 1), tid);
+      if (kb < kb_last) {
+        store_block(f, kv_tile(smem, (kb + 1) & 1, u), tid);
+        if (u == 0) fetch(a.v, kb + 1);
+      }
     }
   }
-  // D of dQ tile j: lane (l16, q4), register r -> query 16 w + 4 q4 + r, column 16 j + l16
+  // D of dQ tile j: lane (l16, q4), register r -> query 16 c + 4 q4 + r of the wave's, column 16 j + l16
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int qi = 16 * w + 4 * q4 + r;
-    if (qi >= nq) continue;
-    bf16_t* dqr = a.dq + ((int64_t)(E.row0 + q0 + qi) * a.heads + h) * DH;
+  for (int c = 0; c < QT; ++c)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) dqr[16 * j + l16] = f2bf(dq[j][r] * a.scale);
-  }
+    for (int r = 0; r < 4; ++r) {
+      const int qi = wq + 16 * c + 4 * q4 + r;
+      if (qi >= nq) continue;
+      bf16_t* dqr = a.dq + ((int64_t)(E.row0 + q0 + qi) * a.heads + h) * DH;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dqr[16 * j + l16] = f2bf(dq[c][j][r] * a.scale);
+    }
 }
 
 size_t attn_lds_bytes(int kernel) { return 2 * (size_t)(kernel == 1 ? kQoBuf : kKvBuf); }
 
-hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, int wgs, hipStream_t s) {
-  if (wgs <= 0) return hipSuccess;
-  static bool attr[3] = {false, false, false};
-  const void* fns[3] = {(const void*)attn_fwd_stats_kernel, (const void*)attn_dkdv_kernel, (const void*)attn_dq_kernel};
-  const size_t lds = attn_lds_bytes(kernel);
-  if (!attr[kernel]) {
-    hipError_t e = hipFuncSetAttribute(fns[kernel], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+template <class K>
+static hipError_t launch_blocks(K kernel, bool& attr, size_t lds, int rows, int per, const AttnArgs& a, AttnBatch b,
+                                int id, hipStream_t s) {
+  if (!attr) {
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    attr[kernel] = true;
+    attr = true;
   }
-  KernelTimer t(kernel == 0 ? K_ATTN_FWD : kernel == 1 ? K_ATTN_DKDV : K_ATTN_DQ, s);
-  if (kernel == 0) {
-    // the statistics kernel works on 128-query blocks: its own block counts and grid
-    AttnBatch b2 = b;
-    int n = 0;
-    for (int i = 0; i < b2.count; ++i) {
-      b2.e[i].blocks = (b2.e[i].L + SBLK - 1) / SBLK;
-      b2.e[i].wg_begin = n;
-      n += b2.e[i].blocks * a.heads;
-    }
-    if (n > 0) hipLaunchKernelGGL(attn_fwd_stats_kernel, dim3(n), dim3(256), lds, s, a, b2);
+  int n = 0;
+  for (int i = 0; i < b.count; ++i) {
+    b.e[i].blocks = (b.e[i].L + rows - 1) / rows;
+    b.e[i].wg_begin = n;
+    n += b.e[i].blocks * per;
   }
-  if (kernel == 1) hipLaunchKernelGGL(attn_dkdv_kernel, dim3(wgs), dim3(256), lds, s, a, b);
-  if (kernel == 2) hipLaunchKernelGGL(attn_dq_kernel, dim3(wgs), dim3(256), lds, s, a, b);
+  if (n <= 0) return hipSuccess;
+  KernelTimer t(id, s);
+  hipLaunchKernelGGL(kernel, dim3(n), dim3(256), lds, s, a, b);
   return hipGetLastError();
+}
+
+hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStream_t s) {
+  static bool attr[5] = {};
+  const size_t lds = attn_lds_bytes(kernel);
+  // Two query tiles per wave where their workgroups fill the chip's two per CU more than once; below that
+  // the longest chain of key blocks is the time, and a step of one tile is the shorter one. Statistics
+  // + dQ, one tile / two: 2048 rows x 16 heads (256 two-tile workgroups) 110 / 131 us, 4 episodes of 4096
+  // rows x 16 (512) 119 / 140, 4096 rows x 32 (1024) 514 / 413, 16 episodes of 1024 x 8 (1024) 239 / 225.
+  int n2 = 0;
+  for (int i = 0; i < b.count; ++i) n2 += (b.e[i].L + 127) / 128 * a.heads;
+  const bool wide = n2 > 512;
+  if (kernel == 0)
+    return wide ? launch_blocks(attn_fwd_stats_kernel<2>, attr[0], lds, 128, a.heads, a, b, K_ATTN_FWD, s)
+                : launch_blocks(attn_fwd_stats_kernel<1>, attr[1], lds, 64, a.heads, a, b, K_ATTN_FWD, s);
+  if (kernel == 1) return launch_blocks(attn_dkdv_kernel, attr[2], lds, 64, a.kv_heads, a, b, K_ATTN_DKDV, s);
+  return wide ? launch_blocks(attn_dq_kernel<2>, attr[3], lds, 128, a.heads, a, b, K_ATTN_DQ, s)
+              : launch_blocks(attn_dq_kernel<1>, attr[4], lds, 64, a.heads, a, b, K_ATTN_DQ, s);
 }
 
 }  // namespace attt

@@ -162,7 +162,7 @@ struct AttnArgs {
 struct AttnEp {
   int64_t row0;     // first row of the episode
   int32_t L;        // rows
-  int32_t blocks;   // 64-row blocks
+  int32_t blocks;   // blocks of the kernel's rows (set at launch, as is wg_begin)
   int32_t wg_begin; // first workgroup of the episode within the launch
   int32_t pad;
 };
@@ -172,7 +172,7 @@ struct AttnBatch {
   AttnEp e[kEpBatch];
 };
 // kernel 0: forward statistics, 1: dK and dV, 2: dQ
-hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, int wgs, hipStream_t s);
+hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStream_t s);
 
 // ---- persistent n-gram set ---------------------------------------------------------------
 struct NgramSetJob {

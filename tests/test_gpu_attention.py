@@ -105,6 +105,17 @@ def test_many_episodes_two_checked(attt):
         _cmp(f"dV ep{e}", dv[rs], r["dV"])
 
 
+@pytest.mark.parametrize("H,wide", [(16, False), (32, True)])
+def test_one_or_two_query_tiles_per_wave(attt, H, wide):
+    """Workgroups of 64 and of 128 queries (more than 512 of the latter): episodes that end inside the
+    first and the second half of a 128-query block, on its edges and on those of a wave's 32 queries."""
+    lens = [1, 31, 33, 63, 64, 65, 97, 127, 128, 129, 191, 192, 193, 200, 256, 257]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    assert (sum((n + 127) // 128 for n in lens) * H > 512) == wide
+    note(f"attention ragged: {H} heads, episodes {lens}")
+    _check_full(attt, int(off[-1]), H, 4, off, 71)
+
+
 def test_deterministic(attt):
     q, k, v, do = _inputs(1000, 8, 2, 61)
     off = np.array([0, 300, 1000], np.int64)
