@@ -139,6 +139,18 @@ attt_status attt_attention_bwd(const void* q, const void* k, const void* v, cons
                                int32_t heads, int32_t kv_heads, int32_t head_dim, float scale,
                                void* dq, void* dk, void* dv, float* lse, float* dsum, void* stream);
 
+/* attt_attention_bwd with a workspace for partial dK and dV: where one workgroup per key block would
+ * leave most of the chip idle (few rows or few key/value heads), several walk parts of its queries
+ * and their float32 sums are added in a fixed order. Size 0: the shape is not split, and the call is
+ * attt_attention_bwd. ATTT_ENOSPACE for a workspace that is too small; 256-byte aligned. */
+attt_status attt_attention_workspace_size(const int64_t* row_offsets, int32_t num_episodes, int64_t N,
+                                          int32_t heads, int32_t kv_heads, int32_t head_dim, size_t* bytes);
+attt_status attt_attention_bwd_split(const void* q, const void* k, const void* v, const void* dout,
+                                     const int64_t* row_offsets, int32_t num_episodes, int64_t N,
+                                     int32_t heads, int32_t kv_heads, int32_t head_dim, float scale,
+                                     void* dq, void* dk, void* dv, float* lse, float* dsum, void* workspace,
+                                     size_t workspace_bytes, void* stream);
+
 /* --------------------------------------------------------------------------------------
  * Update-text repetition and the sequence-level filter (Sec. 3.2, Eq. 6-7; tau of Appendix C):
  *     rho(x_k) = max over x' in H_k of J(W(x_k), W(x')),   J(A, B) = |A & B| / |A | B|,

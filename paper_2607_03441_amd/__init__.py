@@ -13,7 +13,7 @@ import os
 import numpy as np
 
 __all__ = ["load", "lib_path", "AtttError", "ngram_weights", "ngram_weights_noalloc", "ngram_workspace_size",
-           "update_repetition", "repetition_workspace_size", "attention_bwd",
+           "update_repetition", "repetition_workspace_size", "attention_bwd", "attention_workspace_size",
            "ngram_set_size", "ngram_set_init", "ngram_set_append", "ngram_set_weights",
            "weighted_ce_fwd_bwd", "ce_workspace_size", "ce_head_t_size", "ce_head_transpose", "lora_grad", "lora_workspace_size", "lora_sgd_step",
            "lora_forward", "lora_hot_swap",
@@ -86,6 +86,11 @@ def load():
     L.attt_ngram_weights.argtypes = [vp, p64, vp, p64, i32, i32, f32, vp, vp, vp, sz, vp]
     L.attt_attention_bwd.restype = i32
     L.attt_attention_bwd.argtypes = [vp, vp, vp, vp, p64, i32, i64, i32, i32, i32, f32, vp, vp, vp, vp, vp, vp]
+    L.attt_attention_workspace_size.restype = i32
+    L.attt_attention_workspace_size.argtypes = [p64, i32, i64, i32, i32, i32, psz]
+    L.attt_attention_bwd_split.restype = i32
+    L.attt_attention_bwd_split.argtypes = [vp, vp, vp, vp, p64, i32, i64, i32, i32, i32, f32, vp, vp, vp, vp, vp, vp,
+                                           sz, vp]
     L.attt_repetition_workspace_size.restype = i32
     L.attt_repetition_workspace_size.argtypes = [p64, p64, i32, psz]
     L.attt_update_repetition.restype = i32
@@ -239,11 +244,24 @@ def ngram_weights(history, history_offsets, tokens, token_offsets, n=3, w_min=0.
     return f, w
 
 
-def attention_bwd(q, k, v, dout, row_offsets=None, scale=None, out=None):
+def attention_workspace_size(N, heads, kv_heads, row_offsets=None, head_dim=128):
+    """Bytes of the workspace attention_bwd uses for a shape (0 where it needs none)."""
+    L = load()
+    E, op = 1, None
+    if row_offsets is not None:
+        oo, op = _offsets(row_offsets)
+        E = len(oo) - 1
+    need = ctypes.c_size_t()
+    _check(L.attt_attention_workspace_size(op, E, N, heads, kv_heads, head_dim, ctypes.byref(need)))
+    return need.value
+
+
+def attention_bwd(q, k, v, dout, row_offsets=None, scale=None, out=None, workspace=None):
     """Backward of one causal grouped-head attention block: (dq, dk, dv, lse, dsum).
 
     q, dout: device bf16 [N, heads, 128]; k, v: [N, kv_heads, 128]; row_offsets: host int64
-    episode offsets or None; scale defaults to 1/sqrt(128). lse, dsum: float32 [heads, N]."""
+    episode offsets or None; scale defaults to 1/sqrt(128). lse, dsum: float32 [heads, N].
+    workspace: uint8 tensor of attention_workspace_size bytes (allocated here when not given)."""
     torch = _torch()
     L = load()
     for t, name in ((q, "q"), (k, "k"), (v, "v"), (dout, "dout")):
@@ -263,8 +281,12 @@ def attention_bwd(q, k, v, dout, row_offsets=None, scale=None, out=None):
     else:
         oo, op = _offsets(row_offsets)
         E = len(oo) - 1
-    _check(L.attt_attention_bwd(_dptr(q), _dptr(k), _dptr(v), _dptr(dout), op, E, N, H, Hkv, dh, scale,
-                                _dptr(dq), _dptr(dk), _dptr(dv), _dptr(lse), _dptr(dsum), _stream_ptr()))
+    need = ctypes.c_size_t()
+    _check(L.attt_attention_workspace_size(op, E, N, H, Hkv, dh, ctypes.byref(need)))
+    ws = _workspace(need.value, q.device, workspace) if need.value else None
+    _check(L.attt_attention_bwd_split(_dptr(q), _dptr(k), _dptr(v), _dptr(dout), op, E, N, H, Hkv, dh, scale,
+                                      _dptr(dq), _dptr(dk), _dptr(dv), _dptr(lse), _dptr(dsum), _dptr(ws),
+                                      ws.numel() if ws is not None else 0, _stream_ptr()))
     return dq, dk, dv, lse, dsum
 
 

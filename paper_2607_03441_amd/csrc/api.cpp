@@ -400,33 +400,124 @@ attt_status ngram_run(const NgramPlan& P, const int32_t* history, const int32_t*
 // ------------------------------------------------------------------------------------------
 // Attention-block backward
 // ------------------------------------------------------------------------------------------
-extern "C" attt_status attt_attention_bwd(const void* q, const void* k, const void* v, const void* dout,
-                                          const int64_t* row_offsets, int32_t num_episodes, int64_t N,
-                                          int32_t heads, int32_t kv_heads, int32_t head_dim, float scale,
-                                          void* dq, void* dk, void* dv, float* lse, float* dsum, void* stream) {
+namespace {
+// How the dK / dV kernel's workgroups of one launch batch take its key blocks.
+struct AttnSplit {
+  int32_t tiles = 2, splits = 1, chunk = INT32_MAX;
+  size_t bytes = 0;
+};
+
+// A key block's workgroup walks heads / kv_heads steps for each 64-query block at or after it. One
+// workgroup per block leaves the chip idle where there are few of them or where the first block's walk
+// is much longer than the average; blocks of 64 keys make twice the workgroups and shorter steps, and
+// (`may_split`) cutting every walk of 128 keys into pieces of `chunk` steps bounds the longest at the
+// price of a float32 partial per piece. The choice is the shortest by this estimate in microseconds: a
+// step takes 1.86 (64 keys) or 2.63 (128) alone on its CU and 2.3 or 3.0 where a CU has more than one
+// workgroup to do; whole pieces run in rounds of 256, and the rests of the walks fill the last (a
+// quarter of a piece short of even); partials take 15 and 0.05 a workgroup. Measured, one walk of 64 /
+// of 128 keys / the best split / the choice: 2048 rows, 16 heads over 4: 249 / 340 / 76 / 76 us;
+// 4096, 8 over 2: 464 / 666 / 125 / 125; 4096, 32 over 8: 552 / 667 / 420 / 466; 8 episodes of 2000
+// rows in all, 8 over 8: 21 / 28 / 30 / 22; 8192, 32 over 8: 2066 / 1509 / 1509 / 1509.
+AttnSplit attn_split(const int64_t* off, int32_t E, int32_t heads, int32_t kv_heads, bool may_split) {
+  const int64_t g = heads / kv_heads;
+  int64_t longest = 0, blocks = 0;
+  for (int32_t e = 0; e < E; ++e) {
+    const int64_t L = off[e + 1] - off[e];
+    longest = std::max(longest, g * ceil_div(L, 64));
+    blocks += ceil_div(L, kAttnKeyBlock);
+  }
+  AttnSplit best;
+  if (blocks * kv_heads >= 2048 || blocks == 0) return best;  // eight rounds of the chip: even as they are
+  double best_us = 0.0;
+  auto consider = [&](int32_t tiles, int64_t chunk) {
+    int64_t wgs = 0, whole = 0, total = 0;
+    for (int32_t e = 0; e < E; ++e) {
+      const int64_t nqb = ceil_div(off[e + 1] - off[e], 64);
+      for (int64_t q = 0; q < nqb; q += tiles) {
+        const int64_t steps = g * (nqb - q);
+        wgs += ceil_div(steps, chunk);
+        whole += steps / chunk;
+        total += steps;
+      }
+    }
+    wgs *= kv_heads;
+    whole *= kv_heads;
+    total *= kv_heads;
+    const int32_t splits = (int32_t)ceil_div(longest, chunk);
+    if (splits > 1 && chunk % (2 * g) != 0 && wgs > 256) return;
+    const int64_t rounds = splits > 1 ? whole / 256 : 0;
+    const double tail = std::max((double)(whole > rounds * 256 ? chunk : 0),
+                                 (double)(total - rounds * 256 * chunk) / 256);
+    double us = (double)(rounds * chunk) + tail;
+    if (splits == 1) us = std::max((double)longest, (double)total / 256 + (double)longest / 16);
+    else if (wgs > 256) us += (double)chunk / 4;
+    us *= wgs <= 256 ? (tiles == 1 ? 1.86 : 2.63) : (tiles == 1 ? 2.3 : 3.0);
+    if (splits > 1) us += 15 + 0.05 * (double)wgs;
+    if (best_us == 0.0 || us < best_us) {
+      best_us = us;
+      best.tiles = tiles;
+      best.splits = splits;
+      best.chunk = splits == 1 ? INT32_MAX : (int32_t)chunk;
+    }
+  };
+  consider(2, longest);
+  consider(1, longest);
+  if (may_split)
+    for (int32_t k : {2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24}) {
+      const int64_t chunk = ceil_div(longest, k), even = ceil_div(chunk, 2 * g) * 2 * g;
+      if (chunk < 3) break;
+      if (even < longest) consider(2, even);
+      if (even != chunk) consider(2, chunk);  // in one round only
+    }
+  if (best.splits > 1) best.bytes = (size_t)blocks * kv_heads * best.splits * kAttnPartBytes;
+  return best;
+}
+
+attt_status attn_check(const int64_t*& off, int64_t (&single)[2], int32_t num_episodes, int64_t N, int32_t heads,
+                       int32_t kv_heads, int32_t head_dim) {
   if (head_dim != 128) return fail(ATTT_EUNSUPPORTED, "attention: head_dim must be 128 (got %d)", head_dim);
   if (heads < 1 || kv_heads < 1 || heads % kv_heads != 0)
     return fail(ATTT_EINVAL, "attention: heads (%d) must be a positive multiple of kv_heads (%d)", heads, kv_heads);
-  if (!(scale > 0.0f) || !std::isfinite(scale)) return fail(ATTT_EINVAL, "attention: scale must be finite and > 0");
   if (N < 0) return fail(ATTT_EINVAL, "attention: N must be >= 0");
   if (N * heads >= INT32_MAX) return fail(ATTT_EUNSUPPORTED, "attention: N x heads must be < 2^31");
   if (heads >= (1 << 16)) return fail(ATTT_EUNSUPPORTED, "attention: heads must be < 2^16 (got %d)", heads);
   if (num_episodes < 1) return fail(ATTT_EINVAL, "attention: num_episodes must be >= 1 (got %d)", num_episodes);
-  int64_t single[2] = {0, N};
-  const int64_t* off = row_offsets;
   if (!off) {
     if (num_episodes != 1) return fail(ATTT_EINVAL, "attention: row_offsets may be NULL only for one episode");
+    single[0] = 0;
+    single[1] = N;
     off = single;
   }
   attt_status st = check_offsets("attention rows", off, num_episodes, INT32_MAX);
   if (st) return st;
   if (off[num_episodes] != N)
     return fail(ATTT_EINVAL, "attention: row_offsets[E] (%lld) != N (%lld)", (long long)off[num_episodes], (long long)N);
+  return ATTT_OK;
+}
+
+attt_status attn_run(const void* q, const void* k, const void* v, const void* dout, const int64_t* row_offsets,
+                     int32_t num_episodes, int64_t N, int32_t heads, int32_t kv_heads, int32_t head_dim, float scale,
+                     void* dq, void* dk, void* dv, float* lse, float* dsum, bool split, void* workspace,
+                     size_t workspace_bytes, void* stream) {
+  int64_t single[2];
+  const int64_t* off = row_offsets;
+  attt_status st = attn_check(off, single, num_episodes, N, heads, kv_heads, head_dim);
+  if (st) return st;
+  if (!(scale > 0.0f) || !std::isfinite(scale)) return fail(ATTT_EINVAL, "attention: scale must be finite and > 0");
   if (N == 0) return ATTT_OK;
   const void* ptrs[] = {q, k, v, dout, dq, dk, dv, lse, dsum};
   for (const void* ptr : ptrs) {
     if (!ptr) return fail(ATTT_EINVAL, "attention: null pointer");
     if (!aligned16(ptr)) return fail(ATTT_EINVAL, "attention: device pointers must be 16-byte aligned");
+  }
+  std::vector<AttnSplit> splits;
+  for (int32_t e0 = 0; e0 < num_episodes; e0 += kEpBatch) {
+    const AttnSplit sp = attn_split(off + e0, std::min<int32_t>(kEpBatch, num_episodes - e0), heads, kv_heads, split);
+    if (workspace_bytes < sp.bytes)
+      return fail(ATTT_ENOSPACE, "attention: workspace %zu bytes, need %zu", workspace_bytes, sp.bytes);
+    if (sp.bytes && !workspace) return fail(ATTT_EINVAL, "attention: workspace is null");
+    if (sp.bytes && !aligned256(workspace)) return fail(ATTT_EINVAL, "attention: workspace must be 256-byte aligned");
+    splits.push_back(sp);
   }
   AttnArgs a{};
   a.q = static_cast<const bf16_t*>(q);
@@ -450,10 +541,46 @@ extern "C" attt_status attt_attention_bwd(const void* q, const void* k, const vo
       b.e[i].row0 = off[e0 + i];
       b.e[i].L = (int32_t)(off[e0 + i + 1] - off[e0 + i]);
     }
+    b.tiles = splits[e0 / kEpBatch].tiles;
+    b.splits = splits[e0 / kEpBatch].splits;
+    b.chunk = splits[e0 / kEpBatch].chunk;
+    b.part = static_cast<float*>(workspace);
     for (int kernel = 0; kernel < 3; ++kernel)
       HIP_TRY(launch_attn(kernel, a, b, s), kernel == 0 ? "attn_fwd_stats" : kernel == 1 ? "attn_dkdv" : "attn_dq");
   }
   return ATTT_OK;
+}
+
+}  // namespace
+
+extern "C" attt_status attt_attention_workspace_size(const int64_t* row_offsets, int32_t num_episodes, int64_t N,
+                                                     int32_t heads, int32_t kv_heads, int32_t head_dim, size_t* bytes) {
+  if (!bytes) return fail(ATTT_EINVAL, "attention: bytes is null");
+  int64_t single[2];
+  const int64_t* off = row_offsets;
+  attt_status st = attn_check(off, single, num_episodes, N, heads, kv_heads, head_dim);
+  if (st) return st;
+  *bytes = 0;
+  for (int32_t e0 = 0; e0 < num_episodes; e0 += kEpBatch)
+    *bytes = std::max(*bytes, attn_split(off + e0, std::min<int32_t>(kEpBatch, num_episodes - e0), heads, kv_heads, true).bytes);
+  return ATTT_OK;
+}
+
+extern "C" attt_status attt_attention_bwd(const void* q, const void* k, const void* v, const void* dout,
+                                          const int64_t* row_offsets, int32_t num_episodes, int64_t N,
+                                          int32_t heads, int32_t kv_heads, int32_t head_dim, float scale,
+                                          void* dq, void* dk, void* dv, float* lse, float* dsum, void* stream) {
+  return attn_run(q, k, v, dout, row_offsets, num_episodes, N, heads, kv_heads, head_dim, scale, dq, dk, dv, lse, dsum,
+                  false, nullptr, 0, stream);
+}
+
+extern "C" attt_status attt_attention_bwd_split(const void* q, const void* k, const void* v, const void* dout,
+                                                const int64_t* row_offsets, int32_t num_episodes, int64_t N,
+                                                int32_t heads, int32_t kv_heads, int32_t head_dim, float scale,
+                                                void* dq, void* dk, void* dv, float* lse, float* dsum, void* workspace,
+                                                size_t workspace_bytes, void* stream) {
+  return attn_run(q, k, v, dout, row_offsets, num_episodes, N, heads, kv_heads, head_dim, scale, dq, dk, dv, lse, dsum,
+                  true, workspace, workspace_bytes, stream);
 }
 
 // ------------------------------------------------------------------------------------------

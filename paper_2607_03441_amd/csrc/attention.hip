@@ -9,9 +9,9 @@
 // the longest rows first, the next block's global loads in flight while the current one computes:
 //   attn_fwd_stats_kernel  per (query head, 64- or 128-query block): lse and D (online softmax; D as
 //                          the softmax-weighted sum of dP = dO V^T, so O is never formed)
-//   attn_dkdv_kernel       per (key/value head, 64-key block): dK and dV accumulated in
-//                          registers over every query head of the group and every later query
-//                          block, in a fixed order (no atomics)
+//   attn_dkdv_kernel       per (key/value head, 64- or 128-key block, part of its queries): dK and dV
+//                          accumulated in registers over every query head of the group and every
+//                          later query block, in a fixed order (no atomics), 512 threads
 //   attn_dq_kernel         per (query head, 64- or 128-query block): dQ over the allowed key blocks
 // The operand that stays in a wave (its 16 queries, or its 16 keys) is held in registers as
 // the B operand of the score products, so each lane ends up with 16 scores of its own row. The
@@ -35,6 +35,7 @@ namespace attt {
 namespace {
 constexpr int DH = 128;     // head dimension
 constexpr int BLK = 64;     // query / key rows per block
+constexpr int KBLK = kAttnKeyBlock;  // keys per block of a split dK / dV walk
 constexpr int PR = DH + 8;  // LDS pitch of a [64][128] tile (bf16): 272 B, conflict-free b128 reads
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -278,137 +279,276 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, Attn
   }
 }
 
-// dK, dV of one (key/value head, 64-key block). Wave w owns keys 16 w .. 16 w + 15; their K and
-// V fragments stay in registers. Per query block: S = Q K^T and dP = dO V^T with the queries on
-// the MFMA rows (four tiles of 16) and this wave's keys on the columns, so each lane holds 16
-// (query, key) values of its own key. P and dS = P (dP - D) then feed dV += P^T dO and
-// dK += dS^T Q straight from those registers as the A operand: the contraction runs over the
-// queries, and the 8 values a lane holds per 32-query chunk (tile rows 4 q4 .. +3 of two tiles)
-// are its k slots; the B operand reads the transposed dO and Q tiles in the same query order.
-__global__ __launch_bounds__(256, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch b) {
-  int ei, kh, kb;
-  attn_locate(b, a.kv_heads, false, ei, kh, kb);
+// Key blocks of an episode (64 KT keys each) whose walk of g steps per query block has a whole piece
+// number `split`: the first ones, since a block's walk is KT g steps shorter than that of the one before.
+template <int KT>
+__host__ __device__ __forceinline__ int whole_pieces(int L, int g, int split, int chunk) {
+  const int64_t left = (int64_t)g * ((L + BLK - 1) / BLK) - (int64_t)(split + 1) * chunk;
+  return left >= 0 ? (int)(left / (KT * g)) + 1 : 0;
+}
+
+// dK, dV of one (key/value head, 64 KT-key block) over a range of its (query block, query head) steps.
+// Eight waves: wave (kw, qw) owns keys 16 KT kw .. + 16 KT - 1, as KT tiles of 16, and half qw (32
+// queries) of every 64-query step. S = Q K^T and dP = dO V^T with the queries on the MFMA rows (two tiles
+// of 16) and the wave's keys on the columns; K and V come from LDS tiles kept for the whole walk. Each
+// lane holds 8 (query, key) values of its own key of a tile. P and dS = P (dP - D) then feed dV += P^T dO
+// and dK += dS^T Q straight from those registers as the A operand: the contraction runs over the 32
+// queries, whose 8 values a lane holds (tile rows 4 q4 .. +3 of two tiles) are its k slots; the B operand
+// reads the dO and Q tiles through transposing reads in the same query order. At the end the two halves
+// of the queries are added through LDS (one order, no atomics).
+// LDS reads bound the layout of 16 keys and 64 queries per wave (2304 of 3312 cycles a 64-key step against
+// 1536 of MFMA): here a wave's 96 products read 48 KiB instead of 64 per 32. K in registers spilled 34
+// of them (1935 us); the matrix phases at raised wave priority, so that one wave's products run under the
+// other's softmax, took 1594 -> 1558 us. 8192 rows, 32 heads over 8: 1726 -> 1558 us.
+template <int KT>
+__global__ __launch_bounds__(512, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch b) {
+  constexpr int KBLK = 64 * KT;
+  int ei = 0;
+  while (ei + 1 < b.count && b.e[ei + 1].wg_begin <= (int)blockIdx.x) ++ei;
   const AttnEp E = b.e[ei];
   const int g = a.heads / a.kv_heads;
-  const int k0 = kb * BLK, nk = min(BLK, E.L - k0);
-  extern __shared__ __align__(16) uint8_t smem[];  // two buffers of [Q tile][dO tile][lse][D]
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int l16 = lane & 15, q4 = lane >> 4;
-  const int key = 16 * w + l16;  // this lane's key in the block
-  const int64_t qs = (int64_t)a.heads * DH, ks = (int64_t)a.kv_heads * DH;
-  bf16x8 kf[4], vf[4];
-  load_key_frags(kf, a.k + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
-  load_key_frags(vf, a.v + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
-  f32x4 dk[8], dv[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) dk[j] = f32x4{0, 0, 0, 0}, dv[j] = f32x4{0, 0, 0, 0};
-  const float sl = a.scale * kLog2e;
+  // The pieces of `chunk` steps first, then the rests of the walks, the longest first, so that the last
+  // round is filled by short ones. Where `chunk` is m times the KT g steps by which the walks of
+  // neighbouring blocks differ, blocks c, c + m, ... leave the same rest; otherwise the launch is one round
+  // and the order does not matter. (By block, with
+  // workgroups past a walk's end that left at once, and rests in the blocks' order: 2048 rows, 16 heads over
+  // 4, 6 pieces 120 us, here 81; 8192 rows, 8 over 2, 4 pieces 686 us, here 455.)
+  int local = (int)blockIdx.x - E.wg_begin, split = 0;
+  for (int n; split < b.splits && local >= (n = whole_pieces<KT>(E.L, g, split, b.chunk) * a.kv_heads); ++split)
+    local -= n;
+  const int kh = local % a.kv_heads;
+  int kb = local / a.kv_heads;
+  if (split == b.splits && b.splits > 1 && b.chunk % (KT * g) == 0) {
+    const int m = b.chunk / (KT * g), q = E.blocks / m, r = E.blocks % m;
+    int c = g * ((E.L + BLK - 1) / BLK) % b.chunk / (KT * g) + 1;  // the longest rests
+    for (int n;; ++c) {
+      if (c == m) c = 0;
+      n = q + (c < r);
+      if (kb < n) break;  // the classes hold all E.blocks blocks
+      kb -= n;
+    }
+    kb = c + m * kb;
+  }
+  const int k0 = kb * KBLK, nk = min(KBLK, E.L - k0);
   const int nqb = (E.L + BLK - 1) / BLK;
-  // (query block, query head) steps: query blocks from the last down to kb, the group's query
-  // heads inside. Every workgroup of a key/value head walks the same blocks in the same order
-  // (starting at the last, stopping at its own key block), so those running together on an XCD
-  // read each Q and dO block from its L2.
-  const int steps = g * (nqb - kb);
-  u32x4 fq[4], fo[4];
-  float fl = INFINITY, fd = 0.0f;
+  // (query block, query head) steps: query blocks from the last down to the key block's first, the
+  // group's query heads inside. Every workgroup of a key/value head walks the same blocks in the same
+  // order, so those running together on an XCD read each Q and dO block from its L2.
+  const int steps = g * (nqb - kb * KT);
+  if (split == b.splits) split = steps / b.chunk;
+  const int i0 = split * b.chunk, i1 = min(steps, i0 + b.chunk);
+  if (i0 >= i1) return;  // a walk of whole pieces has no rest
+  extern __shared__ __align__(16) uint8_t smem[];  // two buffers of [Q tile][dO tile][lse][D], the V tile
+  bf16_t* Vs = reinterpret_cast<bf16_t*>(smem + 2 * kQoBuf);
+  bf16_t* Ks = Vs + KBLK * PR;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kw = w & 3, qw = w >> 2;
+  const int l16 = lane & 15, q4 = lane >> 4;
+  const int64_t qs = (int64_t)a.heads * DH, ks = (int64_t)a.kv_heads * DH;
+  const int64_t krow = ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH;
+  const int r0 = (tid >> 4) * 2, c0 = (tid & 15) * 8;  // a thread's two rows of a 64-row block, and columns
+  {
+    const int bytes = (int)(((int64_t)(nk - 1) * ks + DH) * 2);
+    const __amdgpu_buffer_rsrc_t rk = buffer_rsrc(a.k + krow, bytes), rv = buffer_rsrc(a.v + krow, bytes);
+#pragma unroll
+    for (int i = 0; i < 2 * KT; ++i) {
+      const int r = (i >> 1) * BLK + r0 + (i & 1);
+      const uint32_t off = (uint32_t)(((int64_t)r * ks + c0) * 2);
+      *reinterpret_cast<u32x4*>(Ks + r * PR + c0) =
+          __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, off, 0, 0));
+      *reinterpret_cast<u32x4*>(Vs + r * PR + c0) =
+          __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0));
+    }
+  }
+  f32x4 dk[KT][8], dv[KT][8];
+#pragma unroll
+  for (int c = 0; c < KT; ++c)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) dk[c][j] = f32x4{0, 0, 0, 0}, dv[c][j] = f32x4{0, 0, 0, 0};
+  const float sl = a.scale * kLog2e;
+  u32x4 fq[2], fo[2];
+  float fs = 0.0f;
   auto fetch = [&](int i) {
     const int h = kh * g + i % g, q0 = (nqb - 1 - i / g) * BLK, nq = min(BLK, E.L - q0);
-    fetch_block(fq, a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, nq, tid);
-    fetch_block(fo, a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, nq, tid);
-    if (tid < BLK) {
-      const int64_t t = (int64_t)h * a.N + E.row0 + q0 + tid;
-      fl = tid < nq ? a.lse[t] * kLog2e : INFINITY;  // absent rows: P = 0
-      fd = tid < nq ? a.dsum[t] : 0.0f;
+    const int64_t row = ((int64_t)(E.row0 + q0) * a.heads + h) * DH;
+    const int bytes = (int)(((int64_t)(nq - 1) * qs + DH) * 2);
+    const __amdgpu_buffer_rsrc_t rq = buffer_rsrc(a.q + row, bytes), ro = buffer_rsrc(a.dout + row, bytes);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const uint32_t off = (uint32_t)(((int64_t)(r0 + r) * qs + c0) * 2);
+      fq[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rq, off, 0, 0));
+      fo[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ro, off, 0, 0));
+    }
+    if (tid < 2 * BLK) {
+      const int ql = tid & (BLK - 1);
+      const int64_t t = (int64_t)h * a.N + E.row0 + q0 + ql;
+      if (tid < BLK)
+        fs = ql < nq ? a.lse[t] * kLog2e : INFINITY;  // absent rows: P = 0
+      else
+        fs = ql < nq ? a.dsum[t] : 0.0f;
     }
   };
   auto stage = [&](int buf) {
-    store_block(fq, qo_tile(smem, buf, 0), tid);
-    store_block(fo, qo_tile(smem, buf, 1), tid);
-    if (tid < BLK) qo_stats(smem, buf)[tid] = fl, qo_stats(smem, buf)[BLK + tid] = fd;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      *reinterpret_cast<u32x4*>(qo_tile(smem, buf, 0) + (r0 + r) * PR + c0) = fq[r];
+      *reinterpret_cast<u32x4*>(qo_tile(smem, buf, 1) + (r0 + r) * PR + c0) = fo[r];
+    }
+    if (tid < 2 * BLK) qo_stats(smem, buf)[tid] = fs;
   };
-  fetch(0);
+  fetch(i0);
   stage(0);
-  for (int i = 0; i < steps; ++i) {
-    const int q0 = (nqb - 1 - i / g) * BLK;
+  for (int i = i0; i < i1; ++i) {
+    const int buf = (i - i0) & 1;
+    const int qw0 = (nqb - 1 - i / g) * BLK + 32 * qw;  // this wave's first query
     // This step's tiles are stored, and every wave is done with the other buffer.
     __syncthreads();
-    if (i + 1 < steps) fetch(i + 1);  // the next step's blocks load while this one computes
-    const bf16_t* Qs = qo_tile(smem, i & 1, 0);
-    const bf16_t* dOs = qo_tile(smem, i & 1, 1);
-    const float* lse_s = qo_stats(smem, i & 1);
-    const float* d_s = lse_s + BLK;
-    {
-      // S[16 t + 4 q4 + r][key] and dP likewise
-      f32x4 st[4], dp[4];
+    if (i + 1 < i1) fetch(i + 1);  // the next step's blocks load while this one computes
+    // A wave whose queries all precede its keys has nothing to add.
+    if (qw0 + 31 >= k0 + 16 * KT * kw) {
+      const bf16_t* Qs = qo_tile(smem, buf, 0);
+      const bf16_t* dOs = qo_tile(smem, buf, 1);
+      const float* lse_s = qo_stats(smem, buf) + 32 * qw;
+      const float* d_s = lse_s + BLK;
+      __builtin_amdgcn_s_setprio(1);
+      // S[16 t + 4 q4 + r][key] and dP likewise, for both key tiles
+      f32x4 st[KT][2], dp[KT][2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) st[t] = f32x4{0, 0, 0, 0}, dp[t] = f32x4{0, 0, 0, 0};
+      for (int c = 0; c < KT; ++c)
 #pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4)
+        for (int t = 0; t < 2; ++t) st[c][t] = f32x4{0, 0, 0, 0}, dp[c][t] = f32x4{0, 0, 0, 0};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const bf16x8 aq = __builtin_bit_cast(
-              bf16x8, *reinterpret_cast<const u32x4*>(Qs + (16 * t + l16) * PR + 32 * s4 + 8 * q4));
-          const bf16x8 ao = __builtin_bit_cast(
-              bf16x8, *reinterpret_cast<const u32x4*>(dOs + (16 * t + l16) * PR + 32 * s4 + 8 * q4));
-          st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, kf[s4], st[t], 0, 0, 0);
-          dp[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao, vf[s4], dp[t], 0, 0, 0);
+      for (int s4 = 0; s4 < 4; ++s4) {
+        bf16x8 bk[KT], bv[KT];
+#pragma unroll
+        for (int c = 0; c < KT; ++c) {
+          bk[c] = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const u32x4*>(Ks + (16 * KT * kw + 16 * c + l16) * PR + 32 * s4 + 8 * q4));
+          bv[c] = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const u32x4*>(Vs + (16 * KT * kw + 16 * c + l16) * PR + 32 * s4 + 8 * q4));
         }
-      // P and dS of this lane's 16 (query, key) pairs, in fragment order: chunk u, slot i is
-      // query 32 u + 4 q4 + i (i < 4) or 32 u + 16 + 4 q4 + i - 4. A query block after the key
-      // block sees every key, and the key block is then not the last, so it is whole: no mask.
-      float pv[2][8], dsv[2][8];
-      auto probs = [&](auto masked) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const f32x4 ls = *reinterpret_cast<const f32x4*>(lse_s + 16 * t + 4 * q4);
-          const f32x4 dd = *reinterpret_cast<const f32x4*>(d_s + 16 * t + 4 * q4);
+        for (int t = 0; t < 2; ++t) {
+          const bf16x8 aq = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const u32x4*>(Qs + (32 * qw + 16 * t + l16) * PR + 32 * s4 + 8 * q4));
+          const bf16x8 ao = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const u32x4*>(dOs + (32 * qw + 16 * t + l16) * PR + 32 * s4 + 8 * q4));
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int ql = 16 * t + 4 * q4 + r;
-            float p = __builtin_amdgcn_exp2f(st[t][r] * sl - ls[r]);
-            if constexpr (decltype(masked)::value) p = (k0 + key <= q0 + ql && key < nk) ? p : 0.0f;
-            pv[t >> 1][4 * (t & 1) + r] = p;
-            dsv[t >> 1][4 * (t & 1) + r] = p * (dp[t][r] - dd[r]);
+          for (int c = 0; c < KT; ++c) {
+            st[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, bk[c], st[c][t], 0, 0, 0);
+            dp[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao, bv[c], dp[c][t], 0, 0, 0);
           }
         }
+      }
+      // P and dS of this lane's 8 (query, key) pairs of each key tile, in fragment order: slot i is
+      // query 4 q4 + i (i < 4) or 16 + 4 q4 + i - 4. Queries at or after the wave's last key see all of
+      // its keys: no mask there. (Keys past the episode only reach rows that are not written.)
+      bf16x8 ph[KT], pl[KT], sh[KT], slo[KT];
+      auto probs = [&](auto masked) {
+#pragma unroll
+        for (int c = 0; c < KT; ++c) {
+          float pv[8], dsv[8];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const f32x4 ls = *reinterpret_cast<const f32x4*>(lse_s + 16 * t + 4 * q4);
+            const f32x4 dd = *reinterpret_cast<const f32x4*>(d_s + 16 * t + 4 * q4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              float p = __builtin_amdgcn_exp2f(st[c][t][r] * sl - ls[r]);
+              if constexpr (decltype(masked)::value)
+                p = (k0 + 16 * KT * kw + 16 * c + l16 <= qw0 + 16 * t + 4 * q4 + r) ? p : 0.0f;
+              pv[4 * t + r] = p;
+              dsv[4 * t + r] = p * (dp[c][t][r] - dd[r]);
+            }
+          }
+          split_frag(pv, ph[c], pl[c]);
+          split_frag(dsv, sh[c], slo[c]);
+        }
       };
-      if (q0 > k0)
+      __builtin_amdgcn_s_setprio(0);
+      if (qw0 >= k0 + 16 * KT * kw + 16 * KT - 1)
         probs(std::false_type{});
       else
         probs(std::true_type{});
-      bf16x8 ph[2], pl[2], sh[2], slo[2];
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        split_frag(pv[u], ph[u], pl[u]);
-        split_frag(dsv[u], sh[u], slo[u]);
-      }
+      for (int j = 0; j < 8; ++j) {
+        const bf16x8 bo = trfrag(dOs, 16 * j, qw, lane), bq = trfrag(Qs, 16 * j, qw, lane);
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const bf16x8 bo = trfrag(dOs, 16 * j, u, lane);
-          dv[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph[u], bo, dv[j], 0, 0, 0);
-          dv[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[u], bo, dv[j], 0, 0, 0);
-          const bf16x8 bq = trfrag(Qs, 16 * j, u, lane);
-          dk[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sh[u], bq, dk[j], 0, 0, 0);
-          dk[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(slo[u], bq, dk[j], 0, 0, 0);
+        for (int c = 0; c < KT; ++c) {
+          dv[c][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph[c], bo, dv[c][j], 0, 0, 0);
+          dv[c][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[c], bo, dv[c][j], 0, 0, 0);
+          dk[c][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sh[c], bq, dk[c][j], 0, 0, 0);
+          dk[c][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(slo[c], bq, dk[c][j], 0, 0, 0);
         }
+      }
     }
-    if (i + 1 < steps) stage((i + 1) & 1);
+    __builtin_amdgcn_s_setprio(0);
+    if (i + 1 < i1) stage(buf ^ 1);
   }
-  // D of dV / dK tile j: lane (l16, q4), register r -> key 16 w + 4 q4 + r, column 16 j + l16
+  // Both query halves: per key tile the waves of the second half hand over dK, those of the first dV,
+  // and each adds the other's to its own. 64 KiB of the tiles' LDS.
+  f32x4* ex = reinterpret_cast<f32x4*>(smem);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int kr = 16 * w + 4 * q4 + r;
-    if (kr >= nk) continue;
-    bf16_t* dkr = a.dk + ((int64_t)(E.row0 + k0 + kr) * a.kv_heads + kh) * DH;
-    bf16_t* dvr = a.dv + ((int64_t)(E.row0 + k0 + kr) * a.kv_heads + kh) * DH;
+  for (int c = 0; c < KT; ++c) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ex[(w * 8 + j) * 64 + lane] = qw ? dk[c][j] : dv[c][j];
+    __syncthreads();
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      dkr[16 * j + l16] = f2bf(dk[j][r] * a.scale);
-      dvr[16 * j + l16] = f2bf(dv[j][r]);
+      const f32x4 o = ex[((w ^ 4) * 8 + j) * 64 + lane];
+      if (qw)
+        dv[c][j] += o;
+      else
+        dk[c][j] += o;
     }
   }
+  // D of tile (c, j): lane (l16, q4), register r -> key 32 kw + 16 c + 4 q4 + r, column 16 j + l16
+  const float os = qw ? 1.0f : a.scale;
+  float* part = b.part + (((int64_t)(E.blocks0 + kb) * a.kv_heads + kh) * b.splits + split) * (2 * KBLK * DH) +
+                qw * KBLK * DH;
+  bf16_t* outp = qw ? a.dv : a.dk;
+#pragma unroll
+  for (int c = 0; c < KT; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int kr = 16 * KT * kw + 16 * c + 4 * q4 + r;
+      if (kr >= nk) continue;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float v = (qw ? dv[c][j][r] : dk[c][j][r]) * os;
+        if (b.splits > 1)
+          part[kr * DH + 16 * j + l16] = v;
+        else
+          outp[krow + (int64_t)kr * ks + 16 * j + l16] = f2bf(v);
+      }
+    }
+}
+
+// Sums the float32 partials of a key block's step ranges in their order and rounds once. One thread per
+// 8 columns of a key's dK or dV row.
+__global__ __launch_bounds__(256) void attn_dkdv_reduce_kernel(AttnArgs a, AttnBatch b) {
+  int ei = 0;
+  const int blk = (int)blockIdx.x / 16;  // (key block, key/value head) of the launch
+  while (ei + 1 < b.count && b.e[ei + 1].blocks0 * a.kv_heads <= blk) ++ei;
+  const AttnEp E = b.e[ei];
+  const int kh = blk % a.kv_heads, kb = blk / a.kv_heads - E.blocks0;
+  const int id = ((int)blockIdx.x & 15) * 256 + threadIdx.x;
+  const int which = id >> 11, kr = (id >> 4) & (KBLK - 1), c0 = (id & 15) * 8;
+  if (kb * KBLK + kr >= E.L) return;
+  const int steps = (a.heads / a.kv_heads) * ((E.L + BLK - 1) / BLK - kb * (KBLK / BLK));
+  const int ns = (steps + b.chunk - 1) / b.chunk;
+  const float* p = b.part + (int64_t)blk * b.splits * (2 * KBLK * DH) + (which * KBLK + kr) * DH + c0;
+  f32x4 s0 = *reinterpret_cast<const f32x4*>(p), s1 = *reinterpret_cast<const f32x4*>(p + 4);
+  for (int i = 1; i < ns; ++i) {
+    p += 2 * KBLK * DH;
+    s0 += *reinterpret_cast<const f32x4*>(p);
+    s1 += *reinterpret_cast<const f32x4*>(p + 4);
+  }
+  bf16_t* o = (which ? a.dv : a.dk) + ((int64_t)(E.row0 + kb * KBLK + kr) * a.kv_heads + kh) * DH + c0;
+  *reinterpret_cast<u32x4*>(o) = u32x4{pack_bf16x2(s0[0], s0[1]), pack_bf16x2(s0[2], s0[3]),
+                                       pack_bf16x2(s1[0], s1[1]), pack_bf16x2(s1[2], s1[3])};
 }
 
 // dQ of one (query head, 64 QT-query block). Wave w owns queries 16 QT w .. + 16 QT - 1 as QT tiles of
@@ -545,21 +685,24 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnArgs a, AttnBatch b
     }
 }
 
-size_t attn_lds_bytes(int kernel) { return 2 * (size_t)(kernel == 1 ? kQoBuf : kKvBuf); }
-
 template <class K>
-static hipError_t launch_blocks(K kernel, bool& attr, size_t lds, int rows, int per, const AttnArgs& a, AttnBatch b,
-                                int id, hipStream_t s) {
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+static hipError_t set_lds(K kernel, bool& attr, size_t lds) {
+  if (attr) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  attr = e == hipSuccess;
+  return e;
+}
+
+// A per-query kernel on blocks of `rows` queries.
+template <class K>
+static hipError_t launch_queries(K kernel, bool& attr, int rows, const AttnArgs& a, AttnBatch b, int id, hipStream_t s) {
+  constexpr size_t lds = 2 * (size_t)kKvBuf;
+  if (hipError_t e = set_lds(kernel, attr, lds)) return e;
   int n = 0;
   for (int i = 0; i < b.count; ++i) {
     b.e[i].blocks = (b.e[i].L + rows - 1) / rows;
     b.e[i].wg_begin = n;
-    n += b.e[i].blocks * per;
+    n += b.e[i].blocks * a.heads;
   }
   if (n <= 0) return hipSuccess;
   KernelTimer t(id, s);
@@ -567,22 +710,45 @@ static hipError_t launch_blocks(K kernel, bool& attr, size_t lds, int rows, int 
   return hipGetLastError();
 }
 
+template <int KT>
+static hipError_t launch_keys(bool& attr, const AttnArgs& a, AttnBatch b, hipStream_t s) {
+  constexpr int KBLK = 64 * KT;
+  constexpr size_t lds = 2 * (size_t)kQoBuf + 2 * KBLK * PR * 2;
+  static_assert(2 * kQoBuf >= 65536 && lds <= 160 * 1024, "the exchange at the end needs 64 KiB");
+  if (hipError_t e = set_lds(attn_dkdv_kernel<KT>, attr, lds)) return e;
+  int n = 0, blocks = 0;
+  for (int i = 0; i < b.count; ++i) {
+    b.e[i].blocks = (b.e[i].L + KBLK - 1) / KBLK;
+    b.e[i].blocks0 = blocks;
+    b.e[i].wg_begin = n;
+    blocks += b.e[i].blocks;
+    for (int p = 0; p < b.splits; ++p)
+      n += whole_pieces<KT>(b.e[i].L, a.heads / a.kv_heads, p, b.chunk) * a.kv_heads;
+    n += b.e[i].blocks * a.kv_heads;
+  }
+  if (n <= 0) return hipSuccess;
+  KernelTimer t(K_ATTN_DKDV, s);
+  hipLaunchKernelGGL(attn_dkdv_kernel<KT>, dim3(n), dim3(512), lds, s, a, b);
+  if (b.splits > 1)
+    hipLaunchKernelGGL(attn_dkdv_reduce_kernel, dim3(blocks * a.kv_heads * 16), dim3(256), 0, s, a, b);
+  return hipGetLastError();
+}
+
 hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStream_t s) {
-  static bool attr[5] = {};
-  const size_t lds = attn_lds_bytes(kernel);
-  // Two query tiles per wave where their workgroups fill the chip's two per CU more than once; below that
-  // the longest chain of key blocks is the time, and a step of one tile is the shorter one. Statistics
+  static bool attr[6] = {};
+  if (kernel == 1) return b.tiles == 1 ? launch_keys<1>(attr[4], a, b, s) : launch_keys<2>(attr[5], a, b, s);
+  // Two query tiles per wave where their workgroups fill the chip's two per CU one and a half times; below
+  // that the longest chain of key blocks is the time, and a step of one tile is the shorter one. Statistics
   // + dQ, one tile / two: 2048 rows x 16 heads (256 two-tile workgroups) 110 / 131 us, 4 episodes of 4096
-  // rows x 16 (512) 119 / 140, 4096 rows x 32 (1024) 514 / 413, 16 episodes of 1024 x 8 (1024) 239 / 225.
+  // rows x 16 (528) 119 / 140, 4096 rows x 32 (1024) 514 / 413, 16 episodes of 1024 x 8 (1024) 239 / 225.
   int n2 = 0;
   for (int i = 0; i < b.count; ++i) n2 += (b.e[i].L + 127) / 128 * a.heads;
-  const bool wide = n2 > 512;
+  const bool wide = n2 > 768;
   if (kernel == 0)
-    return wide ? launch_blocks(attn_fwd_stats_kernel<2>, attr[0], lds, 128, a.heads, a, b, K_ATTN_FWD, s)
-                : launch_blocks(attn_fwd_stats_kernel<1>, attr[1], lds, 64, a.heads, a, b, K_ATTN_FWD, s);
-  if (kernel == 1) return launch_blocks(attn_dkdv_kernel, attr[2], lds, 64, a.kv_heads, a, b, K_ATTN_DKDV, s);
-  return wide ? launch_blocks(attn_dq_kernel<2>, attr[3], lds, 128, a.heads, a, b, K_ATTN_DQ, s)
-              : launch_blocks(attn_dq_kernel<1>, attr[4], lds, 64, a.heads, a, b, K_ATTN_DQ, s);
+    return wide ? launch_queries(attn_fwd_stats_kernel<2>, attr[0], 128, a, b, K_ATTN_FWD, s)
+                : launch_queries(attn_fwd_stats_kernel<1>, attr[1], 64, a, b, K_ATTN_FWD, s);
+  return wide ? launch_queries(attn_dq_kernel<2>, attr[2], 128, a, b, K_ATTN_DQ, s)
+              : launch_queries(attn_dq_kernel<1>, attr[3], 64, a, b, K_ATTN_DQ, s);
 }
 
 }  // namespace attt

@@ -164,11 +164,16 @@ struct AttnEp {
   int32_t L;        // rows
   int32_t blocks;   // blocks of the kernel's rows (set at launch, as is wg_begin)
   int32_t wg_begin; // first workgroup of the episode within the launch
-  int32_t pad;
+  int32_t blocks0;  // first key block of the episode within the launch (dK / dV)
 };
+constexpr int kAttnKeyBlock = 128;  // keys per block of a split dK / dV walk
+constexpr size_t kAttnPartBytes = 2 * kAttnKeyBlock * 128 * sizeof(float);  // one partial dK, dV of a block
 struct AttnBatch {
   int32_t count;
-  int32_t pad;
+  // dK / dV: keys per block / 64; workgroups per key block, each over `chunk` (query block, query head)
+  // steps; above one (128 keys) they write partials [block][kv head][split][2][128][128]
+  int32_t tiles, splits, chunk;
+  float* part;
   AttnEp e[kEpBatch];
 };
 // kernel 0: forward statistics, 1: dK and dV, 2: dQ

@@ -340,6 +340,36 @@ def test_attention_validation(L):
     assert _attn(L, N=0, off=[0, 0]) == attt.OK               # nothing to do, nothing touched
 
 
+def test_attention_split_validation(L):
+    need = ctypes.c_size_t(7)
+
+    def size(N=64, H=4, Hkv=2, dh=128, off=None, E=1):
+        op = None
+        if off is not None:
+            _, op = _off(off)
+            E = len(off) - 1
+        return L.attt_attention_workspace_size(op, E, N, H, Hkv, dh, ctypes.byref(need))
+
+    assert size(dh=64) == attt.EUNSUPPORTED
+    assert size(H=6, Hkv=4) == attt.EINVAL
+    assert size(N=-1) == attt.EINVAL
+    assert size(off=[0, 10, 60]) == attt.EINVAL
+    assert L.attt_attention_workspace_size(None, 1, 64, 4, 2, 128, None) == attt.EINVAL
+    assert size(N=0, off=[0, 0]) == attt.OK and need.value == 0
+    # a long batch fills the chip by itself; one short episode on few key/value heads does not
+    assert size(N=16 * 8192, H=32, Hkv=8, off=list(range(0, 16 * 8192 + 1, 8192))) == attt.OK and need.value == 0
+    assert size(N=2048, H=16, Hkv=4) == attt.OK and need.value > 0
+    assert need.value % (16 * 4 * 131072) == 0   # float32 dK and dV of 128 keys per piece of each block
+
+    def call(ws, nbytes):
+        return L.attt_attention_bwd_split(FAKE, FAKE, FAKE, FAKE, None, 1, 2048, 16, 4, 128, 0.088, FAKE, FAKE, FAKE,
+                                          FAKE, FAKE, ws, nbytes, None)
+
+    assert call(FAKE_WS, need.value - 1) == attt.ENOSPACE
+    assert call(None, need.value) == attt.EINVAL
+    assert call(ctypes.c_void_p(0x7F0000000010), need.value) == attt.EINVAL  # misaligned
+
+
 def _fwd(L, count=1, **kw):
     p = dict(x=FAKE, y=FAKE_WS, A=FAKE, B=FAKE_WS, rows=32, d_in=64, d_out=64, rank=8, scale=2.0)
     p.update(kw)

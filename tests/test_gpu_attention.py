@@ -107,13 +107,48 @@ def test_many_episodes_two_checked(attt):
 
 @pytest.mark.parametrize("H,wide", [(16, False), (32, True)])
 def test_one_or_two_query_tiles_per_wave(attt, H, wide):
-    """Workgroups of 64 and of 128 queries (more than 512 of the latter): episodes that end inside the
+    """Workgroups of 64 and of 128 queries (more than 768 of the latter): episodes that end inside the
     first and the second half of a 128-query block, on its edges and on those of a wave's 32 queries."""
-    lens = [1, 31, 33, 63, 64, 65, 97, 127, 128, 129, 191, 192, 193, 200, 256, 257]
+    lens = [1, 31, 33, 63, 64, 65, 97, 127, 128, 129, 191, 192, 193, 200, 256, 257, 130]
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
-    assert (sum((n + 127) // 128 for n in lens) * H > 512) == wide
+    assert (sum((n + 127) // 128 for n in lens) * H > 768) == wide
     note(f"attention ragged: {H} heads, episodes {lens}")
     _check_full(attt, int(off[-1]), H, 4, off, 71)
+
+
+def _no_workspace(attt, q, k, v, do, off):
+    """The C entry point that takes no workspace: one workgroup per key block."""
+    import ctypes
+
+    import torch
+    N, H, _ = q.shape
+    out = [torch.empty_like(q), torch.empty_like(k), torch.empty_like(v), torch.empty(H, N, device="cuda"),
+           torch.empty(H, N, device="cuda")]
+    st = attt.load().attt_attention_bwd(*[t.data_ptr() for t in (q, k, v, do)],
+                                        off.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)), len(off) - 1, N, H,
+                                        k.shape[1], DH, 1.0 / DH ** 0.5, *[t.data_ptr() for t in out],
+                                        torch.cuda.current_stream().cuda_stream)
+    assert st == attt.OK
+    return out
+
+
+@pytest.mark.parametrize("lens,H,Hkv", [([1, 64, 65, 127, 128, 129], 4, 2), ([700], 8, 1), ([257, 1100, 1, 383], 8, 2),
+                                        ([1024], 16, 1), ([33 * 64], 8, 8), ([3000, 64, 2000], 8, 4)])
+def test_split_walks(attt, lens, H, Hkv):
+    """dK and dV by parts of the queries (whole pieces and rests; a walk of whole pieces alone) and by one
+    walk per key block, against the oracle."""
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    N = int(off[-1])
+    note(f"attention split: heads {H}/{Hkv}, episodes {lens}, workspace {attt.attention_workspace_size(N, H, Hkv, off)}")
+    q, k, v, do = _inputs(N, H, Hkv, 81)
+    one = [host(t) for t in _no_workspace(attt, *[dev_dense(t) for t in (q, k, v, do)], off)]
+    got = _gpu(attt, q, k, v, do, off)
+    r = oat.attention_fwd_bwd(q.f32, k.f32, v.f32, do.f32, off)
+    for name, g, o in zip(("dQ", "dK", "dV"), got, one):
+        _cmp(name, g, r[name])
+        _cmp(name + " (one walk)", o, r[name])
+    if sum(lens) > 650:
+        assert attt.attention_workspace_size(N, H, Hkv, off) > 0
 
 
 def test_deterministic(attt):
