@@ -1392,9 +1392,16 @@ extern "C" attt_status attt_lora_grad(const attt_lora_problem* problems, int32_t
       p1, [&](const LoraP1Job& J) { return J.rows_pad / (dtype == ATTT_BF16 ? kLoraP1Rows : kLoraP1RowsF32); },
       [&](const LoraP1Batch& b, int n) { return launch_lora_pass1(dtype, b.j[0].nt, b, n, ws, s); }, "lora_u_du");
   if (st) return st;
+  // Pass 2 in bf16 on 128 columns a workgroup where that leaves four per CU, else on 64 (64 / 128: 2304
+  // workgroups of 128 at 8192 rows of a 4096 model 69.5 / 66.4 us, about 3000 at 3 episodes of 10000 rows of
+  // 5120 120 / 108, 8 of 16384 rows at rank 64 360 / 291; 1008 at 4 ragged episodes of 1024 39.4 / 41.4, 288 at 2048 rows of 2048
+  // 13.2 / 16.1).
+  int64_t wide = 0;
+  for (const LoraP2Job& J : p2) wide += J.splits * ceil_div(J.cols, 2 * kLoraColTile);
+  const int col_tile = dtype == ATTT_BF16 && wide >= 1024 ? 2 * kLoraColTile : kLoraColTile;
   st = lora_launch_all(
-      p2, [](const LoraP2Job& J) { return J.splits * (int)ceil_div(J.cols, kLoraColTile); },
-      [&](const LoraP2Batch& b, int n) { return launch_lora_pass2(dtype, b, n, ws, s); }, "lora_dadb");
+      p2, [&](const LoraP2Job& J) { return J.splits * (int)ceil_div(J.cols, col_tile); },
+      [&](const LoraP2Batch& b, int n) { return launch_lora_pass2(dtype, col_tile, b, n, ws, s); }, "lora_dadb");
   if (st) return st;
   return lora_launch_all(
       red, [](const LoraRedJob& J) { return (int)ceil_div((int64_t)J.rank * J.d_in + (int64_t)J.d_out * J.rank, 256); },

@@ -293,7 +293,7 @@ constexpr int kLoraRowTile = 128;  // row padding of the transposed pass-1 resul
 constexpr int kLoraP1Rows = 64;    // pass-1 rows per workgroup (16 per wave)
 constexpr int kLoraP1RowsF32 = 16; // the same, float32 (the waves split the contraction)
 constexpr int kLoraKBlock = 128;   // pass-1 contraction step
-constexpr int kLoraColTile = 64;   // pass-2 output columns per workgroup
+constexpr int kLoraColTile = 64;   // pass-2 output columns per workgroup (bf16: or twice as many)
 constexpr int kLoraTStep = 64;     // pass-2 rows per step
 constexpr int kLoraMaxTiles = 4;   // rank tiles of 16 per job (64 ranks)
 constexpr int kLoraJobBatch = 16;  // jobs per launch (kernel-argument descriptors)
@@ -376,7 +376,7 @@ hipError_t launch_lora_bt(int dtype, const LoraBTBatch& b, int blocks, uint8_t* 
 // nt: the largest rank-tile count of the batch's jobs (bf16 kernels are specialised on it)
 hipError_t launch_lora_pass1(int dtype, int nt, const LoraP1Batch& b, int blocks, uint8_t* ws,
                              hipStream_t s);
-hipError_t launch_lora_pass2(int dtype, const LoraP2Batch& b, int blocks, uint8_t* ws, hipStream_t s);
+hipError_t launch_lora_pass2(int dtype, int col_tile, const LoraP2Batch& b, int blocks, uint8_t* ws, hipStream_t s);
 hipError_t launch_lora_reduce(const LoraRedBatch& b, int blocks, uint8_t* ws, hipStream_t s);
 
 // ---- serving: grouped multi-adapter forward, adapter swap --------------------------------

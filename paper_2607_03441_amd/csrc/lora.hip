@@ -16,9 +16,9 @@
 //     value v ([2][16, rows_pad]), so pass 2 contracts with ~16 significant bits.
 //   Pass 2 (lora_p2_*): out[c, k] = sum_t L[c, t] src[t, k] with (L, src) = (s dU^T, x) for dA
 //     and (s U^T, dy) for dB. The contraction runs over rows, the slow index of src, so 64-row
-//     x 64-column tiles of src are written transposed into LDS (two rows per 32-bit store,
-//     double-buffered, one barrier per step) and read back as K-contiguous MFMA operands; the
-//     step's slice of L (both planes) is staged in LDS once per workgroup beside them.
+//     x 64- or 128-column tiles of src go to LDS row-major (double-buffered, one barrier per
+//     step) and come back as MFMA operands through transposing reads; the step's slice of L (both
+//     planes) is staged in LDS once per workgroup beside them.
 //     Rows are split into `splits` ranges whose float32 partials go to the workspace.
 //   Reduce (lora_reduce_kernel): sums the split partials in a fixed order and adds them to
 //     dA [r, d_in] and dB [d_out, r]. No float atomics: results are bit-reproducible.
@@ -168,36 +168,49 @@ __global__ __launch_bounds__(256) void lora_p1_bf16_kernel(LoraP1Batch b, uint8_
 // ------------------------------------------------------------------------------------------
 // bf16 pass 2
 // ------------------------------------------------------------------------------------------
-constexpr int kP2Pitch = kLoraTStep + 8;  // LDS row pitch (bf16) of the transposed tile
+constexpr int kP2Pitch = kLoraTStep + 8;  // LDS row pitch (bf16) of L's slices
 
-size_t lora_p2_lds(int max_nt) { return (size_t)(2 * kLoraColTile + 2 * max_nt * 32) * kP2Pitch * 2; }
+template <int CT>
+constexpr size_t lora_p2_lds(int max_nt) {
+  return (size_t)(2 * kLoraTStep * (64 * CT + 8) + 2 * max_nt * 32 * kP2Pitch) * 2;
+}
 
+// 64 CT columns x one row range per workgroup, CT column tiles of 16 per wave. Each step's 64 rows go to
+// LDS row-major with 16-byte stores and are read as the MFMA's B operand with transposing reads
+// (ds_read_tr16_b64): lane (l16, g) receives its column at rows 32 ks + 4 g .. +3 and 16 rows further, so
+// L's slices are staged in that order. Bound by memory: two tiles per wave read rows 256 bytes at a time
+// and stage half the L slices for each byte of them. Transposed stores of 32-bit words (eight for these two)
+// and 128-byte rows took 82 us for 288 MB of inputs at 8192 rows of a 4096 model; this takes 66 (4.3 TB/s).
+template <int CT>
 __global__ __launch_bounds__(256) void lora_p2_bf16_kernel(LoraP2Batch b, int max_nt, uint8_t* __restrict__ ws) {
+  constexpr int kCols = 64 * CT, kPitch = kCols + 8, kGroups = kCols / 8, kRows = 256 / kGroups;
   const int ji = find_job(b, (int)blockIdx.x);
   const LoraP2Job& Jr = b.j[ji];
   const int cols = Jr.cols, nt = Jr.nt;
-  const int ncb = (cols + kLoraColTile - 1) / kLoraColTile;
+  const int ncb = (cols + kCols - 1) / kCols;
   const int local = (int)blockIdx.x - Jr.b_begin;
   const int sp = local / ncb, cb = local % ncb;
-  const int col0 = cb * kLoraColTile;
+  const int col0 = cb * kCols;
   const int tper = ((Jr.rows_pad / Jr.splits + kLoraTStep - 1) / kLoraTStep) * kLoraTStep;
   const int t_begin = sp * tper;
   const int t_end = min(Jr.rows_pad, t_begin + tper);
 
-  // Dynamic LDS: xs[2][kLoraColTile * kP2Pitch], then lt[2][max_nt][32 * kP2Pitch], the step's
-  // slice of every tile's L (planes hi, lo: 32 rows of kLoraTStep), shared by the workgroup's
-  // four waves, which all contract with the same fragments. max_nt: the batch's largest nt.
+  // Dynamic LDS: xs[2][kLoraTStep * kPitch], then lt[2][max_nt][32 * kP2Pitch], the step's slice of every
+  // tile's L (planes hi, lo: 32 rows of kLoraTStep), shared by the workgroup's four waves, which all
+  // contract with the same fragments. max_nt: the batch's largest nt.
   extern __shared__ __align__(16) uint8_t p2_smem[];
-  bf16_t (*xs)[kLoraColTile * kP2Pitch] = reinterpret_cast<bf16_t (*)[kLoraColTile * kP2Pitch]>(p2_smem);
-  bf16_t* lt_base = reinterpret_cast<bf16_t*>(p2_smem) + 2 * kLoraColTile * kP2Pitch;
+  bf16_t (*xs)[kLoraTStep * kPitch] = reinterpret_cast<bf16_t (*)[kLoraTStep * kPitch]>(p2_smem);
+  bf16_t* lt_base = reinterpret_cast<bf16_t*>(p2_smem) + 2 * kLoraTStep * kPitch;
   auto lt = [&](int buf, int t) { return lt_base + (buf * max_nt + t) * (32 * kP2Pitch); };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4;
-  // staging: rows 2*pr, 2*pr+1 of the step, columns 8*cg .. 8*cg+7 of the tile
-  const int pr = tid >> 3, cg = tid & 7;
+  // staging: rows pr, pr + kRows, ... of the step, columns 8*cg .. 8*cg+7 of the tile
+  const int pr = tid / kGroups, cg = tid % kGroups;
   const bool cin = col0 + cg * 8 < cols;  // cols % 8 == 0: a column chunk is whole or absent
-  // L staging: plane row lr (hi rows 0-15, lo rows 16-31), 8 consecutive t from 8*lk
+  // L staging: plane row lr (hi rows 0-15, lo rows 16-31), 8 consecutive t from 8*lk; of a chunk of 32, t =
+  // 16 h + 4 g + i is stored at 8 g + 4 h + i
   const int lr = tid >> 3, lk = tid & 7;
+  const int lpos = lr * kP2Pitch + 32 * (lk >> 2) + 16 * (lk & 1) + 4 * ((lk >> 1) & 1);
   const bf16_t* src = static_cast<const bf16_t*>(Jr.src);
   // a tile's pass-1 result: planes hi and lo, [2][16][rows_pad] bf16
   __amdgpu_buffer_rsrc_t rl[kLoraMaxTiles];
@@ -205,54 +218,63 @@ __global__ __launch_bounds__(256) void lora_p2_bf16_kernel(LoraP2Batch b, int ma
   for (int t = 0; t < kLoraMaxTiles; ++t)
     rl[t] = buffer_rsrc(ws + (t < nt ? Jr.t[t].lt_off : 0), t < nt ? 2 * 16 * Jr.rows_pad * 2 : 0);
 
-  f32x4 acc[kLoraMaxTiles];
+  f32x4 acc[kLoraMaxTiles][CT];
 #pragma unroll
-  for (int t = 0; t < kLoraMaxTiles; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < kLoraMaxTiles; ++t)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Rows of step t0 go through a descriptor based at row t0 (offsets stay small) whose range
   // ends at the input's last row.
-  auto load = [&](int t0, u32x4 (&v)[2], u32x4 (&la)[kLoraMaxTiles]) {
+  auto load = [&](int t0, u32x4 (&v)[2 * CT], u32x4 (&la)[kLoraMaxTiles]) {
     const int nr = max(0, min(kLoraTStep, Jr.rows - t0));
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(src + (int64_t)t0 * cols, nr * cols * 2);
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int e = 0; e < 2 * CT; ++e)
       v[e] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, cin ? (uint32_t)((2 * pr + e) * cols + col0 + cg * 8) * 2u : kOOB, 0, 0));
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, cin ? (uint32_t)((pr + e * kRows) * cols + col0 + cg * 8) * 2u : kOOB, 0, 0));
 #pragma unroll
     for (int t = 0; t < kLoraMaxTiles; ++t)
       if (t < nt)  // uniform: a job's tile count; unused tiles issue no load
         la[t] = __builtin_bit_cast(
             u32x4, __builtin_amdgcn_raw_buffer_load_b128(rl[t], (uint32_t)(lr * Jr.rows_pad + t0 + lk * 8) * 2u, 0, 0));
   };
-  u32x4 v0[2], v1[2], la0[kLoraMaxTiles], la1[kLoraMaxTiles];
-  // One step: store its rows transposed (row pairs as 32-bit words) into buffer `buf` and the L
-  // slices into lt[buf], one barrier, two MFMA k-steps of 32 rows, each as the hi and then the
-  // lo plane of L. Both buffers `buf` were last read two steps earlier, before the previous
-  // step's barrier.
-  auto step = [&](int buf, const u32x4 (&v)[2], const u32x4 (&la)[kLoraMaxTiles]) {
-    uint32_t* dst = reinterpret_cast<uint32_t*>(xs[buf]);
+  u32x4 v0[2 * CT], v1[2 * CT], la0[kLoraMaxTiles], la1[kLoraMaxTiles];
+  // One step: store its rows into buffer `buf` and the L slices into lt[buf], one barrier, two MFMA
+  // k-steps of 32 rows, each as the hi and then the lo plane of L. Both buffers `buf` were last read two
+  // steps earlier, before the previous step's barrier.
+  auto step = [&](int buf, const u32x4 (&v)[2 * CT], const u32x4 (&la)[kLoraMaxTiles]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t lo0 = v[0][e] & 0xFFFFu, hi0 = v[0][e] >> 16;
-      const uint32_t lo1 = v[1][e] & 0xFFFFu, hi1 = v[1][e] >> 16;
-      dst[((cg * 8 + 2 * e) * kP2Pitch + 2 * pr) >> 1] = lo0 | (lo1 << 16);
-      dst[((cg * 8 + 2 * e + 1) * kP2Pitch + 2 * pr) >> 1] = hi0 | (hi1 << 16);
-    }
+    for (int e = 0; e < 2 * CT; ++e) *reinterpret_cast<u32x4*>(xs[buf] + (pr + e * kRows) * kPitch + cg * 8) = v[e];
 #pragma unroll
     for (int t = 0; t < kLoraMaxTiles; ++t)
-      if (t < nt) *reinterpret_cast<u32x4*>(lt(buf, t) + lr * kP2Pitch + lk * 8) = la[t];
+      if (t < nt) {
+        *reinterpret_cast<uint2*>(lt(buf, t) + lpos) = uint2{la[t][0], la[t][1]};
+        *reinterpret_cast<uint2*>(lt(buf, t) + lpos + 8) = uint2{la[t][2], la[t][3]};
+      }
     __syncthreads();
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      const bf16x8 bv = __builtin_bit_cast(
-          bf16x8, *reinterpret_cast<const u32x4*>(xs[buf] + (wave * 16 + l16) * kP2Pitch + ks * 32 + g * 8));
+      typedef short v4s __attribute__((ext_vector_type(4)));
+      typedef __attribute__((address_space(3))) v4s* lds_v4s;
+      bf16x8 bv[CT];
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+        // within a group of 16 lanes, lane 4 e + j addresses row e at columns 4 j .. +3
+        const bf16_t* p = xs[buf] + (32 * ks + 4 * g + ((lane >> 2) & 3)) * kPitch + (wave * CT + c) * 16 + 4 * (lane & 3);
+        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p)));
+        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + 16 * kPitch)));
+        bv[c] = __builtin_bit_cast(bf16x8, u32x4{lo.x, lo.y, hi.x, hi.y});
+      }
 #pragma unroll
       for (int t = 0; t < kLoraMaxTiles; ++t) {
         if (t >= nt) break;
 #pragma unroll
         for (int hl = 0; hl < 2; ++hl) {
-          const u32x4 a = *reinterpret_cast<const u32x4*>(lt(buf, t) + (hl * 16 + l16) * kP2Pitch + ks * 32 + g * 8);
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), bv, acc[t], 0, 0, 0);
+          const bf16x8 a = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const u32x4*>(lt(buf, t) + (hl * 16 + l16) * kP2Pitch + ks * 32 + g * 8));
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bv[c], acc[t][c], 0, 0, 0);
         }
       }
     }
@@ -266,14 +288,16 @@ __global__ __launch_bounds__(256) void lora_p2_bf16_kernel(LoraP2Batch b, int ma
     if (t0 + 2 * kLoraTStep < t_end) load(t0 + 2 * kLoraTStep, v0, la0);
     step(1, v1, la1);
   }
-  const int col = col0 + wave * 16 + l16;
-  if (col < cols) {
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const int col = col0 + (wave * CT + c) * 16 + l16;
+    if (col >= cols) continue;
 #pragma unroll
     for (int t = 0; t < kLoraMaxTiles; ++t) {
       if (t >= nt) break;
       float* part = reinterpret_cast<float*>(ws + Jr.t[t].part_off) + (int64_t)sp * 16 * cols;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) part[(int64_t)(g * 4 + v) * cols + col] = acc[t][v];
+      for (int v = 0; v < 4; ++v) part[(int64_t)(g * 4 + v) * cols + col] = acc[t][c][v];
     }
   }
 }
@@ -524,15 +548,22 @@ hipError_t launch_lora_pass1(int dtype, int nt, const LoraP1Batch& b, int blocks
   return hipGetLastError();
 }
 
-hipError_t launch_lora_pass2(int dtype, const LoraP2Batch& b, int blocks, uint8_t* ws, hipStream_t s) {
-  if (blocks <= 0) return hipSuccess;
-  KernelTimer t(K_LORA_DADB, s);
+template <int CT>
+static hipError_t launch_p2_bf16(const LoraP2Batch& b, int blocks, uint8_t* ws, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute((const void*)lora_p2_bf16_kernel<CT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)lora_p2_lds<CT>(kLoraMaxTiles));
+  if (attr != hipSuccess) return attr;
   int max_nt = 1;
   for (int i = 0; i < b.count; ++i) max_nt = max(max_nt, b.j[i].nt);
-  if (dtype == 1)
-    hipLaunchKernelGGL(lora_p2_bf16_kernel, dim3(blocks), dim3(256), lora_p2_lds(max_nt), s, b, max_nt, ws);
-  else
-    hipLaunchKernelGGL(lora_p2_f32_kernel, dim3(blocks), dim3(256), 0, s, b, ws);
+  hipLaunchKernelGGL(lora_p2_bf16_kernel<CT>, dim3(blocks), dim3(256), lora_p2_lds<CT>(max_nt), s, b, max_nt, ws);
+  return hipGetLastError();
+}
+
+hipError_t launch_lora_pass2(int dtype, int col_tile, const LoraP2Batch& b, int blocks, uint8_t* ws, hipStream_t s) {
+  if (blocks <= 0) return hipSuccess;
+  KernelTimer t(K_LORA_DADB, s);
+  if (dtype == 1) return col_tile == 128 ? launch_p2_bf16<2>(b, blocks, ws, s) : launch_p2_bf16<1>(b, blocks, ws, s);
+  hipLaunchKernelGGL(lora_p2_f32_kernel, dim3(blocks), dim3(256), 0, s, b, ws);
   return hipGetLastError();
 }
 

@@ -543,3 +543,24 @@ def test_ce_fused_exact_after_abort_is_deterministic(attt):
     finally:
         attt.ce_set_wait_limit()
     assert not bad, bad
+
+
+@pytest.mark.parametrize("count", [3, 58])
+def test_lora_grad_column_tiles(attt, count):
+    """Pass 2 on 64 and (58 problems: 1160 workgroups) on 128 columns a workgroup: 264 and 136 columns end
+    inside a tile, 2000 rows inside a step. Float32 results of 16-bit factors: 2^-17 each, 1e-5 in norm."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17)
+    rows, d_in, d_out, r = 2000, 264, 136, 20
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=g, device="cuda").bfloat16()
+
+    ps = [dict(x=rnd(rows, d_in), dy=rnd(rows, d_out), A=rnd(r, d_in), B=rnd(d_out, r), scale=0.8,
+               dA=torch.zeros(r, d_in, device="cuda"), dB=torch.zeros(d_out, r, device="cuda")) for _ in range(count)]
+    attt.lora_grad(ps)
+    for p in ps:
+        x, dy, A, B = (p[k].double() for k in ("x", "dy", "A", "B"))
+        for got, want in ((p["dA"], 0.8 * (dy @ B).t() @ x), (p["dB"], 0.8 * dy.t() @ (x @ A.t()))):
+            assert float((got.double() - want).norm() / want.norm()) < 1e-5
