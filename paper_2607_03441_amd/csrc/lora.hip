@@ -550,12 +550,15 @@ hipError_t launch_lora_pass1(int dtype, int nt, const LoraP1Batch& b, int blocks
 
 template <int CT>
 static hipError_t launch_p2_bf16(const LoraP2Batch& b, int blocks, uint8_t* ws, hipStream_t s) {
-  static const hipError_t attr = hipFuncSetAttribute((const void*)lora_p2_bf16_kernel<CT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)lora_p2_lds<CT>(kLoraMaxTiles));
-  if (attr != hipSuccess) return attr;
   int max_nt = 1;
   for (int i = 0; i < b.count; ++i) max_nt = max(max_nt, b.j[i].nt);
-  hipLaunchKernelGGL(lora_p2_bf16_kernel<CT>, dim3(blocks), dim3(256), lora_p2_lds<CT>(max_nt), s, b, max_nt, ws);
+  const size_t lds = lora_p2_lds<CT>(max_nt);
+  if (lds > 65536) {  // four rank tiles on 128 columns; per device, so on every such call
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)lora_p2_bf16_kernel<CT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(lora_p2_bf16_kernel<CT>, dim3(blocks), dim3(256), lds, s, b, max_nt, ws);
   return hipGetLastError();
 }
 
