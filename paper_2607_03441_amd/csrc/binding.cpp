@@ -19,41 +19,51 @@ namespace {
 // A Python error is set; unwinds to the module function's handler.
 struct PyError {};
 
-struct Ref {  // an owned reference
-  PyObject* p;
-  explicit Ref(PyObject* q) : p(q) {
-    if (!p) throw PyError{};
-  }
-  ~Ref() { Py_XDECREF(p); }
-  Ref(const Ref&) = delete;
-  Ref& operator=(const Ref&) = delete;
-};
-
 [[noreturn]] void raise(PyObject* type, const char* fmt, const char* arg = "") {
   PyErr_Format(type, fmt, arg);
   throw PyError{};
 }
 
-// What the call's mappings hand out, held until it returns (a dict holds its own values).
+// What a call reads, held until it returns: the problems, and the tensors that their mappings hand out.
+// Only then may the allocator give their memory to the call's own workspace, whatever the caller's
+// objects do meanwhile (a sequence may make its problems on access).
 struct Held {
   std::vector<PyObject*> v;
   ~Held() {
     for (PyObject* o : v) Py_DECREF(o);
   }
+  PyObject* keep(PyObject* o) {  // takes over the caller's reference
+    if (!o) throw PyError{};
+    try {
+      v.push_back(o);
+    } catch (...) {
+      Py_DECREF(o);
+      throw;
+    }
+    return o;
+  }
 };
+
+// The problems of a call: a tuple of their own. Like len(), this refuses what has no length (a generator).
+PyObject* list(Held& held, PyObject* seq) {
+  const Py_ssize_t n = PyObject_Size(seq);
+  if (n < 0) throw PyError{};
+  return held.keep(PySequence_Tuple(seq));
+}
 
 // A mapping's entry; nullptr when `optional` and absent.
 PyObject* item(Held& held, PyObject* map, PyObject* key, bool optional = false) {
   if (PyDict_CheckExact(map)) {
     PyObject* v = PyDict_GetItemWithError(map, key);
-    if (v || (optional && !PyErr_Occurred())) return v;
+    if (v) {
+      Py_INCREF(v);
+      return held.keep(v);
+    }
+    if (optional && !PyErr_Occurred()) return nullptr;
     if (!PyErr_Occurred()) PyErr_SetObject(PyExc_KeyError, key);
     throw PyError{};
   }
-  PyObject* v = optional ? PyObject_CallMethod(map, "get", "O", key) : PyObject_GetItem(map, key);
-  if (!v) throw PyError{};
-  held.v.push_back(v);
-  return v;
+  return held.keep(optional ? PyObject_CallMethod(map, "get", "O", key) : PyObject_GetItem(map, key));
 }
 
 const at::Tensor& tensor(PyObject* o, const char* name) {
@@ -83,11 +93,11 @@ float scale_of(Held& held, PyObject* map) {
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 std::vector<attt_lora_problem> lora_problems(Held& held, PyObject* seq, bool check, at::ScalarType* dt, at::Device* dev) {
-  Ref f(PySequence_Fast(seq, "problems must be a sequence"));
-  const Py_ssize_t n = PySequence_Fast_GET_SIZE(f.p);
+  PyObject* f = list(held, seq);
+  const Py_ssize_t n = PyTuple_GET_SIZE(f);
   std::vector<attt_lora_problem> v(n);
   for (Py_ssize_t i = 0; i < n; ++i) {
-    PyObject* p = PySequence_Fast_GET_ITEM(f.p, i);
+    PyObject* p = PyTuple_GET_ITEM(f, i);
     auto get = [&](PyObject* key, const char* name) -> const at::Tensor& {
       PyObject* o = item(held, p, key);
       return check ? device_tensor(o, name) : tensor(o, name);
@@ -144,11 +154,11 @@ PyObject* lora_sgd_step(PyObject* args) {
   double lr;
   int zero;
   if (!PyArg_ParseTuple(args, "Odp", &seq, &lr, &zero)) throw PyError{};
-  Ref f(PySequence_Fast(seq, "params must be a sequence"));
-  const Py_ssize_t n = PySequence_Fast_GET_SIZE(f.p);
+  PyObject* f = list(held, seq);
+  const Py_ssize_t n = PyTuple_GET_SIZE(f);
   std::vector<attt_lora_param> v(n);
   for (Py_ssize_t i = 0; i < n; ++i) {
-    PyObject* p = PySequence_Fast_GET_ITEM(f.p, i);
+    PyObject* p = PyTuple_GET_ITEM(f, i);
     const at::Tensor &P = device_tensor(item(held, p, k_param), "param"), &G = device_tensor(item(held, p, k_grad), "grad");
     if (P.scalar_type() != at::kFloat || G.scalar_type() != at::kFloat || G.numel() != P.numel())
       raise(PyExc_ValueError, "param and grad must be float32 tensors of equal size");
@@ -170,11 +180,11 @@ PyObject* lora_forward(PyObject* args) {
   Held held;
   PyObject* seq;
   if (!PyArg_ParseTuple(args, "O", &seq)) throw PyError{};
-  Ref f(PySequence_Fast(seq, "problems must be a sequence"));
-  const Py_ssize_t n = PySequence_Fast_GET_SIZE(f.p);
+  PyObject* f = list(held, seq);
+  const Py_ssize_t n = PyTuple_GET_SIZE(f);
   std::vector<attt_lora_fwd_problem> v(n);
   for (Py_ssize_t i = 0; i < n; ++i) {
-    PyObject* p = PySequence_Fast_GET_ITEM(f.p, i);
+    PyObject* p = PyTuple_GET_ITEM(f, i);
     auto get = [&](PyObject* key, const char* name) -> const at::Tensor& {
       const at::Tensor& t = device_tensor(item(held, p, key), name);
       if (t.scalar_type() != at::kBFloat16 || t.dim() != 2) raise(PyExc_ValueError, "%s must be a 2-D bfloat16 tensor", name);
@@ -189,16 +199,17 @@ PyObject* lora_forward(PyObject* args) {
 
 // lora_hot_swap(pairs) -> status
 PyObject* lora_hot_swap(PyObject* args) {
+  Held held;
   PyObject* seq;
   if (!PyArg_ParseTuple(args, "O", &seq)) throw PyError{};
-  Ref f(PySequence_Fast(seq, "pairs must be a sequence"));
-  const Py_ssize_t n = PySequence_Fast_GET_SIZE(f.p);
+  PyObject* f = list(held, seq);
+  const Py_ssize_t n = PyTuple_GET_SIZE(f);
   std::vector<attt_lora_swap_item> v(n);
   for (Py_ssize_t i = 0; i < n; ++i) {
-    Ref pair(PySequence_Fast(PySequence_Fast_GET_ITEM(f.p, i), "a pair must be a sequence"));
-    if (PySequence_Fast_GET_SIZE(pair.p) != 2) raise(PyExc_ValueError, "a pair must be (src, dst)");
-    const at::Tensor &src = device_tensor(PySequence_Fast_GET_ITEM(pair.p, 0), "src"),
-                     &dst = device_tensor(PySequence_Fast_GET_ITEM(pair.p, 1), "dst");
+    PyObject* pair = held.keep(PySequence_Tuple(PyTuple_GET_ITEM(f, i)));
+    if (PyTuple_GET_SIZE(pair) != 2) raise(PyExc_ValueError, "a pair must be (src, dst)");
+    const at::Tensor &src = device_tensor(PyTuple_GET_ITEM(pair, 0), "src"),
+                     &dst = device_tensor(PyTuple_GET_ITEM(pair, 1), "dst");
     if (src.scalar_type() != at::kFloat || dst.scalar_type() != at::kBFloat16 || src.numel() != dst.numel())
       raise(PyExc_ValueError, "src must be float32 and dst bfloat16 of the same numel");
     v[i] = {static_cast<const float*>(src.data_ptr()), dst.data_ptr(), src.numel()};

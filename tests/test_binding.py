@@ -49,3 +49,48 @@ def test_any_mapping_and_no_problems():
     assert attt.lora_workspace_size((Mapping(FULL),), attt.BF16) == want > 256
     assert attt.lora_workspace_size([], attt.BF16) == 256
     assert attt.lora_grad([]) is None
+
+
+class OnAccess:
+    """A sequence that makes its problems when they are read and keeps none of them."""
+
+    def __init__(self, n, make):
+        self.n, self.make = n, make
+
+    def __len__(self):
+        return self.n
+
+    def __getitem__(self, i):
+        if i >= self.n:
+            raise IndexError
+        return self.make(i)
+
+
+def test_problems_live_until_the_call_returns():
+    """A problem that only the call refers to is released when the library is done with its pointers, not
+    before: the last of 8000 problems (whose grouping takes the library most of the call) goes at the end."""
+    import time
+    import weakref
+    big = dict(FULL, A=torch.zeros(64, 8), B=torch.zeros(8, 64), x=torch.zeros(4, 8))
+    seen = {}
+
+    class Problem(dict):
+        pass
+
+    def make(i):
+        p = Problem(big)
+        if i == 7999:
+            seen["read"] = time.perf_counter()
+            weakref.finalize(p, lambda: seen.setdefault("released", time.perf_counter()))
+        return p
+
+    attt.lora_workspace_size(OnAccess(8000, make), attt.BF16)
+    done = time.perf_counter()
+    assert done - seen["released"] < 0.5 * (done - seen["read"])
+
+
+@pytest.mark.parametrize("call", [lambda p: attt.lora_workspace_size(p, attt.BF16), attt.lora_grad, attt.lora_forward,
+                                  lambda p: attt.lora_sgd_step(p, 0.1), attt.lora_hot_swap])
+def test_a_generator_has_no_length(call):
+    with pytest.raises(TypeError):
+        call(FULL for _ in range(1))

@@ -564,3 +564,27 @@ def test_lora_grad_column_tiles(attt, count):
         x, dy, A, B = (p[k].double() for k in ("x", "dy", "A", "B"))
         for got, want in ((p["dA"], 0.8 * (dy @ B).t() @ x), (p["dB"], 0.8 * dy.t() @ (x @ A.t()))):
             assert float((got.double() - want).norm() / want.norm()) < 1e-5
+
+
+def test_lora_grad_of_temporaries(attt):
+    """Problems made on access, whose tensors only the call holds: its workspace is not laid over them.
+    Bitwise the gradients of the same problems kept by the caller."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(19)
+    rows, d, r = 1000, 512, 16
+    src = [{k: torch.randn(s, generator=g, device="cuda").bfloat16() for k, s in
+            (("x", (rows, d)), ("dy", (rows, d)), ("A", (r, d)), ("B", (d, r)))} for _ in range(4)]
+    outs = [[dict(dA=torch.zeros(r, d, device="cuda"), dB=torch.zeros(d, r, device="cuda")) for _ in src] for _ in range(2)]
+
+    class OnAccess:
+        def __len__(self):
+            return len(src)
+
+        def __getitem__(self, i):
+            return dict({k: t.clone() for k, t in src[i].items()}, scale=0.5, **outs[0][i])
+
+    attt.lora_grad(OnAccess())
+    attt.lora_grad([dict(s, scale=0.5, **o) for s, o in zip(src, outs[1])])
+    for a, b in zip(*outs):
+        assert torch.equal(a["dA"], b["dA"]) and torch.equal(a["dB"], b["dB"]) and a["dB"].any()
