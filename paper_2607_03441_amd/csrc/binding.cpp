@@ -90,6 +90,17 @@ float scale_of(Held& held, PyObject* map) {
   return (float)v;
 }
 
+// The library plans, launches and, the first time, loads its code: other Python threads run meanwhile. The
+// tensors stay held, and nothing of Python is touched.
+template <class F>
+auto without_gil(F f) {
+  struct Released {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Released() { PyEval_RestoreThread(state); }
+  } released;
+  return f();
+}
+
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 std::vector<attt_lora_problem> lora_problems(Held& held, PyObject* seq, bool check, at::ScalarType* dt, at::Device* dev) {
@@ -120,7 +131,7 @@ PyObject* lora_workspace_size(PyObject* args) {
   if (!PyArg_ParseTuple(args, "Oi", &seq, &dtype)) throw PyError{};
   const auto v = lora_problems(held, seq, false, nullptr, nullptr);
   size_t need = 0;
-  const attt_status st = attt_lora_workspace_size(v.data(), (int32_t)v.size(), dtype, &need);
+  const attt_status st = without_gil([&] { return attt_lora_workspace_size(v.data(), (int32_t)v.size(), dtype, &need); });
   return Py_BuildValue("in", (int)st, (Py_ssize_t)need);
 }
 
@@ -137,13 +148,16 @@ PyObject* lora_grad(PyObject* args) {
     raise(PyExc_TypeError, "unsupported dtype torch.%s (float32 or bfloat16)", c10::toString(dt));
   const int32_t dtype = dt == at::kBFloat16 ? ATTT_BF16 : ATTT_F32;
   size_t need = 0;
-  attt_status st = attt_lora_workspace_size(v.data(), (int32_t)v.size(), dtype, &need);
+  attt_status st = without_gil([&] { return attt_lora_workspace_size(v.data(), (int32_t)v.size(), dtype, &need); });
   if (st) return PyLong_FromLong(st);
   at::Tensor ws;
   if (ws_obj != Py_None) ws = tensor(ws_obj, "workspace");
-  if (!ws.defined() || ws.numel() < (int64_t)need)
-    ws = at::empty({(int64_t)(need > 256 ? need : 256)}, at::TensorOptions().dtype(at::kByte).device(dev));
-  st = attt_lora_grad(v.data(), (int32_t)v.size(), dtype, ws.data_ptr(), (size_t)ws.numel(), stream());
+  void* s = stream();
+  st = without_gil([&] {
+    if (!ws.defined() || ws.numel() < (int64_t)need)
+      ws = at::empty({(int64_t)(need > 256 ? need : 256)}, at::TensorOptions().dtype(at::kByte).device(dev));
+    return attt_lora_grad(v.data(), (int32_t)v.size(), dtype, ws.data_ptr(), (size_t)ws.numel(), s);
+  });
   return PyLong_FromLong(st);
 }
 
@@ -172,7 +186,8 @@ PyObject* lora_sgd_step(PyObject* args) {
     }
     v[i] = {static_cast<float*>(P.data_ptr()), static_cast<float*>(G.data_ptr()), copy, P.numel()};
   }
-  return PyLong_FromLong(attt_lora_sgd_step(v.data(), (int32_t)n, (float)lr, zero, stream()));
+  void* s = stream();
+  return PyLong_FromLong(without_gil([&] { return attt_lora_sgd_step(v.data(), (int32_t)n, (float)lr, zero, s); }));
 }
 
 // lora_forward(problems) -> status
@@ -194,7 +209,8 @@ PyObject* lora_forward(PyObject* args) {
     v[i] = {x.data_ptr(), y.data_ptr(), A.data_ptr(), B.data_ptr(), x.size(0), x.size(1), y.size(1), (int32_t)A.size(0),
             scale_of(held, p)};
   }
-  return PyLong_FromLong(attt_lora_forward(v.data(), (int32_t)n, stream()));
+  void* s = stream();
+  return PyLong_FromLong(without_gil([&] { return attt_lora_forward(v.data(), (int32_t)n, s); }));
 }
 
 // lora_hot_swap(pairs) -> status
@@ -214,7 +230,8 @@ PyObject* lora_hot_swap(PyObject* args) {
       raise(PyExc_ValueError, "src must be float32 and dst bfloat16 of the same numel");
     v[i] = {static_cast<const float*>(src.data_ptr()), dst.data_ptr(), src.numel()};
   }
-  return PyLong_FromLong(attt_lora_hot_swap(v.data(), (int32_t)n, stream()));
+  void* s = stream();
+  return PyLong_FromLong(without_gil([&] { return attt_lora_hot_swap(v.data(), (int32_t)n, s); }));
 }
 
 // No C++ exception leaves a module function.

@@ -94,3 +94,29 @@ def test_problems_live_until_the_call_returns():
 def test_a_generator_has_no_length(call):
     with pytest.raises(TypeError):
         call(FULL for _ in range(1))
+
+
+def test_other_threads_run_during_a_call():
+    """8000 problems of their own: the library plans them for longer than the marshalling takes, and a
+    second Python thread gets to run meanwhile."""
+    import threading
+    import time
+    big = dict(FULL, A=torch.zeros(64, 8), B=torch.zeros(8, 64))
+    problems, ticks, stop = [big] * 8000, [], threading.Event()
+
+    def tick():
+        while not stop.is_set():
+            ticks.append(time.perf_counter())
+            time.sleep(0.001)
+
+    t = threading.Thread(target=tick)
+    t.start()
+    while len(ticks) < 5:
+        time.sleep(0.001)
+    begin = time.perf_counter()
+    attt.lora_workspace_size(problems, attt.BF16)
+    end = time.perf_counter()
+    stop.set()
+    t.join()
+    at = [begin] + [x for x in ticks if begin < x < end] + [end]
+    assert max(b - a for a, b in zip(at, at[1:])) < 0.5 * (end - begin)
