@@ -5,11 +5,11 @@
 #include <Python.h>
 
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ops/empty.h>
 
-#include <exception>
 #include <vector>
 
 #include "attt.h"
@@ -234,18 +234,17 @@ PyObject* lora_hot_swap(PyObject* args) {
   return PyLong_FromLong(without_gil([&] { return attt_lora_hot_swap(v.data(), (int32_t)n, s); }));
 }
 
-// No C++ exception leaves a module function.
+// No C++ exception leaves a module function; torch's become the Python errors they are elsewhere (its
+// OutOfMemoryError among them).
 template <PyObject* (*Fn)(PyObject*)>
 PyObject* guarded(PyObject*, PyObject* args) {
+  HANDLE_TH_ERRORS
   try {
     return Fn(args);
   } catch (const PyError&) {
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-  } catch (...) {
-    PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
+    return nullptr;
   }
-  return nullptr;
+  END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef kMethods[] = {{"lora_workspace_size", guarded<lora_workspace_size>, METH_VARARGS, nullptr},

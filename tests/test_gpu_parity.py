@@ -588,3 +588,18 @@ def test_lora_grad_of_temporaries(attt):
     attt.lora_grad([dict(s, scale=0.5, **o) for s, o in zip(src, outs[1])])
     for a, b in zip(*outs):
         assert torch.equal(a["dA"], b["dA"]) and torch.equal(a["dB"], b["dB"]) and a["dB"].any()
+
+
+def test_lora_grad_without_memory_for_its_workspace(attt):
+    """A workspace that torch cannot allocate is torch's OutOfMemoryError."""
+    import torch
+    t = torch.zeros(128, 4096, dtype=torch.bfloat16, device="cuda")
+    A, B = t[:64], torch.zeros(4096, 64, dtype=torch.bfloat16, device="cuda")
+    p = dict(x=t, dy=t, A=A, B=B, dA=torch.zeros(64, 4096, device="cuda"), dB=torch.zeros(4096, 64, device="cuda"), scale=1.0)
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(0.001)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            attt.lora_grad([p] * 600)  # 1.5 GB
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
