@@ -286,11 +286,15 @@ __global__ __launch_bounds__(256) void ce_fwd_f32_kernel(const float* __restrict
   for (int r = 0; r < 16; ++r) {
     const int v = vb + mfma_row(r, lane);
     if (v < V) {
-      if (mx != -INFINITY) s += expf(acc[r] - mx);
+      if (mx != -INFINITY)
+        s += expf(acc[r] - mx);
+      else if (acc[r] != acc[r])
+        s = acc[r];
       if (v == y) label_logit[row] = acc[r];
     }
   }
   s += __shfl_xor(s, 32, 64);
+  if (s != s) mx = s;  // the maxima and merges pass NaNs over: without a finite logit beside it, one would be lost
   if (lane < 32) {
     red[0][wm][tl] = mx;
     red[1][wm][tl] = s;

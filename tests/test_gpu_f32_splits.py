@@ -49,3 +49,35 @@ def test_lora_f32_remainders(attt, rows, d_in, d_out, ranks):
     attt.lora_grad(probs)
     for p, (dA, dB) in zip(probs, refs):
         assert rel_norm(host(p["dA"]), dA) <= TOL and rel_norm(host(p["dB"]), dB) <= TOL
+
+
+@pytest.mark.parametrize("V", [1, 33, 64, 65, 97, 128, 161])
+@pytest.mark.parametrize("bad", ["nan", "-inf", "mixed", "inf"])
+def test_ce_f32_head_rows_not_finite(attt, V, bad):
+    """Non-finite logits in the last head row, in its whole block of 32 and in all of them: a NaN or +inf
+    logit makes the loss, lse and dH of every token NaN; -inf logits have probability 0. (lse within the
+    float32 bar of this file.)"""
+    import torch
+    note(f"ce f32 V={V} {bad}")
+    N, d = 5, 8
+    g = torch.Generator()
+    g.manual_seed(V)
+    # positive hidden states and one head entry of 1 in the rows' column 0: the logit is h_0 times that entry
+    h = torch.rand(N, d, generator=g) + 0.5
+    labels, w = torch.zeros(N, dtype=torch.int32), torch.ones(N)
+    for first in sorted({V - 1, (V - 1) // 32 * 32, 0}):
+        W = torch.randn(V, d, generator=g) * 0.1
+        W[first:] = 0.0
+        W[first:, 0] = float(bad) if bad != "mixed" else float("-inf")
+        if bad == "mixed":
+            W[V - 1, 0] = float("nan")
+        for grad in (False, True):
+            loss, lse, dH = attt.weighted_ce_fwd_bwd(h.cuda(), W.cuda(), labels.cuda(), w.cuda(), want_grad=grad)
+            if bad == "-inf":
+                z = h.double() @ torch.where(torch.isinf(W), 0.0, W).double().t()
+                z[:, first:] = float("-inf")
+                assert torch.allclose(lse.cpu().double(), torch.logsumexp(z, 1), rtol=TOL, atol=TOL)
+                assert torch.isnan(loss).all() == (first == 0)  # the label's logit is -inf too
+            else:
+                assert torch.isnan(loss).all() and torch.isnan(lse).all(), (first, loss, lse)
+                assert dH is None or torch.isnan(dH).any(1).all()
