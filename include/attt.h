@@ -141,8 +141,11 @@ attt_status attt_attention_bwd(const void* q, const void* k, const void* v, cons
 
 /* attt_attention_bwd with a workspace for partial dK and dV: where one workgroup per key block would
  * leave most of the chip idle (few rows or few key/value heads), several walk parts of its queries
- * and their float32 sums are added in a fixed order. Size 0: the shape is not split, and the call is
- * attt_attention_bwd. ATTT_ENOSPACE for a workspace that is too small; 256-byte aligned. */
+ * and their float32 sums are added in a fixed order. The size is at most
+ * ATTT_ATTENTION_MAX_WORKSPACE_BYTES; 0: the shape is not split, and the call is attt_attention_bwd,
+ * which is also the call to make where there is no memory for a workspace. ATTT_ENOSPACE for a
+ * workspace that is too small; 256-byte aligned. */
+#define ATTT_ATTENTION_MAX_WORKSPACE_BYTES ((size_t)256 << 20)
 attt_status attt_attention_workspace_size(const int64_t* row_offsets, int32_t num_episodes, int64_t N,
                                           int32_t heads, int32_t kv_heads, int32_t head_dim, size_t* bytes);
 attt_status attt_attention_bwd_split(const void* q, const void* k, const void* v, const void* dout,

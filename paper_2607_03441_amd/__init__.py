@@ -261,7 +261,8 @@ def attention_bwd(q, k, v, dout, row_offsets=None, scale=None, out=None, workspa
 
     q, dout: device bf16 [N, heads, 128]; k, v: [N, kv_heads, 128]; row_offsets: host int64
     episode offsets or None; scale defaults to 1/sqrt(128). lse, dsum: float32 [heads, N].
-    workspace: uint8 tensor of attention_workspace_size bytes (allocated here when not given)."""
+    workspace: uint8 tensor of attention_workspace_size bytes (at most 256 MiB; allocated here when not
+    given, and done without where there is no memory for it)."""
     torch = _torch()
     L = load()
     for t, name in ((q, "q"), (k, "k"), (v, "v"), (dout, "dout")):
@@ -283,10 +284,18 @@ def attention_bwd(q, k, v, dout, row_offsets=None, scale=None, out=None, workspa
         E = len(oo) - 1
     need = ctypes.c_size_t()
     _check(L.attt_attention_workspace_size(op, E, N, H, Hkv, dh, ctypes.byref(need)))
-    ws = _workspace(need.value, q.device, workspace) if need.value else None
-    _check(L.attt_attention_bwd_split(_dptr(q), _dptr(k), _dptr(v), _dptr(dout), op, E, N, H, Hkv, dh, scale,
-                                      _dptr(dq), _dptr(dk), _dptr(dv), _dptr(lse), _dptr(dsum), _dptr(ws),
-                                      ws.numel() if ws is not None else 0, _stream_ptr()))
+    args = (_dptr(q), _dptr(k), _dptr(v), _dptr(dout), op, E, N, H, Hkv, dh, scale, _dptr(dq), _dptr(dk), _dptr(dv),
+            _dptr(lse), _dptr(dsum))
+    ws = None
+    if need.value:
+        try:
+            ws = _workspace(need.value, q.device, workspace)
+        except torch.OutOfMemoryError:
+            pass
+    if ws is not None:
+        _check(L.attt_attention_bwd_split(*args, _dptr(ws), ws.numel(), _stream_ptr()))
+    else:
+        _check(L.attt_attention_bwd(*args, _stream_ptr()))
     return dq, dk, dv, lse, dsum
 
 

@@ -18,6 +18,7 @@
 
 using namespace attt;
 
+static_assert(kAttnMaxParts * kAttnPartBytes == ATTT_ATTENTION_MAX_WORKSPACE_BYTES, "header and library agree on the bound");
 static_assert(kNgramScratchBytes == ATTT_NGRAM_NOALLOC_SCRATCH_BYTES, "header and library agree on the scratch size");
 
 // ------------------------------------------------------------------------------------------
@@ -444,6 +445,9 @@ AttnSplit attn_split(const int64_t* off, int32_t E, int32_t heads, int32_t kv_he
     whole *= kv_heads;
     total *= kv_heads;
     const int32_t splits = (int32_t)ceil_div(longest, chunk);
+    // Every block has a slot for each piece of the longest walk. Beyond the bound blocks are many, and walks
+    // cut into more pieces than it allows would gain a tenth at most.
+    if (splits > 1 && blocks * kv_heads * splits > (int64_t)kAttnMaxParts) return;
     if (splits > 1 && chunk % (2 * g) != 0 && wgs > 256) return;
     const int64_t rounds = splits > 1 ? whole / 256 : 0;
     const double tail = std::max((double)(whole > rounds * 256 ? chunk : 0),

@@ -168,6 +168,7 @@ struct AttnEp {
 };
 constexpr int kAttnKeyBlock = 128;  // keys per block of a split dK / dV walk
 constexpr size_t kAttnPartBytes = 2 * kAttnKeyBlock * 128 * sizeof(float);  // one partial dK, dV of a block
+constexpr size_t kAttnMaxParts = 2048;  // partials a split plan may hold: 256 MiB, eight a CU
 struct AttnBatch {
   int32_t count;
   // dK / dV: keys per block / 64; workgroups per key block, each over `chunk` (query block, query head)

@@ -370,6 +370,23 @@ def test_attention_split_validation(L):
     assert call(ctypes.c_void_p(0x7F0000000010), need.value) == attt.EINVAL  # misaligned
 
 
+def test_attention_workspace_is_bounded(L):
+    """Long walks on few key/value heads, one long episode among short ones, batches of ragged ones: at
+    most 256 MiB of partial sums, whatever the rows."""
+    rng = np.random.default_rng(3)
+    shapes = [([n], h, k) for n in (8192, 20000, 65536, 100000, 131072, 200000, 260000, 1 << 20)
+              for h, k in ((4, 1), (8, 1), (16, 2), (64, 8)) if n * h < 1 << 31]
+    shapes += [([40000] + [64] * m, 8, 1) for m in (1, 62, 63, 64, 300)]
+    shapes += [(rng.integers(1, 20000, e).tolist(), 8, 2) for e in (2, 17, 70)]
+    most = 0
+    for lens, h, k in shapes:
+        off = np.concatenate([[0], np.cumsum(lens)])
+        need = attt.attention_workspace_size(int(off[-1]), h, k, off)
+        assert need <= 256 << 20, (lens[:3], h, k, need)
+        most = max(most, need)
+    assert most > 64 << 20
+
+
 def _fwd(L, count=1, **kw):
     p = dict(x=FAKE, y=FAKE_WS, A=FAKE, B=FAKE_WS, rows=32, d_in=64, d_out=64, rank=8, scale=2.0)
     p.update(kw)

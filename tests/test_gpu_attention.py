@@ -132,6 +132,23 @@ def _no_workspace(attt, q, k, v, do, off):
     return out
 
 
+def test_no_memory_for_the_workspace(attt):
+    """Where the workspace cannot be allocated the block runs unsplit: bitwise attt_attention_bwd's result."""
+    import torch
+    off = np.array([0, 2048], np.int64)
+    q, k, v, do = (dev_dense(t) for t in _inputs(2048, 8, 2, 85))
+    assert attt.attention_workspace_size(2048, 8, 2, off) > 20 << 20  # no cached block holds it
+    want = _no_workspace(attt, q, k, v, do, off)
+    out = tuple(torch.empty_like(t) for t in want)
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-9)
+    try:
+        attt.attention_bwd(q, k, v, do, off, out=out)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
 @pytest.mark.parametrize("lens,H,Hkv", [([1, 64, 65, 127, 128, 129], 4, 2), ([700], 8, 1), ([257, 1100, 1, 383], 8, 2),
                                         ([1024], 16, 1), ([33 * 64], 8, 8), ([3000, 64, 2000], 8, 4)])
 def test_split_walks(attt, lens, H, Hkv):
