@@ -402,78 +402,97 @@ attt_status ngram_run(const NgramPlan& P, const int32_t* history, const int32_t*
 // Attention-block backward
 // ------------------------------------------------------------------------------------------
 namespace {
-// How the dK / dV kernel's workgroups of one launch batch take its key blocks.
+// How the dK / dV kernels' workgroups of one launch batch take its key blocks.
 struct AttnSplit {
-  int32_t tiles = 2, splits = 1, chunk = INT32_MAX;
+  int32_t tiles = 0, splits = 1, chunk = INT32_MAX;
   size_t bytes = 0;
 };
 
-// A key block's workgroup walks heads / kv_heads steps for each 64-query block at or after it. One
-// workgroup per block leaves the chip idle where there are few of them or where the first block's walk
-// is much longer than the average; blocks of 64 keys make twice the workgroups and shorter steps, and
-// (`may_split`) cutting every walk of 128 keys into pieces of `chunk` steps bounds the longest at the
-// price of a float32 partial per piece. The choice is the shortest by this estimate in microseconds: a
-// step takes 1.86 (64 keys) or 2.63 (128) alone on its CU and 2.3 or 3.0 where a CU has more than one
-// workgroup to do; whole pieces run in rounds of 256, and the rests of the walks fill the last (a
-// quarter of a piece short of even); partials take 15 and 0.05 a workgroup. Measured, one walk of 64 /
-// of 128 keys / the best split / the choice: 2048 rows, 16 heads over 4: 249 / 340 / 76 / 76 us;
-// 4096, 8 over 2: 464 / 666 / 125 / 125; 4096, 32 over 8: 552 / 667 / 420 / 466; 8 episodes of 2000
-// rows in all, 8 over 8: 21 / 28 / 30 / 22; 8192, 32 over 8: 2066 / 1509 / 1509 / 1509.
+// A key block's workgroup walks heads / kv_heads steps for each 64-query block at or after it. Walks are
+// taken whole by one of three kernels (tiles 0: two small workgroups per CU; 1 and 2: 64 or 128 keys with the
+// CU to themselves), or (`may_split`) those of 128 keys are cut into pieces of `chunk` steps at the price of
+// a float32 partial per piece. The choice is the shortest by these estimates in microseconds: a CU's share of
+// the steps and of the workgroups' starts and ends, behind it parts of the longest walk and of the longest that
+// starts late (in the second half of the episodes); but no less than that walk alone, or than the rounds of
+// whole pieces; and each partial is written and read. Pieces that all run at once take the time of one.
+// The constants are fitted to 394 shapes (1-200 episodes of 20-131072 rows, 1-64 heads; rms errors 5-6%),
+// over which the choice takes 1.016 times the best candidate's time on average and at most 1.08 times that of
+// tiles 0, which was the only kernel before. Tiles 0 / 1 / 2 / best pieces / the choice, in us: 2048 rows, 16 heads over 4:
+// 279 / 237 / 336 / 76 / 76; 4096, 32 over 8: 572 / 508 / 660 / 394 / 394; 64 episodes of 64, 32 over 32: 46 / 70 / 87 / - /
+// 46; 2 of 1500, 40 over 8: 279 / 231 / 322 / 179 / 179; 8192, 32 over 8: 1660 / 1968 / 1442 / 1436 / 1442; 18 of up to 2210,
+// 4 over 4: 322 / 399 / 336 / - / 322.
+struct AttnCost {
+  double base, alone, step, wg, longest, late, part;
+  double us(int64_t walk, int64_t late_walk, int64_t steps, int64_t wgs, int64_t rounds = 1) const {
+    return base + std::max(alone * walk * rounds, (step * steps + wg * wgs) / 256 + longest * walk + late * late_walk) + part * wgs;
+  }
+};
+constexpr AttnCost kAttnWalk[3] = {
+    {5.8, 2.17, 1.32, 3.0, 0.6, 0.7, 0}, {7.2, 1.8, 1.85, 5.4, 0.15, 0.54, 0}, {8.6, 2.56, 2.61, 6.1, 0.43, 0.78, 0}};
+constexpr AttnCost kAttnPieces = {9.9, 2.61, 2.705, 1.6, 0.37, 0.46, 0.049};
+constexpr AttnCost kAttnPiecesAtOnce = {12.4, 2.57, 0, 0, 0, 0, 0.042};  // at most one workgroup per CU
+
+// sum over i = 1 .. n of ceil(i / m)
+int64_t sum_ceil(int64_t n, int64_t m) { return m * (n / m) * (n / m + 1) / 2 + n % m * (n / m + 1); }
+
 AttnSplit attn_split(const int64_t* off, int32_t E, int32_t heads, int32_t kv_heads, bool may_split) {
   const int64_t g = heads / kv_heads;
-  int64_t longest = 0, blocks = 0;
+  int64_t longest = 0, late = 0, blocks[3] = {}, steps[3] = {};  // of each kernel: key blocks and all their steps
   for (int32_t e = 0; e < E; ++e) {
-    const int64_t L = off[e + 1] - off[e];
-    longest = std::max(longest, g * ceil_div(L, 64));
-    blocks += ceil_div(L, kAttnKeyBlock);
+    const int64_t q = ceil_div(off[e + 1] - off[e], 64), k = ceil_div(q, 2);
+    longest = std::max(longest, g * q);
+    if (E > 1 && e >= E / 2) late = std::max(late, g * q);
+    blocks[0] += q;
+    steps[0] += g * (q * (q + 1) / 2);
+    blocks[2] += k;
+    steps[2] += g * (k * q - k * (k - 1));
   }
+  blocks[1] = blocks[0];
+  steps[1] = steps[0];
   AttnSplit best;
-  if (blocks * kv_heads >= 2048 || blocks == 0) return best;  // eight rounds of the chip: even as they are
   double best_us = 0.0;
-  auto consider = [&](int32_t tiles, int64_t chunk) {
-    int64_t wgs = 0, whole = 0, total = 0;
+  for (int32_t tiles = 0; tiles < 3; ++tiles) {
+    const double us = kAttnWalk[tiles].us(longest, late, steps[tiles] * kv_heads, blocks[tiles] * kv_heads);
+    if (tiles == 0 || us < best_us) best_us = us, best.tiles = tiles;
+  }
+  if (!may_split || blocks[2] == 0) return best;
+  auto consider = [&](int64_t chunk) {
+    // Every block has a slot for each piece of the longest walk. Beyond the bound blocks are many, and cutting
+    // their walks gains little: 65536 rows of 8 heads over 1 take 23.2 ms unsplit, 22.5 in 24 pieces (1.6 GB).
+    const int64_t splits = ceil_div(longest, chunk);
+    if (splits < 2 || blocks[2] * kv_heads * splits > (int64_t)kAttnMaxParts) return;
+    const bool even = chunk % (2 * g) == 0;
+    if (!even && blocks[2] * kv_heads > 256) return;  // uneven pieces run in one round only
+    int64_t wgs = 0, whole = 0;
     for (int32_t e = 0; e < E; ++e) {
-      const int64_t nqb = ceil_div(off[e + 1] - off[e], 64);
-      for (int64_t q = 0; q < nqb; q += tiles) {
-        const int64_t steps = g * (nqb - q);
-        wgs += ceil_div(steps, chunk);
-        whole += steps / chunk;
-        total += steps;
+      const int64_t q = ceil_div(off[e + 1] - off[e], 64), k = ceil_div(q, 2), m = chunk / (2 * g);
+      if (even) {  // walks of g q, g (q - 2), ... steps: the last of g or 2 g
+        wgs += sum_ceil(k, m);
+        whole += sum_ceil(k, m) - k + (q % 2 ? 0 : k / m);
+      } else {
+        for (int64_t i = q; i > 0; i -= 2) wgs += ceil_div(g * i, chunk);
       }
     }
     wgs *= kv_heads;
     whole *= kv_heads;
-    total *= kv_heads;
-    const int32_t splits = (int32_t)ceil_div(longest, chunk);
-    // Every block has a slot for each piece of the longest walk. Beyond the bound blocks are many, and walks
-    // cut into more pieces than it allows would gain a tenth at most.
-    if (splits > 1 && blocks * kv_heads * splits > (int64_t)kAttnMaxParts) return;
-    if (splits > 1 && chunk % (2 * g) != 0 && wgs > 256) return;
-    const int64_t rounds = splits > 1 ? whole / 256 : 0;
-    const double tail = std::max((double)(whole > rounds * 256 ? chunk : 0),
-                                 (double)(total - rounds * 256 * chunk) / 256);
-    double us = (double)(rounds * chunk) + tail;
-    if (splits == 1) us = std::max((double)longest, (double)total / 256 + (double)longest / 16);
-    else if (wgs > 256) us += (double)chunk / 4;
-    us *= wgs <= 256 ? (tiles == 1 ? 1.86 : 2.63) : (tiles == 1 ? 2.3 : 3.0);
-    if (splits > 1) us += 15 + 0.05 * (double)wgs;
-    if (best_us == 0.0 || us < best_us) {
+    if (!even && wgs > 256) return;
+    // more than one round is the less certain estimate, and its workspace is larger: a margin of a tenth
+    const double us = wgs <= 256 ? kAttnPiecesAtOnce.us(chunk, 0, 0, wgs)
+                                 : 1.1 * kAttnPieces.us(chunk, std::min(late, chunk), steps[2] * kv_heads, wgs, ceil_div(whole, 256));
+    if (us < best_us) {
       best_us = us;
-      best.tiles = tiles;
-      best.splits = splits;
-      best.chunk = splits == 1 ? INT32_MAX : (int32_t)chunk;
+      best.tiles = 2;
+      best.splits = (int32_t)splits;
+      best.chunk = (int32_t)chunk;
     }
   };
-  consider(2, longest);
-  consider(1, longest);
-  if (may_split)
-    for (int32_t k : {2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24}) {
-      const int64_t chunk = ceil_div(longest, k), even = ceil_div(chunk, 2 * g) * 2 * g;
-      if (chunk < 3) break;
-      if (even < longest) consider(2, even);
-      if (even != chunk) consider(2, chunk);  // in one round only
-    }
-  if (best.splits > 1) best.bytes = (size_t)blocks * kv_heads * best.splits * kAttnPartBytes;
+  for (int32_t k : {2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24}) {
+    const int64_t chunk = ceil_div(longest, k), even = ceil_div(chunk, 2 * g) * 2 * g;
+    if (chunk < 3) break;
+    consider(even);
+    if (even != chunk) consider(chunk);
+  }
+  if (best.splits > 1) best.bytes = (size_t)blocks[2] * kv_heads * best.splits * kAttnPartBytes;
   return best;
 }
 

@@ -12,9 +12,11 @@
 //   attn_dkdv_kernel       per (key/value head, 64- or 128-key block, part of its queries): dK and dV
 //                          accumulated in registers over every query head of the group and every
 //                          later query block, in a fixed order (no atomics), 512 threads
+//   attn_dkdv_short_kernel the same for a 64-key block with half the threads and LDS, where walks are short
 //   attn_dq_kernel         per (query head, 64- or 128-query block): dQ over the allowed key blocks
-// The operand that stays in a wave (its 16 queries, or its 16 keys) is held in registers as
-// the B operand of the score products, so each lane ends up with 16 scores of its own row. The
+// The operand that stays (a wave's 16 or 32 queries, or its keys) is held in registers, or for
+// attn_dkdv_kernel in LDS, as the B operand of the score products, so each lane ends up with scores of its
+// own rows. The
 // probabilities (or dS) of that row then enter the second product (P^T dO, dS^T Q, dS K)
 // directly as the A operand: the contraction index is the one the lane's registers run over,
 // in the order they hold it, and the B operand is read in the same order from the row-major LDS
@@ -526,6 +528,143 @@ __global__ __launch_bounds__(512, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch
     }
 }
 
+// dK, dV of one (key/value head, 64-key block) by four waves and 68 KiB of LDS, so that two workgroups share
+// a CU and one's start and end run under the other's steps: for walks that are short, or many and even. Wave
+// w owns keys 16 w .. 16 w + 15; their K and V fragments stay in registers. Per query block: S = Q K^T and dP = dO V^T with the queries on
+// the MFMA rows (four tiles of 16) and this wave's keys on the columns, so each lane holds 16
+// (query, key) values of its own key. P and dS = P (dP - D) then feed dV += P^T dO and
+// dK += dS^T Q straight from those registers as the A operand: the contraction runs over the
+// queries, and the 8 values a lane holds per 32-query chunk (tile rows 4 q4 .. +3 of two tiles)
+// are its k slots; the B operand reads the transposed dO and Q tiles in the same query order.
+// A step takes a CU 1.36 us (1.34 per 64 keys of the 128-key kernel) and a workgroup's start and end 3.6
+// (6.5): 64 episodes of 64 rows, 32 heads over 32: 46 us against 70 and 87 for the kernel above on 64 and on
+// 128 keys; 3 episodes of 1000 rows, 40 over 40: 124, 159 and 127; 8192 rows, 32 over 8: 1726 against 1509.
+__global__ __launch_bounds__(256, 2) void attn_dkdv_short_kernel(AttnArgs a, AttnBatch b) {
+  int ei, kh, kb;
+  attn_locate(b, a.kv_heads, false, ei, kh, kb);
+  const AttnEp E = b.e[ei];
+  const int g = a.heads / a.kv_heads;
+  const int k0 = kb * BLK, nk = min(BLK, E.L - k0);
+  extern __shared__ __align__(16) uint8_t smem[];  // two buffers of [Q tile][dO tile][lse][D]
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l16 = lane & 15, q4 = lane >> 4;
+  const int key = 16 * w + l16;  // this lane's key in the block
+  const int64_t qs = (int64_t)a.heads * DH, ks = (int64_t)a.kv_heads * DH;
+  bf16x8 kf[4], vf[4];
+  load_key_frags(kf, a.k + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
+  load_key_frags(vf, a.v + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
+  f32x4 dk[8], dv[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) dk[j] = f32x4{0, 0, 0, 0}, dv[j] = f32x4{0, 0, 0, 0};
+  const float sl = a.scale * kLog2e;
+  const int nqb = (E.L + BLK - 1) / BLK;
+  // (query block, query head) steps: query blocks from the last down to kb, the group's query
+  // heads inside. Every workgroup of a key/value head walks the same blocks in the same order
+  // (starting at the last, stopping at its own key block), so those running together on an XCD
+  // read each Q and dO block from its L2.
+  const int steps = g * (nqb - kb);
+  u32x4 fq[4], fo[4];
+  float fl = INFINITY, fd = 0.0f;
+  auto fetch = [&](int i) {
+    const int h = kh * g + i % g, q0 = (nqb - 1 - i / g) * BLK, nq = min(BLK, E.L - q0);
+    fetch_block(fq, a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, nq, tid);
+    fetch_block(fo, a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, nq, tid);
+    if (tid < BLK) {
+      const int64_t t = (int64_t)h * a.N + E.row0 + q0 + tid;
+      fl = tid < nq ? a.lse[t] * kLog2e : INFINITY;  // absent rows: P = 0
+      fd = tid < nq ? a.dsum[t] : 0.0f;
+    }
+  };
+  auto stage = [&](int buf) {
+    store_block(fq, qo_tile(smem, buf, 0), tid);
+    store_block(fo, qo_tile(smem, buf, 1), tid);
+    if (tid < BLK) qo_stats(smem, buf)[tid] = fl, qo_stats(smem, buf)[BLK + tid] = fd;
+  };
+  fetch(0);
+  stage(0);
+  for (int i = 0; i < steps; ++i) {
+    const int q0 = (nqb - 1 - i / g) * BLK;
+    // This step's tiles are stored, and every wave is done with the other buffer.
+    __syncthreads();
+    if (i + 1 < steps) fetch(i + 1);  // the next step's blocks load while this one computes
+    const bf16_t* Qs = qo_tile(smem, i & 1, 0);
+    const bf16_t* dOs = qo_tile(smem, i & 1, 1);
+    const float* lse_s = qo_stats(smem, i & 1);
+    const float* d_s = lse_s + BLK;
+    {
+      // S[16 t + 4 q4 + r][key] and dP likewise
+      f32x4 st[4], dp[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) st[t] = f32x4{0, 0, 0, 0}, dp[t] = f32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const bf16x8 aq = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const u32x4*>(Qs + (16 * t + l16) * PR + 32 * s4 + 8 * q4));
+          const bf16x8 ao = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const u32x4*>(dOs + (16 * t + l16) * PR + 32 * s4 + 8 * q4));
+          st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, kf[s4], st[t], 0, 0, 0);
+          dp[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ao, vf[s4], dp[t], 0, 0, 0);
+        }
+      // P and dS of this lane's 16 (query, key) pairs, in fragment order: chunk u, slot i is
+      // query 32 u + 4 q4 + i (i < 4) or 32 u + 16 + 4 q4 + i - 4. A query block after the key
+      // block sees every key, and the key block is then not the last, so it is whole: no mask.
+      float pv[2][8], dsv[2][8];
+      auto probs = [&](auto masked) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const f32x4 ls = *reinterpret_cast<const f32x4*>(lse_s + 16 * t + 4 * q4);
+          const f32x4 dd = *reinterpret_cast<const f32x4*>(d_s + 16 * t + 4 * q4);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int ql = 16 * t + 4 * q4 + r;
+            float p = __builtin_amdgcn_exp2f(st[t][r] * sl - ls[r]);
+            if constexpr (decltype(masked)::value) p = (k0 + key <= q0 + ql && key < nk) ? p : 0.0f;
+            pv[t >> 1][4 * (t & 1) + r] = p;
+            dsv[t >> 1][4 * (t & 1) + r] = p * (dp[t][r] - dd[r]);
+          }
+        }
+      };
+      if (q0 > k0)
+        probs(std::false_type{});
+      else
+        probs(std::true_type{});
+      bf16x8 ph[2], pl[2], sh[2], slo[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        split_frag(pv[u], ph[u], pl[u]);
+        split_frag(dsv[u], sh[u], slo[u]);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const bf16x8 bo = trfrag(dOs, 16 * j, u, lane);
+          dv[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph[u], bo, dv[j], 0, 0, 0);
+          dv[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[u], bo, dv[j], 0, 0, 0);
+          const bf16x8 bq = trfrag(Qs, 16 * j, u, lane);
+          dk[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sh[u], bq, dk[j], 0, 0, 0);
+          dk[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(slo[u], bq, dk[j], 0, 0, 0);
+        }
+    }
+    if (i + 1 < steps) stage((i + 1) & 1);
+  }
+  // D of dV / dK tile j: lane (l16, q4), register r -> key 16 w + 4 q4 + r, column 16 j + l16
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int kr = 16 * w + 4 * q4 + r;
+    if (kr >= nk) continue;
+    bf16_t* dkr = a.dk + ((int64_t)(E.row0 + k0 + kr) * a.kv_heads + kh) * DH;
+    bf16_t* dvr = a.dv + ((int64_t)(E.row0 + k0 + kr) * a.kv_heads + kh) * DH;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      dkr[16 * j + l16] = f2bf(dk[j][r] * a.scale);
+      dvr[16 * j + l16] = f2bf(dv[j][r]);
+    }
+  }
+}
+
 // Sums the float32 partials of a key block's step ranges in their order and rounds once. One thread per
 // 8 columns of a key's dK or dV row.
 __global__ __launch_bounds__(256) void attn_dkdv_reduce_kernel(AttnArgs a, AttnBatch b) {
@@ -693,16 +832,16 @@ static hipError_t set_lds(K kernel, bool& attr, size_t lds) {
   return e;
 }
 
-// A per-query kernel on blocks of `rows` queries.
+// A kernel whose 256-thread workgroups take blocks of `rows` queries or keys of one of `heads`.
 template <class K>
-static hipError_t launch_queries(K kernel, bool& attr, int rows, const AttnArgs& a, AttnBatch b, int id, hipStream_t s) {
-  constexpr size_t lds = 2 * (size_t)kKvBuf;
+static hipError_t launch_blocks(K kernel, bool& attr, int rows, int heads, size_t lds, const AttnArgs& a, AttnBatch b,
+                                int id, hipStream_t s) {
   if (hipError_t e = set_lds(kernel, attr, lds)) return e;
   int n = 0;
   for (int i = 0; i < b.count; ++i) {
     b.e[i].blocks = (b.e[i].L + rows - 1) / rows;
     b.e[i].wg_begin = n;
-    n += b.e[i].blocks * a.heads;
+    n += b.e[i].blocks * heads;
   }
   if (n <= 0) return hipSuccess;
   KernelTimer t(id, s);
@@ -735,8 +874,11 @@ static hipError_t launch_keys(bool& attr, const AttnArgs& a, AttnBatch b, hipStr
 }
 
 hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStream_t s) {
-  static bool attr[6] = {};
+  static bool attr[7] = {};
+  if (kernel == 1 && b.tiles == 0)
+    return launch_blocks(attn_dkdv_short_kernel, attr[6], BLK, a.kv_heads, 2 * (size_t)kQoBuf, a, b, K_ATTN_DKDV, s);
   if (kernel == 1) return b.tiles == 1 ? launch_keys<1>(attr[4], a, b, s) : launch_keys<2>(attr[5], a, b, s);
+  constexpr size_t lds = 2 * (size_t)kKvBuf;
   // Two query tiles per wave where their workgroups fill the chip's two per CU one and a half times; below
   // that the longest chain of key blocks is the time, and a step of one tile is the shorter one. Statistics
   // + dQ, one tile / two: 2048 rows x 16 heads (256 two-tile workgroups) 110 / 131 us, 4 episodes of 4096
@@ -745,10 +887,10 @@ hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStr
   for (int i = 0; i < b.count; ++i) n2 += (b.e[i].L + 127) / 128 * a.heads;
   const bool wide = n2 > 768;
   if (kernel == 0)
-    return wide ? launch_queries(attn_fwd_stats_kernel<2>, attr[0], 128, a, b, K_ATTN_FWD, s)
-                : launch_queries(attn_fwd_stats_kernel<1>, attr[1], 64, a, b, K_ATTN_FWD, s);
-  return wide ? launch_queries(attn_dq_kernel<2>, attr[2], 128, a, b, K_ATTN_DQ, s)
-              : launch_queries(attn_dq_kernel<1>, attr[3], 64, a, b, K_ATTN_DQ, s);
+    return wide ? launch_blocks(attn_fwd_stats_kernel<2>, attr[0], 128, a.heads, lds, a, b, K_ATTN_FWD, s)
+                : launch_blocks(attn_fwd_stats_kernel<1>, attr[1], 64, a.heads, lds, a, b, K_ATTN_FWD, s);
+  return wide ? launch_blocks(attn_dq_kernel<2>, attr[2], 128, a.heads, lds, a, b, K_ATTN_DQ, s)
+              : launch_blocks(attn_dq_kernel<1>, attr[3], 64, a.heads, lds, a, b, K_ATTN_DQ, s);
 }
 
 }  // namespace attt

@@ -171,8 +171,8 @@ constexpr size_t kAttnPartBytes = 2 * kAttnKeyBlock * 128 * sizeof(float);  // o
 constexpr size_t kAttnMaxParts = 2048;  // partials a split plan may hold: 256 MiB, eight a CU
 struct AttnBatch {
   int32_t count;
-  // dK / dV: keys per block / 64; workgroups per key block, each over `chunk` (query block, query head)
-  // steps; above one (128 keys) they write partials [block][kv head][split][2][128][128]
+  // dK / dV: keys per block / 64 (0: 64 keys in small workgroups); workgroups per key block, each over `chunk`
+  // (query block, query head) steps; above one (128 keys) they write partials [block][kv head][split][2][128][128]
   int32_t tiles, splits, chunk;
   float* part;
   AttnEp e[kEpBatch];

@@ -132,6 +132,18 @@ def _no_workspace(attt, q, k, v, do, off):
     return out
 
 
+@pytest.mark.parametrize("lens,H,Hkv", [([1, 63, 64, 65, 127, 128, 129, 200] * 9, 8, 8), ([30] * 70, 32, 4),
+                                        ([512, 300, 700] * 4, 32, 16)])
+def test_many_short_walks(attt, lens, H, Hkv):
+    """Batches whose walks are short run in small workgroups, two per CU (the first two choose them, the
+    last sits near the line): edges of the 64-row blocks, more episodes than one launch holds."""
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    N = int(off[-1])
+    note(f"attention short walks: {len(lens)} episodes, heads {H}/{Hkv}")
+    assert attt.attention_workspace_size(N, H, Hkv, off) == 0
+    _check_full(attt, N, H, Hkv, off, 91)
+
+
 def test_no_memory_for_the_workspace(attt):
     """Where the workspace cannot be allocated the block runs unsplit: bitwise attt_attention_bwd's result."""
     import torch
