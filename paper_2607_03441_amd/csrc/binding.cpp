@@ -48,6 +48,7 @@ struct Held {
 PyObject* list(Held& held, PyObject* seq) {
   const Py_ssize_t n = PyObject_Size(seq);
   if (n < 0) throw PyError{};
+  held.v.reserve(1 + 8 * (size_t)n);
   return held.keep(PySequence_Tuple(seq));
 }
 

@@ -39,11 +39,11 @@ constexpr int kSP = 144;                 // LDS pitch (bytes) of a staged row's 
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// A lane's SPL consecutive elements of a row of B, from byte offset `off`.
+// A lane's SPL consecutive elements of a row of B, from byte offset `off`; of 16, zero from `valid` on (8 or 16).
 template <int SPL>
 struct BRow {
   uint32_t w[(SPL + 1) / 2];
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off, int valid) {
     if constexpr (SPL == 2) {
       w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
     } else if constexpr (SPL == 4) {
@@ -52,7 +52,7 @@ struct BRow {
     } else {
 #pragma unroll
       for (int q = 0; q < SPL / 8; ++q) {
-        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off + 16u * q, 0, 0));
+        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, 8 * q < valid ? off + 16u * q : kOOBF, 0, 0));
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[4 * q + e] = v[e];
       }
@@ -60,39 +60,40 @@ struct BRow {
   }
   __device__ __forceinline__ float get(int i) const { return (i & 1) ? bf_hi(w[i >> 1]) : bf_lo(w[i >> 1]); }
 };
-// Any rank: element loads, zero past the lane's `n` elements.
+// Any rank: a lane's elements are k = g, g + 4, ... of the row, loaded one by one, zero from `rank` on.
+template <int SPL>
 struct BRowAny {
-  uint32_t w[8];
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off, int n) {
+  uint32_t w[(SPL + 1) / 2];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off, int g, int rank) {
+    auto one = [&](int i) {
+      return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, i < SPL && 4 * i + g < rank ? off + 2u * (4 * i + g) : kOOBF, 0, 0) & 0xFFFFu;
+    };
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(r, 2 * i < n ? off + 4u * i : kOOBF, 0, 0);
-      const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(r, 2 * i + 1 < n ? off + 4u * i + 2u : kOOBF, 0, 0);
-      w[i] = (lo & 0xFFFFu) | (hi << 16);
-    }
+    for (int i = 0; i < (SPL + 1) / 2; ++i) w[i] = SPL == 1 ? one(0) : one(2 * i) | (one(2 * i + 1) << 16);
   }
   __device__ __forceinline__ float get(int i) const { return (i & 1) ? bf_hi(w[i >> 1]) : bf_lo(w[i >> 1]); }
 };
 
 // Phase 2 of one projection: blocks first, first + stride, ... < nb of 64 columns from o_lo. Lane
-// (l16, g) holds row l16 of U and, for column tile q, column TQ l16 + q of B, at k = g SPL .. +SPL-1;
-// it ends up with columns TQ l16 .. + TQ - 1 of rows 4 g .. 4 g + 3. kDepth blocks have their loads in
+// (l16, g) holds row l16 of U and, for column tile q, column TQ l16 + q of B, at k = g SPL .. +SPL-1 (R = 0:
+// the rank is 4 SPL; R = 1: a multiple of min(SPL, 8) below it) or at k = g, g + 4, ... (R = 2: any); it ends up with columns TQ l16 .. + TQ - 1 of rows 4 g .. 4 g + 3. kDepth blocks have their loads in
 // flight.
-template <int SPL, bool kAny, int kDepth>
+template <int SPL, int R, int kDepth>
 __device__ __forceinline__ void add_columns(const LoraFwdOut& O, const float* Uf, int row0, int nrows, int o_lo,
                                             int o_hi, int first, int stride, int nb, int lane) {
   constexpr int TQ = 4;
   typedef uint32_t YVec __attribute__((ext_vector_type(2)));  // 4 bf16 of a row of y
   const int l16 = lane & 15, g = lane >> 4;
   const int d_out = O.d_out, rank = O.rank;
-  const int spl = kAny ? (rank + 3) / 4 : SPL;
   float u[SPL];
 #pragma unroll
-  for (int i = 0; i < SPL; ++i)
-    u[i] = !kAny || (i < spl && g * spl + i < rank) ? Uf[l16 * kUP + 16 * O.u0 + g * spl + i] : 0.0f;
+  for (int i = 0; i < SPL; ++i) {
+    const int k = R == 2 ? 4 * i + g : g * SPL + i;
+    u[i] = R == 0 || k < rank ? Uf[l16 * kUP + 16 * O.u0 + k] : 0.0f;
+  }
   const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(O.B, d_out * rank * 2);
   const __amdgpu_buffer_rsrc_t ry = buffer_rsrc(static_cast<bf16_t*>(O.y) + (int64_t)row0 * d_out, nrows * d_out * 2);
-  using Row = std::conditional_t<kAny, BRowAny, BRow<SPL>>;
+  using Row = std::conditional_t<R == 2, BRowAny<SPL>, BRow<SPL>>;
   YVec yv[kDepth][4];
   Row br[kDepth][TQ];
   // column of the lane's first element of y in a block, and its byte offset in row 4 g + v; rows at or
@@ -106,11 +107,11 @@ __device__ __forceinline__ void add_columns(const LoraFwdOut& O, const float* Uf
       yv[d][v] = __builtin_bit_cast(YVec, __builtin_amdgcn_raw_buffer_load_b64(ry, yoff(yc, v), 0, 0));
 #pragma unroll
     for (int q = 0; q < TQ; ++q) {
-      const uint32_t off = yc < o_hi ? (uint32_t)((yc + q) * rank + g * spl) * 2u : kOOBF;
-      if constexpr (kAny)
-        br[d][q].load(rb, off, yc < o_hi ? min(spl, rank - g * spl) : 0);
+      if constexpr (R == 2)
+        br[d][q].load(rb, (uint32_t)((yc + q) * rank) * 2u, g, yc < o_hi ? rank : 0);
       else
-        br[d][q].load(rb, off);
+        br[d][q].load(rb, yc < o_hi && (R == 0 || g * SPL < rank) ? (uint32_t)((yc + q) * rank + g * SPL) * 2u : kOOBF,
+                      R == 0 ? SPL : rank - g * SPL);
     }
   };
   // Loads past the last block fall outside the descriptors' ranges; they are issued all the same, so that
@@ -146,14 +147,22 @@ __device__ __forceinline__ void add_columns(const LoraFwdOut& O, const float* Uf
 }
 }  // namespace
 
-// Eight waves, blocks of 64 columns. kLight: every rank of the launch is 8 or 16, which keeps the
-// kernel at 100 registers (four waves per SIMD); the other ranks hold up to 16 k values per lane.
+template <int N>
+using I = std::integral_constant<int, N>;
+
+// W = 8 or 4 waves, blocks of 64 columns. Without kHigh every rank of the launch is at most 16, which keeps
+// the kernel at 99 registers (four waves per SIMD); higher ranks hold up to 16 k values per lane. kAny: ranks
+// other than 8, 16, 32 and 64 too. They take the products of the next of 4, 8, 16, 32 and 64, and 12 and the
+// multiples of 8 its loads. (In the products of 64, loaded one by one, rank 4 took 239 us at the prefill
+// below and rank 24 398, here 110 and 161; 187 and 500 with the kernel before.) Ranks of 32 and 64 alone need
+// 112 registers, but four waves per SIMD are one too many for them: 173 us at rank 32 there, 166 with three.
 // 16 x 512 rows of q, k, v and o (483 MB): 279 us with 64-row workgroups that recomputed U in eight
 // column splits and walked the rank per thread, 137 us now (3.5 TB/s); the decoding step of 16 episodes
 // 42 us in two launches, 17 in one.
-template <int NU, bool kLight>
-__global__ __launch_bounds__(512) void lora_fwd_kernel(LoraFwdBatch b, int grid) {
-  constexpr int W = 8, NT = 64 * W, TQ = 4;
+template <int NU, bool kHigh, bool kAny, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, kHigh && !kAny ? 3 : 8))) void lora_fwd_kernel(
+    LoraFwdBatch b, int grid) {
+  constexpr int NT = 64 * W, TQ = 4;
   constexpr int kWaveStage = 16 * (1 + NU) * kSP;  // bytes: 16 rows of x, then the units' rows of A
   static_assert(kWaveStage >= 16 * kUP * 4, "the partial U reuses the stage");
   // hardware places workgroup i on XCD i % 8: give each XCD a contiguous range of logical ids
@@ -275,17 +284,37 @@ __global__ __launch_bounds__(512) void lora_fwd_kernel(LoraFwdBatch b, int grid)
     const int nb = (o_hi - o_lo + CB - 1) / CB;
     const int first = (w - base) & (W - 1);
     base += nb;
+    auto add = [&](auto spl, auto ranks, auto depth) {
+      add_columns<decltype(spl)::value, decltype(ranks)::value, decltype(depth)::value>(O, Uf, row0, nrows, o_lo, o_hi,
+                                                                                         first, W, nb, lane);
+    };
     if (O.rank == 16) {
-      add_columns<4, false, 2>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
+      add(I<4>{}, I<0>{}, I<2>{});
     } else if (O.rank == 8) {
-      add_columns<2, false, 2>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
-    } else if constexpr (!kLight) {
-      if (O.rank == 32)
-        add_columns<8, false, 1>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
-      else if (O.rank == 64)
-        add_columns<16, false, 1>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
-      else
-        add_columns<16, true, 1>(O, Uf, row0, nrows, o_lo, o_hi, first, W, nb, lane);
+      add(I<2>{}, I<0>{}, I<2>{});
+    } else if (kHigh && O.rank == 32) {
+      add(I<8>{}, I<0>{}, I<1>{});
+    } else if (kHigh && O.rank == 64) {
+      add(I<16>{}, I<0>{}, I<1>{});
+    } else if constexpr (kAny) {
+      if (O.rank == 12)
+        add(I<4>{}, I<1>{}, I<2>{});
+      else if (O.rank <= 4)
+        add(I<1>{}, I<2>{}, I<2>{});
+      else if (O.rank < 8)
+        add(I<2>{}, I<2>{}, I<2>{});
+      else if (O.rank < 16)
+        add(I<4>{}, I<2>{}, I<1>{});
+      else if constexpr (kHigh) {
+        if (O.rank == 24)
+          add(I<8>{}, I<1>{}, I<1>{});
+        else if (O.rank % 8 == 0)
+          add(I<16>{}, I<1>{}, I<1>{});
+        else if (O.rank < 32)
+          add(I<8>{}, I<2>{}, I<1>{});
+        else
+          add(I<16>{}, I<2>{}, I<1>{});
+      }
     }
   }
 }
@@ -309,27 +338,42 @@ __global__ __launch_bounds__(256) void lora_swap_kernel(LoraSwapBatch b) {
   }
 }
 
-template <bool kLight>
-static void launch_fwd(int nu, const LoraFwdBatch& b, int grid, hipStream_t s) {
-  const dim3 g(grid), t(512);
+template <bool kHigh, bool kAny>
+static void launch_fwd(int nu, bool four, const LoraFwdBatch& b, int grid, hipStream_t s) {
+  auto launch = [&](auto n) {
+    constexpr int NU = decltype(n)::value;
+    if (four)
+      hipLaunchKernelGGL((lora_fwd_kernel<NU, kHigh, kAny, 4>), dim3(grid), dim3(256), 0, s, b, grid);
+    else
+      hipLaunchKernelGGL((lora_fwd_kernel<NU, kHigh, kAny, 8>), dim3(grid), dim3(512), 0, s, b, grid);
+  };
   switch (nu) {
-    case 1: hipLaunchKernelGGL((lora_fwd_kernel<1, kLight>), g, t, 0, s, b, grid); break;
-    case 2: hipLaunchKernelGGL((lora_fwd_kernel<2, kLight>), g, t, 0, s, b, grid); break;
-    case 3: hipLaunchKernelGGL((lora_fwd_kernel<3, kLight>), g, t, 0, s, b, grid); break;
-    default: hipLaunchKernelGGL((lora_fwd_kernel<4, kLight>), g, t, 0, s, b, grid); break;
+    case 1: launch(I<1>{}); break;
+    case 2: launch(I<2>{}); break;
+    case 3: launch(I<3>{}); break;
+    default: launch(I<4>{}); break;
   }
 }
 
 hipError_t launch_lora_fwd(int nu, const LoraFwdBatch& b, hipStream_t s) {
   if (b.total <= 0) return hipSuccess;
   const int grid = (b.total + 7) & ~7;
-  bool light = true;
-  for (int i = 0; i < b.outs; ++i) light = light && (b.o[i].rank == 8 || b.o[i].rank == 16);
+  bool high = false, any = false;
+  for (int i = 0; i < b.outs; ++i) {
+    const int r = b.o[i].rank;
+    high = high || r > 16;
+    any = any || !(r == 8 || r == 16 || r == 32 || r == 64);
+  }
+  // Four waves where d_in leaves eight too little each to start with and two workgroups per CU are there to
+  // fill it (8 / 4 waves, rank 16: 4 x 5000 rows of 256 55 / 40 us, 8 x 2000 of 1024 72 / 61, 16 x 700 of 2048
+  // 78 / 69, 16 x 512 of 4096 131 / 136; 100 x 3 of 2048, 200 workgroups, 109 / 117).
+  bool four = b.total >= 512;
+  for (int i = 0; i < b.count; ++i) four = four && b.j[i].d_in <= 2048;
   KernelTimer t(K_LORA_FWD, s);
-  if (light)
-    launch_fwd<true>(nu, b, grid, s);
+  if (high)
+    any ? launch_fwd<true, true>(nu, four, b, grid, s) : launch_fwd<true, false>(nu, four, b, grid, s);
   else
-    launch_fwd<false>(nu, b, grid, s);
+    any ? launch_fwd<false, true>(nu, four, b, grid, s) : launch_fwd<false, false>(nu, four, b, grid, s);
   return hipGetLastError();
 }
 

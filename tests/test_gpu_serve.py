@@ -235,3 +235,19 @@ def test_forward_infinities(attt):
     got, = _run(attt, [p])
     bad = (got & 0x7F80) == 0x7F80
     assert bad[:, 5].all() and not np.delete(bad, 5, 1).any() and np.all((got[:, 5] & 0x7F) == 0)
+
+
+@pytest.mark.parametrize("rows", [20, 4100])
+@pytest.mark.parametrize("rank", [1, 3, 4, 5, 7, 9, 12, 15, 17, 20, 24, 31, 33, 40, 48, 56, 63])
+def test_forward_any_rank(attt, rank, rows):
+    """Ranks between the four that are loaded whole, on launches of eight waves and (514 row blocks) of
+    four, one of them beside a rank of 16 and with an infinite last rank that must reach every column."""
+    rng = np.random.default_rng(100 * rank + rows)
+    probs = [_problem(rng, rows, 72, 136, rank), _problem(rng, rows, 72, 64, 16)]
+    note(f"lora_forward {rows} rows rank {rank}")
+    for g, p in zip(_run(attt, probs), probs):
+        _check_forward(g, p)
+    p = _problem(rng, 20, 64, 72, rank)
+    p["B"][:, rank - 1] = 0x7F80
+    got, = _run(attt, [p])
+    assert np.all((got & 0x7F80) == 0x7F80)
