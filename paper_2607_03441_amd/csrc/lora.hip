@@ -466,9 +466,11 @@ __global__ __launch_bounds__(256) void lora_reduce_kernel(LoraRedBatch b, const 
 // Adapter step of Eq. 2: p <- p - lr g in float32, the product and the difference each rounded
 // to nearest (explicit roundings, no contraction into a fused multiply-add), then the bf16
 // copy (round to nearest even) and the gradient reset when asked. Bound by memory (18 bytes an
-// element with copy and reset): 2048 elements per workgroup, eight consecutive ones per thread in
-// 16-byte accesses where the arrays are aligned for them, and up to 72 tensors per launch (the 256 of a
-// 32-layer adapter took 16 launches of 4-byte accesses, 109 us; four of these take 55, 4.5 TB/s).
+// element with copy and reset): 2048 elements per workgroup, twice four consecutive ones per thread in
+// 16-byte accesses (a wave's side by side) where the arrays are aligned for them, all loads ahead of the stores
+// either way, and up to 72 tensors per launch. The 256 of a 32-layer adapter (65536 elements each) took 16
+// launches of 4-byte accesses, 109 us; four of these take 49 (6.2 TB/s, its 302 MB near the last-level cache), 55
+// where the arrays are not aligned; 256 of 163840 150 (5.0 TB/s); one of 20 million 49, as 4-byte accesses did.
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ float sgd_one(float p, float g, float lr) {
 #pragma clang fp contract(off)  // the product keeps its own rounding: no fused multiply-add
@@ -480,36 +482,41 @@ __global__ __launch_bounds__(256) void lora_sgd_kernel(LoraSgdBatch b, float lr,
   const int ji = find_job(b, (int)blockIdx.x);
   const LoraSgdJob J = b.j[ji];
   const int64_t base = (int64_t)((int)blockIdx.x - J.b_begin) * kLoraSgdPerBlock;
-  const int64_t i0 = base + threadIdx.x * 8;
+  const int64_t i0 = base + threadIdx.x * 4;
   if (J.vec && base + kLoraSgdPerBlock <= J.n) {
     f32x4 p[2], g[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      p[h] = *reinterpret_cast<const f32x4*>(J.param + i0 + 4 * h);
-      g[h] = *reinterpret_cast<const f32x4*>(J.grad + i0 + 4 * h);
+      p[h] = *reinterpret_cast<const f32x4*>(J.param + i0 + 1024 * h);
+      g[h] = *reinterpret_cast<const f32x4*>(J.grad + i0 + 1024 * h);
     }
-    u32x4 o;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) p[h][e] = sgd_one(p[h][e], g[h][e], lr);
-      *reinterpret_cast<f32x4*>(J.param + i0 + 4 * h) = p[h];
-      if (zero_grad) *reinterpret_cast<f32x4*>(J.grad + i0 + 4 * h) = f32x4{0.f, 0.f, 0.f, 0.f};
-      o[2 * h] = pack_bf16x2(p[h][0], p[h][1]);
-      o[2 * h + 1] = pack_bf16x2(p[h][2], p[h][3]);
+      *reinterpret_cast<f32x4*>(J.param + i0 + 1024 * h) = p[h];
+      if (zero_grad) *reinterpret_cast<f32x4*>(J.grad + i0 + 1024 * h) = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (J.param_bf16)
+        *reinterpret_cast<uint2*>(J.param_bf16 + i0 + 1024 * h) = uint2{pack_bf16x2(p[h][0], p[h][1]), pack_bf16x2(p[h][2], p[h][3])};
     }
-    if (J.param_bf16) *reinterpret_cast<u32x4*>(J.param_bf16 + i0) = o;
     return;
   }
+  constexpr int kPer = kLoraSgdPerBlock / 256;
+  float p[kPer], g[kPer];
 #pragma unroll
-  for (int u = 0; u < kLoraSgdPerBlock / 256; ++u) {
+  for (int u = 0; u < kPer; ++u) {
     const int64_t i = base + u * 256 + threadIdx.x;
-    if (i < J.n) {
-      const float p = sgd_one(J.param[i], J.grad[i], lr);
-      J.param[i] = p;
-      if (J.param_bf16) J.param_bf16[i] = (uint16_t)f32_to_bf16_bits(p);
-      if (zero_grad) J.grad[i] = 0.0f;
-    }
+    p[u] = i < J.n ? J.param[i] : 0.0f;
+    g[u] = i < J.n ? J.grad[i] : 0.0f;
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t i = base + u * 256 + threadIdx.x;
+    if (i >= J.n) break;
+    p[u] = sgd_one(p[u], g[u], lr);
+    J.param[i] = p[u];
+    if (J.param_bf16) J.param_bf16[i] = (uint16_t)f32_to_bf16_bits(p[u]);
+    if (zero_grad) J.grad[i] = 0.0f;
   }
 }
 
