@@ -123,7 +123,7 @@ hipError_t launch_ngram_weight(const NgramEpBatch& b, int total_blocks, int n, f
 
 // ---- update-text repetition (Eq. 6-7) ------------------------------------------------------
 constexpr int kRepSlots = 16384;        // entries of the largest LDS word set of the count kernel
-constexpr int kRepPartWords = 4096;     // words per hash partition the host plans for (load <= 1/4)
+constexpr int kRepPartWords = 4096;     // words per hash partition the host plans for
 struct RepEp {
   int64_t text0;      // first text of the episode (index into the text offsets)
   int64_t wg_global;  // first count record of the episode ([pair][part] order, 4 ints each)
@@ -132,7 +132,8 @@ struct RepEp {
   int32_t parts;      // hash partitions per pair
   int32_t wg_begin;   // first count-kernel workgroup of the episode within the launch
   int32_t ep;         // episode index (outputs)
-  int32_t slots;      // entries of each LDS word set, a power of two
+  int32_t slots;      // entries of each LDS word set where many share the chip, a power of two: at most half
+                      // full, but for texts of 4097 to 8192 words, which fit whole
 };
 struct RepBatch {
   int32_t count;

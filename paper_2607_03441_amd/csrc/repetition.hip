@@ -34,17 +34,39 @@ __device__ __forceinline__ uint32_t word_hash(int32_t w) {
 __device__ __forceinline__ int part_of(uint32_t h, int parts) { return (int)(((h >> 8) * (uint32_t)parts) >> 24); }
 
 // A set is an array of buckets of four words (bmask + 1 of them), searched bucket by bucket from the
-// hash's low bits; the slots of a bucket are taken in order and kRepEmpty marks a free one, so a bucket
-// with a free slot ends every search, and one 16-byte read settles nearly all of them (a wave walks on
-// for as long as any of its lanes does).
-//
+// hash's low bits; kRepEmpty marks a free slot. A word takes the first free slot of a bucket in an order that
+// begins at its own slot and goes round, and nothing leaves a set: a bucket with a free slot ends every
+// search. Dense sets (up to half full and beyond) read the bucket first, 16 bytes that settle nearly all
+// searches (a wave walks on for as long as any of its lanes does); their own slot is the first. In sparse
+// ones (a quarter full) the own slot comes from two more bits of the hash and is nearly always free or the
+// word's, so that an exchange on it settles the insertion by itself; a free own slot means that the word is
+// not there.
+template <bool kSparse>
+__device__ __forceinline__ uint32_t own_slot(uint32_t h) { return kSparse ? (h >> 12) & 3u : 0u; }
+static_assert(kRepSlots / 4 <= 1 << 12, "the bucket comes from the hash bits below the own slot's");
+
 // set_insert returns 1 if w was new, 0 if present, -1 if the set is full (the caller flags the call).
+template <bool kSparse>
 __device__ __forceinline__ int set_insert(uint32_t* tab, uint32_t bmask, uint32_t h, uint32_t w) {
+  const uint32_t own = own_slot<kSparse>(h);
   uint32_t b = h & bmask;
+  if constexpr (kSparse) {
+    const uint32_t cur = atomicCAS(tab + 4 * b + own, kRepEmpty, w);
+    if (cur == kRepEmpty) return 1;
+    if (cur == w) return 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
   for (uint32_t probe = 0; probe <= bmask;) {
     const u32x4 e = *reinterpret_cast<const u32x4*>(tab + 4 * b);
     if (e[0] == w || e[1] == w || e[2] == w || e[3] == w) return 0;
-    const int free = e[0] == kRepEmpty ? 0 : e[1] == kRepEmpty ? 1 : e[2] == kRepEmpty ? 2 : e[3] == kRepEmpty ? 3 : 4;
+    uint32_t free;
+    if constexpr (kSparse) {
+      const uint32_t m = (e[0] == kRepEmpty ? 1u : 0u) | (e[1] == kRepEmpty ? 2u : 0u) | (e[2] == kRepEmpty ? 4u : 0u) |
+                         (e[3] == kRepEmpty ? 8u : 0u);
+      free = m ? (own + __builtin_ctz((m | m << 4) >> own)) & 3u : 4u;
+    } else {
+      free = e[0] == kRepEmpty ? 0 : e[1] == kRepEmpty ? 1 : e[2] == kRepEmpty ? 2 : e[3] == kRepEmpty ? 3 : 4;
+    }
     if (free == 4) {
       b = (b + 1u) & bmask;
       ++probe;
@@ -57,23 +79,27 @@ __device__ __forceinline__ int set_insert(uint32_t* tab, uint32_t bmask, uint32_
   }
   return -1;
 }
+template <bool kSparse>
 __device__ __forceinline__ bool set_contains(const uint32_t* tab, uint32_t bmask, uint32_t h, uint32_t w) {
   uint32_t b = h & bmask;
   for (uint32_t probe = 0; probe <= bmask; ++probe) {
     const u32x4 e = *reinterpret_cast<const u32x4*>(tab + 4 * b);
     if (e[0] == w || e[1] == w || e[2] == w || e[3] == w) return true;
-    if (e[3] == kRepEmpty) return false;
+    if (e[3] == kRepEmpty || (kSparse && (e[0] == kRepEmpty || e[1] == kRepEmpty || e[2] == kRepEmpty))) return false;
     b = (b + 1u) & bmask;
   }
   return false;
 }
 
-// Bound by latency: the words of both texts, then their probes of the LDS sets. The first kRepAhead
-// words per thread of both texts are loaded before the sets are cleared, and the sets are as small as
-// the texts allow (64 KiB for texts of 4096 words, so two workgroups share a CU). 512 such pairs took
-// 32 us with 128 KiB sets probed word by word, 26 us now.
+// Bound by latency: the words of both texts, then their probes of the LDS sets. A thread takes kRepAhead
+// words at a time; the first of both texts are loaded before the sets are cleared, the next ones while a
+// block is inserted. Sparse sets are the largest LDS holds, dense ones as small as the texts allow (64 KiB for
+// texts of 4096 words, so two workgroups share a CU). 512 such pairs took 32 us with 128 KiB sets probed word by
+// word, 26 with dense ones; the one pair of two texts of 100000 words 112 us with words loaded one by one, 104 now
+// (both kernels).
 constexpr int kRepAhead = 4;
 
+template <bool kSparse>
 __global__ __launch_bounds__(1024) void rep_count_kernel(RepBatch batch, const int32_t* __restrict__ words,
                                                          const int64_t* __restrict__ toff,
                                                          int32_t* __restrict__ counts) {
@@ -93,13 +119,16 @@ __global__ __launch_bounds__(1024) void rep_count_kernel(RepBatch batch, const i
   const uint32_t mask = (uint32_t)(E.slots >> 2) - 1u;  // of the buckets
   __shared__ int cnt[4];                             // |A|, |B|, |A & B|, full
   const int tid = threadIdx.x, nt = blockDim.x;
-  int32_t wa[kRepAhead], wb[kRepAhead];
+  const int na_words = max(0, (int)(a1 - a0)), nb_words = max(0, (int)(b1 - b0));  // at most 2^20 each
+  const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(words + a0, na_words * 4), rb = buffer_rsrc(words + b0, nb_words * 4);
+  // words i, i + nt, ... of a text; zero past its end
+  auto load = [&](uint32_t (&w)[kRepAhead], __amdgpu_buffer_rsrc_t r, int i) {
 #pragma unroll
-  for (int u = 0; u < kRepAhead; ++u) {
-    const int64_t i = tid + (int64_t)u * nt;
-    wa[u] = a0 + i < a1 ? words[a0 + i] : 0;
-    wb[u] = b0 + i < b1 ? words[b0 + i] : 0;
-  }
+    for (int u = 0; u < kRepAhead; ++u) w[u] = __builtin_amdgcn_raw_buffer_load_b32(r, (uint32_t)(i + u * nt) * 4u, 0, 0);
+  };
+  uint32_t wa[kRepAhead], wb[kRepAhead];
+  load(wa, ra, tid);
+  load(wb, rb, tid);
   {
     u32x4* t4 = reinterpret_cast<u32x4*>(smem);
     for (int i = tid; i < E.slots / 2; i += nt) t4[i] = u32x4{kRepEmpty, kRepEmpty, kRepEmpty, kRepEmpty};
@@ -107,32 +136,30 @@ __global__ __launch_bounds__(1024) void rep_count_kernel(RepBatch batch, const i
   }
   __syncthreads();
   int na = 0, nb = 0, ni = 0, full = 0;
-  auto insert_a = [&](int32_t w) {
-    const uint32_t h = word_hash(w);
-    if (part_of(h, E.parts) != part) return;
-    const int r = set_insert(ta, mask, h, (uint32_t)w);
-    na += r > 0;
-    full |= r < 0;
-  };
-  auto insert_b = [&](int32_t w) {
-    const uint32_t h = word_hash(w);
-    if (part_of(h, E.parts) != part) return;
-    const int r = set_insert(tb, mask, h, (uint32_t)w);
-    if (r > 0) {
-      ++nb;
-      ni += set_contains(ta, mask, h, (uint32_t)w);
+  // Inserts the partition's words of a text of n, the thread's first of them in `next`, into `tab`;
+  // added(h, w) for every new one.
+  auto insert_text = [&](uint32_t* tab, __amdgpu_buffer_rsrc_t r, int n, uint32_t (&next)[kRepAhead], auto added) {
+    for (int i = tid; i < n; i += kRepAhead * nt) {
+      uint32_t w[kRepAhead];
+#pragma unroll
+      for (int u = 0; u < kRepAhead; ++u) w[u] = next[u];
+      if (n > kRepAhead * nt) load(next, r, i + kRepAhead * nt);
+#pragma unroll
+      for (int u = 0; u < kRepAhead; ++u) {
+        const uint32_t h = word_hash((int32_t)w[u]);
+        if (i + u * nt >= n || part_of(h, E.parts) != part) continue;
+        const int got = set_insert<kSparse>(tab, mask, h, w[u]);
+        if (got > 0) added(h, w[u]);
+        full |= got < 0;
+      }
     }
-    full |= r < 0;
   };
-#pragma unroll
-  for (int u = 0; u < kRepAhead; ++u)
-    if (a0 + tid + (int64_t)u * nt < a1) insert_a(wa[u]);
-  for (int64_t i = a0 + tid + (int64_t)kRepAhead * nt; i < a1; i += nt) insert_a(words[i]);
+  insert_text(ta, ra, na_words, wa, [&](uint32_t, uint32_t) { ++na; });
   __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kRepAhead; ++u)
-    if (b0 + tid + (int64_t)u * nt < b1) insert_b(wb[u]);
-  for (int64_t i = b0 + tid + (int64_t)kRepAhead * nt; i < b1; i += nt) insert_b(words[i]);
+  insert_text(tb, rb, nb_words, wb, [&](uint32_t h, uint32_t w) {
+    ++nb;
+    ni += set_contains<kSparse>(ta, mask, h, w);
+  });
   // per-thread counts, then one LDS atomic each
   if (na) atomicAdd(cnt + 0, na);
   if (nb) atomicAdd(cnt + 1, nb);
@@ -202,22 +229,36 @@ __global__ __launch_bounds__(64) void rep_reduce_kernel(RepBatch batch, const in
   best[e] = bk;
 }
 
-hipError_t launch_rep_count(const RepBatch& b, int total_wgs, int slots, const int32_t* words, const int64_t* toff,
-                            int32_t* counts, hipStream_t s) {
-  if (total_wgs <= 0) return hipSuccess;
+template <bool kSparse>
+static hipError_t rep_count(const RepBatch& b, int total_wgs, int slots, int threads, const int32_t* words,
+                            const int64_t* toff, int32_t* counts, hipStream_t s) {
   static bool attr = false;
-  const size_t lds = (size_t)2 * slots * 4;
   if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)rep_count_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipError_t e = hipFuncSetAttribute((const void*)rep_count_kernel<kSparse>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        2 * kRepSlots * 4);
     if (e != hipSuccess) return e;
     attr = true;
   }
   KernelTimer t(K_REP_COUNT, s);
-  // four words of each text per thread up to 1024 threads
-  const int threads = slots <= 2048 ? 256 : slots <= 4096 ? 512 : 1024;
-  hipLaunchKernelGGL(rep_count_kernel, dim3(total_wgs), dim3(threads), lds, s, b, words, toff, counts);
+  hipLaunchKernelGGL(rep_count_kernel<kSparse>, dim3(total_wgs), dim3(threads), (size_t)2 * slots * 4, s, b, words, toff,
+                     counts);
   return hipGetLastError();
+}
+
+hipError_t launch_rep_count(const RepBatch& b, int total_wgs, int slots, const int32_t* words, const int64_t* toff,
+                            int32_t* counts, hipStream_t s) {
+  if (total_wgs <= 0) return hipSuccess;
+  // Where there is a CU for every workgroup the latency of one counts, and sparse sets cost nothing. Dense /
+  // sparse, both kernels: one pair of 1000 words 26.0 / 20.2 us, of 4096 31.3 / 27.4, of 100000 (25 workgroups)
+  // 129 / 104; 512 pairs of 4096 words 45 / 57.
+  if (total_wgs <= 256) {
+    RepBatch big = b;
+    for (int i = 0; i < big.count; ++i) big.e[i].slots = kRepSlots;
+    return rep_count<true>(big, total_wgs, kRepSlots, 1024, words, toff, counts, s);
+  }
+  // four words of each text per thread up to 1024 threads, so that CUs share small sets
+  const int threads = slots <= 2048 ? 256 : slots <= 4096 ? 512 : 1024;
+  return rep_count<false>(b, total_wgs, slots, threads, words, toff, counts, s);
 }
 
 hipError_t launch_rep_reduce(const RepBatch& b, const int32_t* counts, double tau, double* rho, double* nu,

@@ -128,3 +128,28 @@ def test_set_sizes(attt, longest):
     assert pairs.tolist() == [list(w) for w in want]
     j = [i / u for i, u in want]
     assert rho[0] == max(j) and best[0] == j.index(max(j)) and nu[0] == 1.0 - rho[0] and skip[0] == (nu[0] < 0.5)
+
+
+@pytest.mark.parametrize("longest", [1, 129, 1025, 4096, 4097, 8192, 8193])
+def test_set_sizes_of_many_pairs(attt, longest):
+    """The same lengths in calls of more than 256 workgroups, whose sets are as small as the texts allow and
+    read before they are written to; duplicates within a text too."""
+    rng = np.random.default_rng(longest + 7)
+    texts = []
+    for k in range(302):
+        n = max(1, longest // (1, 2, 3, 5, 9)[k % 5])
+        texts.append(rng.permutation(3 * longest)[:n].astype(np.int32) if k % 2 else
+                     rng.integers(0, 3 * longest, n).astype(np.int32))
+    etx = np.array([0, 151, 302], np.int64)
+    toff = np.concatenate([[0], np.cumsum([len(t) for t in texts])]).astype(np.int64)
+    note(f"repetition, 300 pairs of up to {longest} words")
+    rho, nu, skip, best, pairs = (t.cpu().numpy() for t in attt.update_repetition(
+        dev_i32(np.concatenate(texts)), toff, etx, tau=0.5, want_pairs=True))
+    want = []
+    for e in range(2):
+        sets = [set(t.tolist()) for t in texts[etx[e]:etx[e + 1]]]
+        mine = [(len(sets[-1] & s), len(sets[-1] | s)) for s in sets[:-1]]
+        j = [i / u for i, u in mine]
+        assert rho[e] == max(j) and best[e] == j.index(max(j)) and nu[e] == 1.0 - rho[e]
+        want += mine
+    assert pairs.tolist() == [list(w) for w in want]
