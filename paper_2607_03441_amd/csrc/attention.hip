@@ -31,6 +31,7 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "lds_limit.hpp"
 
 namespace attt {
 
@@ -824,19 +825,11 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnArgs a, AttnBatch b
     }
 }
 
-template <class K>
-static hipError_t set_lds(K kernel, bool& attr, size_t lds) {
-  if (attr) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  attr = e == hipSuccess;
-  return e;
-}
-
 // A kernel whose 256-thread workgroups take blocks of `rows` queries or keys of one of `heads`.
 template <class K>
-static hipError_t launch_blocks(K kernel, bool& attr, int rows, int heads, size_t lds, const AttnArgs& a, AttnBatch b,
+static hipError_t launch_blocks(K kernel, LdsLimit& limit, int rows, int heads, size_t lds, const AttnArgs& a, AttnBatch b,
                                 int id, hipStream_t s) {
-  if (hipError_t e = set_lds(kernel, attr, lds)) return e;
+  if (hipError_t e = limit.raise((const void*)kernel, lds)) return e;
   int n = 0;
   for (int i = 0; i < b.count; ++i) {
     b.e[i].blocks = (b.e[i].L + rows - 1) / rows;
@@ -850,11 +843,11 @@ static hipError_t launch_blocks(K kernel, bool& attr, int rows, int heads, size_
 }
 
 template <int KT>
-static hipError_t launch_keys(bool& attr, const AttnArgs& a, AttnBatch b, hipStream_t s) {
+static hipError_t launch_keys(LdsLimit& limit, const AttnArgs& a, AttnBatch b, hipStream_t s) {
   constexpr int KBLK = 64 * KT;
   constexpr size_t lds = 2 * (size_t)kQoBuf + 2 * KBLK * PR * 2;
   static_assert(2 * kQoBuf >= 65536 && lds <= 160 * 1024, "the exchange at the end needs 64 KiB");
-  if (hipError_t e = set_lds(attn_dkdv_kernel<KT>, attr, lds)) return e;
+  if (hipError_t e = limit.raise((const void*)attn_dkdv_kernel<KT>, lds)) return e;
   int n = 0, blocks = 0;
   for (int i = 0; i < b.count; ++i) {
     b.e[i].blocks = (b.e[i].L + KBLK - 1) / KBLK;
@@ -874,10 +867,10 @@ static hipError_t launch_keys(bool& attr, const AttnArgs& a, AttnBatch b, hipStr
 }
 
 hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStream_t s) {
-  static bool attr[7] = {};
+  static LdsLimit limits[7];
   if (kernel == 1 && b.tiles == 0)
-    return launch_blocks(attn_dkdv_short_kernel, attr[6], BLK, a.kv_heads, 2 * (size_t)kQoBuf, a, b, K_ATTN_DKDV, s);
-  if (kernel == 1) return b.tiles == 1 ? launch_keys<1>(attr[4], a, b, s) : launch_keys<2>(attr[5], a, b, s);
+    return launch_blocks(attn_dkdv_short_kernel, limits[6], BLK, a.kv_heads, 2 * (size_t)kQoBuf, a, b, K_ATTN_DKDV, s);
+  if (kernel == 1) return b.tiles == 1 ? launch_keys<1>(limits[4], a, b, s) : launch_keys<2>(limits[5], a, b, s);
   constexpr size_t lds = 2 * (size_t)kKvBuf;
   // Two query tiles per wave where their workgroups fill 7/8 of the chip's two per CU; below that the longest
   // chain of key blocks is the time, and a step of one tile is the shorter one. One tile too where blocks of
@@ -889,10 +882,10 @@ hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStr
   for (int i = 0; i < b.count; ++i) n1 += (b.e[i].L + 63) / 64, n2 += (b.e[i].L + 127) / 128;
   const bool wide = (int64_t)n2 * a.heads > 448 && 8 * (int64_t)n1 > 9 * (int64_t)n2;
   if (kernel == 0)
-    return wide ? launch_blocks(attn_fwd_stats_kernel<2>, attr[0], 128, a.heads, lds, a, b, K_ATTN_FWD, s)
-                : launch_blocks(attn_fwd_stats_kernel<1>, attr[1], 64, a.heads, lds, a, b, K_ATTN_FWD, s);
-  return wide ? launch_blocks(attn_dq_kernel<2>, attr[2], 128, a.heads, lds, a, b, K_ATTN_DQ, s)
-              : launch_blocks(attn_dq_kernel<1>, attr[3], 64, a.heads, lds, a, b, K_ATTN_DQ, s);
+    return wide ? launch_blocks(attn_fwd_stats_kernel<2>, limits[0], 128, a.heads, lds, a, b, K_ATTN_FWD, s)
+                : launch_blocks(attn_fwd_stats_kernel<1>, limits[1], 64, a.heads, lds, a, b, K_ATTN_FWD, s);
+  return wide ? launch_blocks(attn_dq_kernel<2>, limits[2], 128, a.heads, lds, a, b, K_ATTN_DQ, s)
+              : launch_blocks(attn_dq_kernel<1>, limits[3], 64, a.heads, lds, a, b, K_ATTN_DQ, s);
 }
 
 }  // namespace attt

@@ -28,6 +28,7 @@
 #include "common.hpp"
 #include "gemm_core.hpp"
 #include "internal.hpp"
+#include "lds_limit.hpp"
 
 namespace attt {
 
@@ -515,22 +516,12 @@ __global__ __launch_bounds__(256) void ce_head_transpose_kernel(const bf16_t* __
 // ------------------------------------------------------------------------------------------
 // Launchers
 // ------------------------------------------------------------------------------------------
-template <class Kern>
-static hipError_t allow_big_lds(Kern k) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-}
-
 template <class C>
 static hipError_t fwd_bf16(const bf16_t* h, const bf16_t* W, int N, int d, int V, float2* partials,
                            int n_vb, const int* gate, hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = allow_big_lds(ce_fwd_bf16_kernel<C>);
-    if (e == hipSuccess) e = allow_big_lds(ce_guard_fwd_bf16_kernel<C>);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit plain, guard;
+  if (hipError_t e = plain.raise((const void*)ce_fwd_bf16_kernel<C>, 160 * 1024)) return e;
+  if (hipError_t e = guard.raise((const void*)ce_guard_fwd_bf16_kernel<C>, 160 * 1024)) return e;
   const int tv = (V + C::BM - 1) / C::BM, tt = (N + C::BN - 1) / C::BN;
   KernelTimer t(gate ? K_CE_GUARD : K_CE_FWD, s);
   if (gate)

@@ -39,6 +39,7 @@
 #include "common.hpp"
 #include "gemm_core.hpp"
 #include "internal.hpp"
+#include "lds_limit.hpp"
 
 namespace attt {
 
@@ -642,14 +643,9 @@ hipError_t launch_ce_fused(bool label, const CeFusedArgs& a, hipStream_t s) {
                             reinterpret_cast<const void*>(ce_fused_bwd_split_kernel<false>)},
                            {reinterpret_cast<const void*>(ce_fused_bwd_kernel<true>),
                             reinterpret_cast<const void*>(ce_fused_bwd_split_kernel<true>)}};
-  static bool attr = false;
-  if (!attr) {
-    for (int i = 0; i < 4; ++i) {
-      hipError_t e = hipFuncSetAttribute(fns[i >> 1][i & 1], hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLds);
-      if (e != hipSuccess) return e;
-    }
-    attr = true;
-  }
+  static LdsLimit limits[4];
+  for (int i = 0; i < 4; ++i)
+    if (hipError_t e = limits[i].raise(fns[i >> 1][i & 1], kFusedLds)) return e;
   CeFusedArgs arg = a;
   void* args[] = {&arg};
   KernelTimer t(label ? K_CE_FUSED : K_CE_GUARD, s);

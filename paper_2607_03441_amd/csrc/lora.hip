@@ -25,6 +25,7 @@
 // The float32 path runs the same jobs on the float32 MFMA.
 #include "common.hpp"
 #include "internal.hpp"
+#include "lds_limit.hpp"
 
 namespace attt {
 
@@ -560,11 +561,8 @@ static hipError_t launch_p2_bf16(const LoraP2Batch& b, int blocks, uint8_t* ws, 
   int max_nt = 1;
   for (int i = 0; i < b.count; ++i) max_nt = max(max_nt, b.j[i].nt);
   const size_t lds = lora_p2_lds<CT>(max_nt);
-  if (lds > 65536) {  // four rank tiles on 128 columns; per device, so on every such call
-    const hipError_t e =
-        hipFuncSetAttribute((const void*)lora_p2_bf16_kernel<CT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  static LdsLimit limit;  // needed for four rank tiles on 128 columns
+  if (hipError_t e = limit.raise((const void*)lora_p2_bf16_kernel<CT>, lora_p2_lds<CT>(kLoraMaxTiles))) return e;
   hipLaunchKernelGGL(lora_p2_bf16_kernel<CT>, dim3(blocks), dim3(256), lds, s, b, max_nt, ws);
   return hipGetLastError();
 }

@@ -28,6 +28,7 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "lds_limit.hpp"
 
 namespace attt {
 
@@ -335,13 +336,8 @@ static size_t ngram_table_lds(int slots) { return (size_t)slots * 4 + (size_t)(k
 template <int N>
 static hipError_t count_n(const NgramPartBatch& b, int total_blocks, size_t lds, const int32_t* history,
                           const int32_t* tokens, const uint2* list, uint16_t* partial, hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)ngram_count_kernel<N>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit limit;
+  if (hipError_t e = limit.raise((const void*)ngram_count_kernel<N>, 160 * 1024)) return e;
   hipLaunchKernelGGL(ngram_count_kernel<N>, dim3(total_blocks), dim3(1024), lds, s, b, history, tokens, list,
                      partial);
   return hipGetLastError();
@@ -350,13 +346,8 @@ static hipError_t count_n(const NgramPartBatch& b, int total_blocks, size_t lds,
 template <int N>
 static hipError_t table_n(const NgramPartBatch& b, size_t lds, const int32_t* tokens, uint16_t* canon, uint2* list,
                           hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)ngram_table_kernel<N>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit limit;
+  if (hipError_t e = limit.raise((const void*)ngram_table_kernel<N>, 160 * 1024)) return e;
   hipLaunchKernelGGL(ngram_table_kernel<N>, dim3(b.count), dim3(1024), lds, s, b, tokens, canon, list);
   return hipGetLastError();
 }

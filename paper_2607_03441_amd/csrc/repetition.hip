@@ -16,6 +16,7 @@
 // Integer counts throughout, so the result is bit-reproducible.
 #include "common.hpp"
 #include "internal.hpp"
+#include "lds_limit.hpp"
 
 namespace attt {
 
@@ -232,13 +233,8 @@ __global__ __launch_bounds__(64) void rep_reduce_kernel(RepBatch batch, const in
 template <bool kSparse>
 static hipError_t rep_count(const RepBatch& b, int total_wgs, int slots, int threads, const int32_t* words,
                             const int64_t* toff, int32_t* counts, hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)rep_count_kernel<kSparse>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       2 * kRepSlots * 4);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit limit;
+  if (hipError_t e = limit.raise((const void*)rep_count_kernel<kSparse>, 2 * kRepSlots * 4)) return e;
   KernelTimer t(K_REP_COUNT, s);
   hipLaunchKernelGGL(rep_count_kernel<kSparse>, dim3(total_wgs), dim3(threads), (size_t)2 * slots * 4, s, b, words, toff,
                      counts);
