@@ -1275,22 +1275,30 @@ LoraPlan lora_plan(const attt_lora_problem* p, int32_t count, int32_t dtype) {
   return P;
 }
 
-// Launches `jobs` in batches of Batch::kCap; blocks(job) gives each job's workgroup count.
-template <class Batch = void, class Job, class Blocks, class Launch>
-attt_status lora_launch_all(const std::vector<Job>& jobs, Blocks blocks, Launch launch, const char* name) {
+// Launches `jobs` in batches of Batch::kCap. form(jobs, n) picks a batch's variant, blocks(job, variant) gives
+// each job's workgroup count.
+template <class Batch = void, class Job, class Form, class Blocks, class Launch>
+attt_status lora_launch_all(const std::vector<Job>& jobs, Form form, Blocks blocks, Launch launch, const char* name) {
   using B = std::conditional_t<std::is_void_v<Batch>, LoraBatchOf<Job>, Batch>;
   for (size_t j0 = 0; j0 < jobs.size(); j0 += B::kCap) {
     B b{};
     b.count = (int32_t)std::min<size_t>(B::kCap, jobs.size() - j0);
+    const auto variant = form(&jobs[j0], b.count);
     int total = 0;
     for (int i = 0; i < b.count; ++i) {
       b.j[i] = jobs[j0 + i];
       b.j[i].b_begin = total;
-      total += blocks(b.j[i]);
+      total += blocks(b.j[i], variant);
     }
-    HIP_TRY(launch(b, total), name);
+    HIP_TRY(launch(b, total, variant), name);
   }
   return ATTT_OK;
+}
+template <class Batch = void, class Job, class Blocks, class Launch>
+attt_status lora_launch_all(const std::vector<Job>& jobs, Blocks blocks, Launch launch, const char* name) {
+  return lora_launch_all<Batch>(
+      jobs, [](const Job*, int) { return 0; }, [&](const Job& J, int) { return blocks(J); },
+      [&](const auto& b, int n, int) { return launch(b, n); }, name);
 }
 
 }  // namespace
@@ -1415,16 +1423,19 @@ extern "C" attt_status attt_lora_grad(const attt_lora_problem* problems, int32_t
       p1, [&](const LoraP1Job& J) { return J.rows_pad / (dtype == ATTT_BF16 ? kLoraP1Rows : kLoraP1RowsF32); },
       [&](const LoraP1Batch& b, int n) { return launch_lora_pass1(dtype, b.j[0].nt, b, n, ws, s); }, "lora_u_du");
   if (st) return st;
-  // Pass 2 in bf16 on 128 columns a workgroup where that leaves four per CU, else on 64 (64 / 128: 2304
-  // workgroups of 128 at 8192 rows of a 4096 model 69.5 / 66.4 us, about 3000 at 3 episodes of 10000 rows of
-  // 5120 120 / 108, 8 of 16384 rows at rank 64 360 / 291; 1008 at 4 ragged episodes of 1024 39.4 / 41.4, 288 at 2048 rows of 2048
-  // 13.2 / 16.1).
-  int64_t wide = 0;
-  for (const LoraP2Job& J : p2) wide += J.splits * ceil_div(J.cols, 2 * kLoraColTile);
-  const int col_tile = dtype == ATTT_BF16 && wide >= 1024 ? 2 * kLoraColTile : kLoraColTile;
+  // Pass 2 in bf16 on 128 columns a workgroup where that leaves a launch two per CU, else on 64. 64 / 128 columns,
+  // by the workgroups of 128 per launch: 128 (64 problems of 600 x 1024 -> 1024) 81.3 / 94.6 us, 160 (58 of 2000 x 264
+  // -> 136) 97.5 / 105.7, 192 (8 episodes of 300 rows of 2048) 41.8 / 48.3, 512 (30 of 2000 x 1024 -> 1024) 71.1 / 68.1, 768
+  // (4 episodes of 1024 rows of 4096) 37.0 / 38.2, 939 (8 of 1000 rows of 5120) 110 / 101, 2304 (8192 rows of 4096) 70.3 / 64.5.
   st = lora_launch_all(
-      p2, [&](const LoraP2Job& J) { return J.splits * (int)ceil_div(J.cols, col_tile); },
-      [&](const LoraP2Batch& b, int n) { return launch_lora_pass2(dtype, col_tile, b, n, ws, s); }, "lora_dadb");
+      p2,
+      [&](const LoraP2Job* J, int n) {
+        int64_t wide = 0;
+        for (int i = 0; i < n; ++i) wide += J[i].splits * ceil_div(J[i].cols, 2 * kLoraColTile);
+        return dtype == ATTT_BF16 && wide >= 512 ? 2 * kLoraColTile : kLoraColTile;
+      },
+      [](const LoraP2Job& J, int col_tile) { return J.splits * (int)ceil_div(J.cols, col_tile); },
+      [&](const LoraP2Batch& b, int n, int col_tile) { return launch_lora_pass2(dtype, col_tile, b, n, ws, s); }, "lora_dadb");
   if (st) return st;
   return lora_launch_all(
       red, [](const LoraRedJob& J) { return (int)ceil_div((int64_t)J.rank * J.d_in + (int64_t)J.d_out * J.rank, 256); },

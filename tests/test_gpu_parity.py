@@ -547,7 +547,7 @@ def test_ce_fused_exact_after_abort_is_deterministic(attt):
 
 @pytest.mark.parametrize("count", [3, 58])
 def test_lora_grad_column_tiles(attt, count):
-    """Pass 2 on 64 and (58 problems: 1160 workgroups) on 128 columns a workgroup: 264 and 136 columns end
+    """Pass 2 on 64 columns a workgroup, in one launch and (58 problems) in eight: 264 and 136 columns end
     inside a tile, 2000 rows inside a step. Float32 results of 16-bit factors: 2^-17 each, 1e-5 in norm."""
     import torch
     g = torch.Generator(device="cuda")
@@ -559,6 +559,33 @@ def test_lora_grad_column_tiles(attt, count):
 
     ps = [dict(x=rnd(rows, d_in), dy=rnd(rows, d_out), A=rnd(r, d_in), B=rnd(d_out, r), scale=0.8,
                dA=torch.zeros(r, d_in, device="cuda"), dB=torch.zeros(d_out, r, device="cuda")) for _ in range(count)]
+    attt.lora_grad(ps)
+    for p in ps:
+        x, dy, A, B = (p[k].double() for k in ("x", "dy", "A", "B"))
+        for got, want in ((p["dA"], 0.8 * (dy @ B).t() @ x), (p["dB"], 0.8 * dy.t() @ (x @ A.t()))):
+            assert float((got.double() - want).norm() / want.norm()) < 1e-5
+
+
+@pytest.mark.parametrize("ranks", [(20,), (64,), (48,), (64, 8, 33, 16)])
+def test_lora_grad_wide_column_tiles(attt, ranks):
+    """Pass 2 on 128 columns a workgroup (16 jobs of 4 row ranges and 9 column tiles fill two per CU): two,
+    three and four rank tiles a job, and jobs of fewer tiles beside those of four; the last columns end
+    inside a tile, the rows inside a step. q and k share their input. Bound as above."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(18)
+    rows, d_in, d_out = 2000, 1032, 1096
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=g, device="cuda").bfloat16()
+
+    ps = []
+    for i in range(9):
+        r = ranks[i % len(ranks)]
+        x = ps[-1]["x"] if i == 4 else rnd(rows, d_in)
+        ps.append(dict(x=x, dy=rnd(rows, d_out), A=rnd(r, d_in), B=rnd(d_out, r), scale=0.8,
+                       dA=torch.zeros(r, d_in, device="cuda"), dB=torch.zeros(d_out, r, device="cuda")))
+    note(f"lora grad on 128 columns, ranks {ranks}")
     attt.lora_grad(ps)
     for p in ps:
         x, dy, A, B = (p[k].double() for k in ("x", "dy", "A", "B"))
