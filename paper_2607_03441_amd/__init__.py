@@ -517,6 +517,8 @@ def lora_workspace_size(problems, dtype):
 def lora_grad(problems, workspace=None):
     """LoRA dA / dB for a group of projections, accumulated (+=) into each problem's float32
     dA [r, d_in] and dB [d_out, r]. Each problem: dict(x, dy, A, B, dA, dB, scale)."""
+    if not problems:
+        return
     _check(_native().lora_grad(problems, workspace))
 
 

@@ -85,11 +85,14 @@ int64_t dim(const at::Tensor& t, int64_t d) {
 
 PyObject *k_x, *k_dy, *k_A, *k_B, *k_dA, *k_dB, *k_y, *k_scale, *k_param, *k_grad, *k_param_bf16;
 
-float scale_of(Held& held, PyObject* map) {
-  const double v = PyFloat_AsDouble(item(held, map, k_scale));
-  if (v == -1.0 && PyErr_Occurred()) throw PyError{};
-  return (float)v;
+// What float() takes, a number's text too; a TypeError for the rest.
+float number(Held& held, PyObject* o) {
+  PyObject* f = PyNumber_Float(o);
+  if (!f && PyErr_ExceptionMatches(PyExc_ValueError)) PyErr_Format(PyExc_TypeError, "%R is not a number", o);
+  return (float)PyFloat_AS_DOUBLE(held.keep(f));
 }
+
+float scale_of(Held& held, PyObject* map) { return number(held, item(held, map, k_scale)); }
 
 // The library plans, launches and, the first time, loads its code: other Python threads run meanwhile. The
 // tensors stay held, and nothing of Python is touched.
@@ -165,10 +168,10 @@ PyObject* lora_grad(PyObject* args) {
 // lora_sgd_step(params, lr, zero_grad) -> status
 PyObject* lora_sgd_step(PyObject* args) {
   Held held;
-  PyObject* seq;
-  double lr;
+  PyObject *seq, *lr_obj;
   int zero;
-  if (!PyArg_ParseTuple(args, "Odp", &seq, &lr, &zero)) throw PyError{};
+  if (!PyArg_ParseTuple(args, "OOp", &seq, &lr_obj, &zero)) throw PyError{};
+  const float lr = number(held, lr_obj);
   PyObject* f = list(held, seq);
   const Py_ssize_t n = PyTuple_GET_SIZE(f);
   std::vector<attt_lora_param> v(n);
@@ -188,7 +191,7 @@ PyObject* lora_sgd_step(PyObject* args) {
     v[i] = {static_cast<float*>(P.data_ptr()), static_cast<float*>(G.data_ptr()), copy, P.numel()};
   }
   void* s = stream();
-  return PyLong_FromLong(without_gil([&] { return attt_lora_sgd_step(v.data(), (int32_t)n, (float)lr, zero, s); }));
+  return PyLong_FromLong(without_gil([&] { return attt_lora_sgd_step(v.data(), (int32_t)n, lr, zero, s); }));
 }
 
 // lora_forward(problems) -> status

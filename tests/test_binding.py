@@ -120,3 +120,20 @@ def test_other_threads_run_during_a_call():
     t.join()
     at = [begin] + [x for x in ticks if begin < x < end] + [end]
     assert max(b - a for a, b in zip(at, at[1:])) < 0.5 * (end - begin)
+
+
+def test_numbers_as_float_takes_them():
+    """scale is what float() makes of it, and nothing but problems is nothing to do."""
+    import numpy as np
+    want = attt.lora_workspace_size([FULL], attt.BF16)
+    for scale in ("2.0", " 1e-3 ", np.float32(2), np.array(0.5), torch.tensor(2.0), True):
+        assert attt.lora_workspace_size([dict(FULL, scale=scale)], attt.BF16) == want
+    for bad in ("two", None, [1.0]):
+        with pytest.raises(TypeError):
+            attt.lora_workspace_size([dict(FULL, scale=bad)], attt.BF16)
+    with pytest.raises(attt.AtttError):
+        attt.lora_workspace_size([dict(FULL, scale="inf")], attt.BF16)
+    with pytest.raises(ValueError):                                       # the device, not the number
+        attt.lora_sgd_step([dict(param=X, grad=X)], "0.1")
+    for nothing in (None, (), []):
+        assert attt.lora_grad(nothing) is None
