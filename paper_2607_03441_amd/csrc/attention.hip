@@ -4,7 +4,7 @@
 // accumulation. With S = scale Q K^T, P = softmax(S) over the allowed keys, O = P V:
 //   D = rowsum(dO * O),  dP = dO V^T,  dS = P * (dP - D),
 //   dQ = scale dS K,  dK = scale dS^T Q,  dV = P^T dO.
-// Three kernels, each recomputing S from Q and K on v_mfma_f32_16x16x32_bf16 over blocks of 64
+// Three passes, each recomputing S from Q and K on v_mfma_f32_16x16x32_bf16 over blocks of 64
 // keys, 256 threads (four waves of 16 rows, or of 32 query rows), blocks in the causal order with
 // the longest rows first, the next block's global loads in flight while the current one computes:
 //   attn_fwd_stats_kernel  per (query head, 64- or 128-query block): lse and D (online softmax; D as
@@ -15,11 +15,10 @@
 //   attn_dkdv_short_kernel the same for a 64-key block with half the threads and LDS, where walks are short
 //   attn_dq_kernel         per (query head, 64- or 128-query block): dQ over the allowed key blocks
 // The operand that stays (a wave's 16 or 32 queries, or its keys) is held in registers, or for
-// attn_dkdv_kernel in LDS, as the B operand of the score products, so each lane ends up with scores of its
-// own rows. The
-// probabilities (or dS) of that row then enter the second product (P^T dO, dS^T Q, dS K)
-// directly as the A operand: the contraction index is the one the lane's registers run over,
-// in the order they hold it, and the B operand is read in the same order from the row-major LDS
+// attn_dkdv_kernel in LDS, as the B operand of the score products, so each lane ends up with scores
+// of its own rows. The probabilities (or dS) of those rows then enter the second product (P^T dO,
+// dS^T Q, dS K) directly as the A operand: the contraction index is the one the lane's registers run
+// over, in the order they hold it, and the B operand is read in the same order from the row-major LDS
 // tile with transposing reads (ds_read_tr16_b64). Every block goes to LDS once, row-major, with
 // 16-byte stores, into one of two buffers (one barrier per block). Blocks strictly below the
 // diagonal skip the causal and ragged-row masks.
@@ -44,7 +43,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // LDS: two buffers, so that the next block is stored while the current one is read and a step
 // needs one barrier. A buffer of the per-query kernels holds the K and V tiles; one of the
-// per-key kernel holds the Q and dO tiles, then lse and D of the block's 64 queries.
+// per-key kernels holds the Q and dO tiles, then lse and D of the block's 64 queries.
 constexpr int kTileBytes = BLK * PR * 2;
 constexpr int kKvBuf = 2 * kTileBytes;
 constexpr int kQoBuf = 2 * kTileBytes + 2 * BLK * 4;
@@ -76,14 +75,14 @@ __device__ __forceinline__ void attn_locate(const AttnBatch& b, int heads, bool 
 
 }  // namespace
 
-// This wave's 16 keys as MFMA B operands over the head dimension: lane (l16, q4) holds key
-// `key` (its own) at columns 32 s + 8 q4 .. +7 for s = 0..3. Keys at or past nvalid read as zero.
-__device__ __forceinline__ void load_key_frags(bf16x8 (&f)[4], const bf16_t* src, int64_t stride, int key,
+// This wave's 16 queries (or keys) as MFMA B operands over the head dimension: lane (l16, q4) holds row
+// `row` (its own) at columns 32 s + 8 q4 .. +7 for s = 0..3. Rows at or past nvalid read as zero.
+__device__ __forceinline__ void load_row_frags(bf16x8 (&f)[4], const bf16_t* src, int64_t stride, int row,
                                                int nvalid, int q4) {
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (key < nvalid) v = *reinterpret_cast<const u32x4*>(src + (int64_t)key * stride + 32 * s + 8 * q4);
+    if (row < nvalid) v = *reinterpret_cast<const u32x4*>(src + (int64_t)row * stride + 32 * s + 8 * q4);
     f[s] = __builtin_bit_cast(bf16x8, v);
   }
 }
@@ -163,8 +162,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_stats_kernel(AttnArgs a, Attn
 #pragma unroll
   for (int c = 0; c < QT; ++c) {
     const int qry = 16 * QT * w + 16 * c + l16;
-    load_key_frags(qf[c], a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
-    load_key_frags(of[c], a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
+    load_row_frags(qf[c], a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
+    load_row_frags(of[c], a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
   }
   const float sl = a.scale * kLog2e;
   // per query tile: running max (base 2, the same in the query's four lanes), and this lane's
@@ -305,7 +304,7 @@ __host__ __device__ __forceinline__ int whole_pieces(int L, int g, int split, in
 // other's softmax, took 1594 -> 1558 us. 8192 rows, 32 heads over 8: 1726 -> 1558 us.
 template <int KT>
 __global__ __launch_bounds__(512, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch b) {
-  constexpr int KBLK = 64 * KT;
+  constexpr int KEYS = 64 * KT;
   int ei = 0;
   while (ei + 1 < b.count && b.e[ei + 1].wg_begin <= (int)blockIdx.x) ++ei;
   const AttnEp E = b.e[ei];
@@ -332,7 +331,7 @@ __global__ __launch_bounds__(512, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch
     }
     kb = c + m * kb;
   }
-  const int k0 = kb * KBLK, nk = min(KBLK, E.L - k0);
+  const int k0 = kb * KEYS, nk = min(KEYS, E.L - k0);
   const int nqb = (E.L + BLK - 1) / BLK;
   // (query block, query head) steps: query blocks from the last down to the key block's first, the
   // group's query heads inside. Every workgroup of a key/value head walks the same blocks in the same
@@ -343,7 +342,7 @@ __global__ __launch_bounds__(512, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch
   if (i0 >= i1) return;  // a walk of whole pieces has no rest
   extern __shared__ __align__(16) uint8_t smem[];  // two buffers of [Q tile][dO tile][lse][D], the V tile
   bf16_t* Vs = reinterpret_cast<bf16_t*>(smem + 2 * kQoBuf);
-  bf16_t* Ks = Vs + KBLK * PR;
+  bf16_t* Ks = Vs + KEYS * PR;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = w & 3, qw = w >> 2;
   const int l16 = lane & 15, q4 = lane >> 4;
@@ -509,8 +508,8 @@ __global__ __launch_bounds__(512, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch
   }
   // D of tile (c, j): lane (l16, q4), register r -> key 32 kw + 16 c + 4 q4 + r, column 16 j + l16
   const float os = qw ? 1.0f : a.scale;
-  float* part = b.part + (((int64_t)(E.blocks0 + kb) * a.kv_heads + kh) * b.splits + split) * (2 * KBLK * DH) +
-                qw * KBLK * DH;
+  float* part = b.part + (((int64_t)(E.blocks0 + kb) * a.kv_heads + kh) * b.splits + split) * (2 * KEYS * DH) +
+                qw * KEYS * DH;
   bf16_t* outp = qw ? a.dv : a.dk;
 #pragma unroll
   for (int c = 0; c < KT; ++c)
@@ -552,8 +551,8 @@ __global__ __launch_bounds__(256, 2) void attn_dkdv_short_kernel(AttnArgs a, Att
   const int key = 16 * w + l16;  // this lane's key in the block
   const int64_t qs = (int64_t)a.heads * DH, ks = (int64_t)a.kv_heads * DH;
   bf16x8 kf[4], vf[4];
-  load_key_frags(kf, a.k + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
-  load_key_frags(vf, a.v + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
+  load_row_frags(kf, a.k + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
+  load_row_frags(vf, a.v + ((int64_t)(E.row0 + k0) * a.kv_heads + kh) * DH, ks, key, nk, q4);
   f32x4 dk[8], dv[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) dk[j] = f32x4{0, 0, 0, 0}, dv[j] = f32x4{0, 0, 0, 0};
@@ -718,8 +717,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnArgs a, AttnBatch b
 #pragma unroll
   for (int c = 0; c < QT; ++c) {
     const int qry = wq + 16 * c + l16;
-    load_key_frags(qf[c], a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
-    load_key_frags(of[c], a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
+    load_row_frags(qf[c], a.q + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
+    load_row_frags(of[c], a.dout + ((int64_t)(E.row0 + q0) * a.heads + h) * DH, qs, qry, nq, q4);
     const int64_t t = (int64_t)h * a.N + E.row0 + q0 + qry;
     ls[c] = qry < nq ? a.lse[t] * kLog2e : INFINITY;  // absent queries: P = 0
     dd[c] = qry < nq ? a.dsum[t] : 0.0f;
@@ -844,13 +843,13 @@ static hipError_t launch_blocks(K kernel, LdsLimit& limit, int rows, int heads, 
 
 template <int KT>
 static hipError_t launch_keys(LdsLimit& limit, const AttnArgs& a, AttnBatch b, hipStream_t s) {
-  constexpr int KBLK = 64 * KT;
-  constexpr size_t lds = 2 * (size_t)kQoBuf + 2 * KBLK * PR * 2;
+  constexpr int KEYS = 64 * KT;
+  constexpr size_t lds = 2 * (size_t)kQoBuf + 2 * KEYS * PR * 2;
   static_assert(2 * kQoBuf >= 65536 && lds <= 160 * 1024, "the exchange at the end needs 64 KiB");
   if (hipError_t e = limit.raise((const void*)attn_dkdv_kernel<KT>, lds)) return e;
   int n = 0, blocks = 0;
   for (int i = 0; i < b.count; ++i) {
-    b.e[i].blocks = (b.e[i].L + KBLK - 1) / KBLK;
+    b.e[i].blocks = (b.e[i].L + KEYS - 1) / KEYS;
     b.e[i].blocks0 = blocks;
     b.e[i].wg_begin = n;
     blocks += b.e[i].blocks;
