@@ -871,15 +871,15 @@ hipError_t launch_attn(int kernel, const AttnArgs& a, const AttnBatch& b, hipStr
     return launch_blocks(attn_dkdv_short_kernel, limits[6], BLK, a.kv_heads, 2 * (size_t)kQoBuf, a, b, K_ATTN_DKDV, s);
   if (kernel == 1) return b.tiles == 1 ? launch_keys<1>(limits[4], a, b, s) : launch_keys<2>(limits[5], a, b, s);
   constexpr size_t lds = 2 * (size_t)kKvBuf;
-  // Two query tiles per wave where their workgroups fill 7/8 of the chip's two per CU; below that the longest
+  // Two query tiles per wave where their workgroups nearly fill the chip's two per CU; below that the longest
   // chain of key blocks is the time, and a step of one tile is the shorter one. One tile too where blocks of
-  // 128 queries are hardly fewer than those of 64 (short episodes). Statistics and dQ, one tile / two: 2048
-  // rows x 16 heads (256 two-tile workgroups) 51 + 61 / 63 + 71 us; 6636 x 8 (416) 169 + 220 / 203 + 244; 3970 x 8, three
-  // episodes (768) 196 + 241 / 157 + 216; 4518 x 20 (720) 190 + 237 / 143 + 190; 9 of 781 x 8 (504) 42 + 50 / 36 + 44; 64 of 64
-  // x 32 (2048 either way) 32 + 39 / 35 + 41.
+  // 128 queries are hardly fewer than those of 64 (short episodes). Statistics + dQ, one tile / two, by the
+  // two-tile workgroups: 256 (2048 rows x 16 heads) 51 + 61 / 63 + 71 us; 416 (6636 x 8) 169 + 220 / 203 + 244; 456
+  // (6540 x 8 and three short ones) 151 + 195 / 190 + 225; 504 (9 of 781 x 8) 42 + 50 / 36 + 44; 720 (4518 x 20)
+  // 190 + 237 / 143 + 190; 768 (3 of 3970 x 8) 196 + 241 / 157 + 216; 2048 of either (64 of 64 x 32) 32 + 39 / 35 + 41.
   int n1 = 0, n2 = 0;
   for (int i = 0; i < b.count; ++i) n1 += (b.e[i].L + 63) / 64, n2 += (b.e[i].L + 127) / 128;
-  const bool wide = (int64_t)n2 * a.heads > 448 && 8 * (int64_t)n1 > 9 * (int64_t)n2;
+  const bool wide = (int64_t)n2 * a.heads > 480 && 8 * (int64_t)n1 > 9 * (int64_t)n2;
   if (kernel == 0)
     return wide ? launch_blocks(attn_fwd_stats_kernel<2>, limits[0], 128, a.heads, lds, a, b, K_ATTN_FWD, s)
                 : launch_blocks(attn_fwd_stats_kernel<1>, limits[1], 64, a.heads, lds, a, b, K_ATTN_FWD, s);
