@@ -215,6 +215,7 @@ NgramPlan ngram_plan(const int64_t* hoff, const int64_t* toff, int32_t E, int32_
     int64_t parts, hist;
   };
   std::vector<Part> parts;
+  parts.reserve(E);
   int64_t work = 0;
   for (int32_t e = 0; e < E; ++e) {
     const int64_t L = toff[e + 1] - toff[e], H = hoff[e + 1] - hoff[e];
@@ -232,7 +233,8 @@ NgramPlan ngram_plan(const int64_t* hoff, const int64_t* toff, int32_t E, int32_
   if (work > 0 && !smallest) {
     const int64_t rounds = ceil_div(blocks(kMax), kRound);
     int64_t lo = std::min(kMax, std::max(kMin, ceil_div(work, rounds * kRound)));
-    for (int64_t hi = kMax; lo < hi;) {  // the shortest chunk with at most `rounds` rounds
+    // the shortest chunk with at most `rounds` rounds; where work is small the first tried already has
+    for (int64_t hi = blocks(lo) <= rounds * kRound ? lo : kMax; lo < hi;) {
       const int64_t mid = (lo + hi) / 2;
       if (blocks(mid) <= rounds * kRound) hi = mid;
       else lo = mid + 1;
