@@ -418,11 +418,12 @@ struct AttnSplit {
 // starts late (in the second half of the episodes); but no less than that walk alone, or than the rounds of
 // whole pieces; and each partial is written and read. Pieces that all run at once take the time of one.
 // The constants are fitted to 394 shapes (1-200 episodes of 20-131072 rows, 1-64 heads; rms errors 5-6%),
-// over which the choice takes 1.016 times the best candidate's time on average and at most 1.08 times that of
-// tiles 0, which was the only kernel before. Tiles 0 / 1 / 2 / best pieces / the choice, in us: 2048 rows, 16 heads over 4:
-// 279 / 237 / 336 / 76 / 76; 4096, 32 over 8: 572 / 508 / 660 / 394 / 394; 64 episodes of 64, 32 over 32: 46 / 70 / 87 / - /
-// 46; 2 of 1500, 40 over 8: 279 / 231 / 322 / 179 / 179; 8192, 32 over 8: 1660 / 1968 / 1442 / 1436 / 1442; 18 of up to 2210,
-// 4 over 4: 322 / 399 / 336 / - / 322.
+// over which the choice takes 1.02 times the best candidate's time on average and at most 1.08 times that of
+// tiles 0, the only kernel there was before the others. Tiles 0 / 1 / 2 / the choice, in us: 64 episodes of 64
+// rows, 32 heads over 32: 46 / 70 / 87 / 46; 18 of up to 2210, 4 over 4: 322 / 399 / 336 / 322; 8192 rows, 32 over 8: 1660 /
+// 1968 / 1442 / 1442; 2048, 16 over 4: 279 / 237 / 336 / 76 in 6 pieces; 4096, 32 over 8: 572 / 508 / 660 / 394 in 4;
+// 2 of 1500, 40 over 8: 279 / 231 / 322 / 183 in 4; 5522, 5 over 1: 947 / 784 / 1114 / 137 in 10. Far from the best: 7030, 4
+// over 2: 226 in 5 pieces, 170 in 4.
 struct AttnCost {
   double base, alone, step, wg, longest, late, part;
   double us(int64_t walk, int64_t late_walk, int64_t steps, int64_t wgs, int64_t rounds = 1) const {
