@@ -157,8 +157,8 @@ using I = std::integral_constant<int, N>;
 // below and rank 24 398, here 110 and 161; 187 and 500 with the kernel before.) Ranks of 32 and 64 alone need
 // 112 registers, but four waves per SIMD are one too many for them: 173 us at rank 32 there, 166 with three.
 // 16 x 512 rows of q, k, v and o (483 MB): 279 us with 64-row workgroups that recomputed U in eight
-// column splits and walked the rank per thread, 137 us now (3.5 TB/s); the decoding step of 16 episodes
-// 42 us in two launches, 17 in one.
+// column splits and walked the rank per thread, 132 us now (3.7 TB/s); the decoding step of 16 episodes
+// 42 us in two launches, 15 in one.
 template <int NU, bool kHigh, bool kAny, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, kHigh && !kAny ? 3 : 8))) void lora_fwd_kernel(
     LoraFwdBatch b, int grid) {
