@@ -417,13 +417,13 @@ struct AttnSplit {
 // the steps and of the workgroups' starts and ends, behind it parts of the longest walk and of the longest that
 // starts late (in the second half of the episodes); but no less than that walk alone, or than the rounds of
 // whole pieces; and each partial is written and read. Pieces that all run at once take the time of one.
-// The constants are fitted to 394 shapes (1-200 episodes of 20-131072 rows, 1-64 heads; rms errors 5-6%),
-// over which the choice takes 1.02 times the best candidate's time on average and at most 1.08 times that of
-// tiles 0, the only kernel there was before the others. Tiles 0 / 1 / 2 / the choice, in us: 64 episodes of 64
-// rows, 32 heads over 32: 46 / 70 / 87 / 46; 18 of up to 2210, 4 over 4: 322 / 399 / 336 / 322; 8192 rows, 32 over 8: 1660 /
-// 1968 / 1442 / 1442; 2048, 16 over 4: 279 / 237 / 336 / 76 in 6 pieces; 4096, 32 over 8: 572 / 508 / 660 / 394 in 4;
-// 2 of 1500, 40 over 8: 279 / 231 / 322 / 183 in 4; 5522, 5 over 1: 947 / 784 / 1114 / 137 in 10. Far from the best: 7030, 4
-// over 2: 226 in 5 pieces, 170 in 4.
+// The constants are fitted to 412 shapes (1-200 episodes of 20-131072 rows, 1-64 heads; rms errors 6%; tiles 1
+// with a margin of 3%), over which the choice takes 1.02 times the best candidate's time on average and at most
+// 1.08 times that of tiles 0, the only kernel there was before the others. Tiles 0 / 1 / 2 / the choice, in us: 64
+// episodes of 64 rows, 32 heads over 32: 46 / 70 / 87 / 46; 18 of up to 2210, 4 over 4: 322 / 399 / 336 / 322; 16 of
+// 4096, 32 over 8: 6554 / 8731 / 6325 / 6325; 8192 rows, 32 over 8: 1660 / 1968 / 1442 / 1442; 2048, 16 over 4: 279 /
+// 237 / 336 / 76 in 6 pieces; 2 of 1500, 40 over 8: 279 / 231 / 322 / 183 in 4; 5522, 5 over 1: 947 / 784 / 1114 / 137
+// in 10. Far from the best: 4096, 32 over 8: 446 in 7 pieces, 394 in 4; 7030, 4 over 2: 226 in 5, 170 in 4.
 struct AttnCost {
   double base, alone, step, wg, longest, late, part;
   double us(int64_t walk, int64_t late_walk, int64_t steps, int64_t wgs, int64_t rounds = 1) const {
@@ -431,7 +431,7 @@ struct AttnCost {
   }
 };
 constexpr AttnCost kAttnWalk[3] = {
-    {5.8, 2.17, 1.32, 3.0, 0.6, 0.7, 0}, {7.2, 1.8, 1.85, 5.4, 0.15, 0.54, 0}, {8.6, 2.56, 2.61, 6.1, 0.43, 0.78, 0}};
+    {5.8, 2.17, 1.42, 3.4, 0.36, 0.79, 0}, {7.4, 1.84, 2.0, 6.4, 0.03, 0.49, 0}, {8.6, 2.57, 2.8, 7.3, 0.19, 0.77, 0}};
 constexpr AttnCost kAttnPieces = {9.9, 2.61, 2.705, 1.6, 0.37, 0.46, 0.049};
 constexpr AttnCost kAttnPiecesAtOnce = {12.4, 2.57, 0, 0, 0, 0, 0.042};  // at most one workgroup per CU
 
@@ -479,9 +479,11 @@ AttnSplit attn_split(const int64_t* off, int32_t E, int32_t heads, int32_t kv_he
     wgs *= kv_heads;
     whole *= kv_heads;
     if (!even && wgs > 256) return;
-    // more than one round is the less certain estimate, and its workspace is larger: a margin of a tenth
+    // More than one round is the less certain estimate, and its workspace is larger: a margin, the more so
+    // where the second round is the last.
+    const double margin = 1.04 + 0.1 * std::max(0.0, 1.0 - (double)(wgs - 256) / 768);
     const double us = wgs <= 256 ? kAttnPiecesAtOnce.us(chunk, 0, 0, wgs)
-                                 : 1.1 * kAttnPieces.us(chunk, std::min(late, chunk), steps[2] * kv_heads, wgs, ceil_div(whole, 256));
+                                 : margin * kAttnPieces.us(chunk, std::min(late, chunk), steps[2] * kv_heads, wgs, ceil_div(whole, 256));
     if (us < best_us) {
       best_us = us;
       best.tiles = 2;

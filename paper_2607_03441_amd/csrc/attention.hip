@@ -536,8 +536,8 @@ __global__ __launch_bounds__(512, 2) void attn_dkdv_kernel(AttnArgs a, AttnBatch
 // dK += dS^T Q straight from those registers as the A operand: the contraction runs over the
 // queries, and the 8 values a lane holds per 32-query chunk (tile rows 4 q4 .. +3 of two tiles)
 // are its k slots; the B operand reads the transposed dO and Q tiles in the same query order.
-// A step takes a CU 1.36 us (1.34 per 64 keys of the 128-key kernel) and a workgroup's start and end 3.6
-// (6.5): 64 episodes of 64 rows, 32 heads over 32: 46 us against 70 and 87 for the kernel above on 64 and on
+// A step takes a CU 1.42 us (1.40 per 64 keys of the 128-key kernel) and a workgroup's start and end 3.4
+// (7.3): 64 episodes of 64 rows, 32 heads over 32: 46 us against 70 and 87 for the kernel above on 64 and on
 // 128 keys; 3 episodes of 1000 rows, 40 over 40: 124, 159 and 127; 8192 rows, 32 over 8: 1726 against 1509.
 __global__ __launch_bounds__(256, 2) void attn_dkdv_short_kernel(AttnArgs a, AttnBatch b) {
   int ei, kh, kb;
