@@ -1428,17 +1428,20 @@ extern "C" attt_status attt_lora_grad(const attt_lora_problem* problems, int32_t
       p1, [&](const LoraP1Job& J) { return J.rows_pad / (dtype == ATTT_BF16 ? kLoraP1Rows : kLoraP1RowsF32); },
       [&](const LoraP1Batch& b, int n) { return launch_lora_pass1(dtype, b.j[0].nt, b, n, ws, s); }, "lora_u_du");
   if (st) return st;
-  // Pass 2 in bf16 on 128 columns a workgroup where that leaves a launch two per CU, else on 64. 64 / 128 columns,
-  // by the workgroups of 128 per launch: 128 (64 problems of 600 x 1024 -> 1024) 81.3 / 94.6 us, 160 (58 of 2000 x 264
-  // -> 136) 97.5 / 105.7, 192 (8 episodes of 300 rows of 2048) 41.8 / 48.3, 512 (30 of 2000 x 1024 -> 1024) 71.1 / 68.1, 768
-  // (4 episodes of 1024 rows of 4096) 37.0 / 38.2, 939 (8 of 1000 rows of 5120) 110 / 101, 2304 (8192 rows of 4096) 70.3 / 64.5.
+  // Pass 2 in bf16 on 128 columns a workgroup where that leaves a launch two per CU and the call four, else on 64:
+  // a lone launch of fewer ends in a part-filled round (672 workgroups, one episode of 3124 rows of 3072: the
+  // call 74.7 us on 64, 76.0 on 128). 64 / 128 columns, by the workgroups of 128 per launch: 128 (64 problems of
+  // 600 x 1024 -> 1024) 81.3 / 94.6 us, 160 (58 of 2000 x 264 -> 136) 97.5 / 105.7, 192 (8 episodes of 300 rows of
+  // 2048) 41.8 / 48.3, 512 (30 of 2000 x 1024 -> 1024) 71.1 / 68.1, 768 (4 episodes of 1024 rows of 4096) 37.0 / 38.2,
+  // 939 (8 of 1000 rows of 5120) 110 / 101, 2304 (8192 rows of 4096) 70.3 / 64.5.
+  auto wide = [](const LoraP2Job* J, size_t n) {
+    int64_t w = 0;
+    for (size_t i = 0; i < n; ++i) w += J[i].splits * ceil_div(J[i].cols, 2 * kLoraColTile);
+    return w;
+  };
+  const bool many = dtype == ATTT_BF16 && wide(p2.data(), p2.size()) >= 1024;
   st = lora_launch_all(
-      p2,
-      [&](const LoraP2Job* J, int n) {
-        int64_t wide = 0;
-        for (int i = 0; i < n; ++i) wide += J[i].splits * ceil_div(J[i].cols, 2 * kLoraColTile);
-        return dtype == ATTT_BF16 && wide >= 512 ? 2 * kLoraColTile : kLoraColTile;
-      },
+      p2, [&](const LoraP2Job* J, int n) { return many && wide(J, n) >= 512 ? 2 * kLoraColTile : kLoraColTile; },
       [](const LoraP2Job& J, int col_tile) { return J.splits * (int)ceil_div(J.cols, col_tile); },
       [&](const LoraP2Batch& b, int n, int col_tile) { return launch_lora_pass2(dtype, col_tile, b, n, ws, s); }, "lora_dadb");
   if (st) return st;

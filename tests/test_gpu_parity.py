@@ -568,8 +568,8 @@ def test_lora_grad_column_tiles(attt, count):
 
 @pytest.mark.parametrize("ranks", [(20,), (64,), (48,), (64, 8, 33, 16)])
 def test_lora_grad_wide_column_tiles(attt, ranks):
-    """Pass 2 on 128 columns a workgroup (16 jobs of 4 row ranges and 9 column tiles fill two per CU): two,
-    three and four rank tiles a job, and jobs of fewer tiles beside those of four; the last columns end
+    """Pass 2 on 128 columns a workgroup (16 jobs of 4 row ranges and 9 column tiles fill two per CU, 35 of
+    them four): two, three and four rank tiles a job, and jobs of fewer tiles beside those of four; the last columns end
     inside a tile, the rows inside a step. q and k share their input. Bound as above."""
     import torch
     g = torch.Generator(device="cuda")
@@ -580,7 +580,7 @@ def test_lora_grad_wide_column_tiles(attt, ranks):
         return torch.randn(shape, generator=g, device="cuda").bfloat16()
 
     ps = []
-    for i in range(9):
+    for i in range(18):
         r = ranks[i % len(ranks)]
         x = ps[-1]["x"] if i == 4 else rnd(rows, d_in)
         ps.append(dict(x=x, dy=rnd(rows, d_out), A=rnd(r, d_in), B=rnd(d_out, r), scale=0.8,
