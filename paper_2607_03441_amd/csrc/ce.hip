@@ -282,15 +282,13 @@ __global__ __launch_bounds__(256) void ce_fwd_f32_kernel(const float* __restrict
   for (int r = 0; r < 16; ++r)
     if (vb + mfma_row(r, lane) < V) mx = fmaxf(mx, acc[r]);
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  const float m0 = mx != -INFINITY ? mx : 0.0f;  // no finite maximum: -inf adds exp(-inf) = 0, a NaN itself
   float s = 0.0f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int v = vb + mfma_row(r, lane);
     if (v < V) {
-      if (mx != -INFINITY)
-        s += expf(acc[r] - mx);
-      else if (acc[r] != acc[r])
-        s = acc[r];
+      s += expf(acc[r] - m0);
       if (v == y) label_logit[row] = acc[r];
     }
   }
